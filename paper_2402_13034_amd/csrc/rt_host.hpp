@@ -223,10 +223,6 @@ bool is_device_ptr(const void* p);
 void sort_keys(Ctx& c, uint64_t* in, uint64_t* out, int64_t n, int words, int begin_bit, int end_bit, hipStream_t st);
 // unique of sorted keys of `words` words; count written to device int64
 void unique_keys(Ctx& c, const uint64_t* in, uint64_t* out, int64_t n, int words, int64_t* d_count, hipStream_t st);
-void sort_u64(Ctx& c, uint64_t* keys, int64_t n, int end_bit, hipStream_t st);
-void sort_u64_into(Ctx& c, uint64_t* keys_in, uint64_t* keys_out, int64_t n, int end_bit, hipStream_t st);
-// unique of sorted keys; count written to device int64
-void unique_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t n, int64_t* d_count, hipStream_t st);
 // exclusive scan of uint8 flags into int64 offsets; total written to d_total
 void scan_flags(Ctx& c, const uint8_t* flags, int64_t* offsets, int64_t n, int64_t* d_total,
                 hipStream_t st);

@@ -1,8 +1,8 @@
 // Karras (HPG 2012) node construction: for internal node i of a binary radix
 // tree over n sorted, unique keys of W 64-bit words (word W-1 the most
 // significant), find its key range and split and return its children (>= 0
-// internal node, < 0 leaf ~index).  Shared by the build kernel and its
-// host-side test.
+// internal node, < 0 leaf ~index) and, where asked for, the first and last
+// leaf below it.  Shared by the build kernel and its host-side test.
 #pragma once
 #include <stdint.h>
 
@@ -36,7 +36,8 @@ RT_HD inline int lbvh_delta(const uint64_t* k, int64_t n, int64_t i, int64_t j)
 }
 
 template <int W>
-RT_HD inline void lbvh_node(const uint64_t* keys, int64_t n, int64_t i, int32_t* cl, int32_t* cr)
+RT_HD inline void lbvh_node(const uint64_t* keys, int64_t n, int64_t i, int32_t* cl, int32_t* cr,
+                            int32_t* first = nullptr, int32_t* last = nullptr)
 {
     int d = (lbvh_delta<W>(keys, n, i, i + 1) - lbvh_delta<W>(keys, n, i, i - 1)) >= 0 ? 1 : -1;
     int dmin = lbvh_delta<W>(keys, n, i, i - d);
@@ -57,6 +58,8 @@ RT_HD inline void lbvh_node(const uint64_t* keys, int64_t n, int64_t i, int32_t*
     int64_t lo = i < j ? i : j, hi = i < j ? j : i;
     *cl = (lo == g) ? ~(int32_t)g : (int32_t)g;
     *cr = (hi == g + 1) ? ~(int32_t)(g + 1) : (int32_t)(g + 1);
+    if (first) *first = (int32_t)lo;
+    if (last) *last = (int32_t)hi;
 }
 
 }  // namespace rt

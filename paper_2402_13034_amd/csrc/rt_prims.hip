@@ -304,8 +304,17 @@ __global__ __launch_bounds__(SMALL_T) void k_sort_small(const uint64_t* in, uint
 // --------------------------------------------------------------------------
 constexpr int RS_T = 256, RS_KPT = 8, RS_TILE = RS_T * RS_KPT;
 
-// digit counts of one tile into cnt[digit * n_tiles + tile]
-template <int W>
+// Up to RS_SELF_TILES tiles every scatter block sums the count table itself
+// (rows of 256 counts per tile, read once per block), so a pass is two
+// launches instead of five; beyond, the table is scanned by kernels of its own
+// (the sums grow with the square of the tile count).  98 tiles (200 000
+// two-word keys): 19 us a pass against 27; at 529 tiles the sums would read
+// 286 MB a pass.
+constexpr int RS_SELF_TILES = 128;
+
+// digit counts of one tile into cnt[digit * n_tiles + tile], or
+// cnt[tile * 256 + digit] for the scatter that sums them itself
+template <int W, bool SELF>
 __global__ __launch_bounds__(RS_T) void k_rs_count(const uint64_t* keys, int64_t n, int shift, int end,
                                                    unsigned* cnt, int n_tiles)
 {
@@ -325,19 +334,33 @@ __global__ __launch_bounds__(RS_T) void k_rs_count(const uint64_t* keys, int64_t
         }
     }
     __syncthreads();
-    cnt[(int64_t)t * n_tiles + blockIdx.x] = h[t];
+    cnt[SELF ? (int64_t)blockIdx.x * 256 + t : (int64_t)t * n_tiles + blockIdx.x] = h[t];
 }
 
 // keys of one tile to their places: start[digit * n_tiles + tile] (the scanned
-// counts) plus the rank among the tile's earlier keys with that digit
-template <int W>
+// counts; SELF: the counts, summed here) plus the rank among the tile's
+// earlier keys with that digit
+template <int W, bool SELF>
 __global__ __launch_bounds__(RS_T) void k_rs_scatter(const uint64_t* keys, uint64_t* out, int64_t n, int shift,
                                                      int end, const unsigned* start, int n_tiles)
 {
     __shared__ unsigned wc[RS_T / 64][256];
     __shared__ unsigned run[256];
     const int t = (int)threadIdx.x, wave = t >> 6;
-    run[t] = start[(int64_t)t * n_tiles + blockIdx.x];
+    if (SELF) {
+        __shared__ unsigned wsum[RS_T / 64];
+        unsigned before = 0, all = 0;   // this digit's keys in earlier tiles, in every tile
+#pragma unroll 8
+        for (int q = 0; q < n_tiles; ++q) {
+            const unsigned x = start[q * 256 + t];
+            before += q < (int)blockIdx.x ? x : 0u;
+            all += x;
+        }
+        unsigned tot;
+        run[t] = block_exclusive_add<unsigned, RS_T>(all, wsum, &tot) + before;
+    } else {
+        run[t] = start[(int64_t)t * n_tiles + blockIdx.x];
+    }
     const int64_t base = (int64_t)blockIdx.x * RS_TILE;
     for (int j = 0; j < RS_KPT; ++j) {
         const int64_t i = base + j * RS_T + t;
@@ -389,15 +412,26 @@ static void sort_keys_w(Ctx& c, uint64_t* in, uint64_t* out, int64_t n, int begi
     if (n >= ((int64_t)1 << 32)) throw inval_error("too many keys to sort");
     const int n_tiles = (int)((n + RS_TILE - 1) / RS_TILE);
     const int64_t table = (int64_t)256 * n_tiles;
-    Scratch cnt(c, sizeof(unsigned) * (size_t)table, st), start(c, sizeof(unsigned) * (size_t)table, st);
+    const bool self = n_tiles <= RS_SELF_TILES;
+    Scratch cnt(c, sizeof(unsigned) * (size_t)table, st), start(c, self ? 0 : sizeof(unsigned) * (size_t)table, st);
     uint64_t* bufs[2] = {in, out};
     int src = 0;
     for (int shift = begin; shift < end; shift += 8) {
-        hipLaunchKernelGGL((k_rs_count<W>), dim3((unsigned)n_tiles), dim3(RS_T), 0, st, bufs[src], n, shift, end,
+        if (self) {
+            hipLaunchKernelGGL((k_rs_count<W, true>), dim3((unsigned)n_tiles), dim3(RS_T), 0, st, bufs[src], n, shift,
+                               end, cnt.as<unsigned>(), n_tiles);
+            HIP_CHECK(hipGetLastError());
+            hipLaunchKernelGGL((k_rs_scatter<W, true>), dim3((unsigned)n_tiles), dim3(RS_T), 0, st, bufs[src],
+                               bufs[src ^ 1], n, shift, end, (const unsigned*)cnt.as<unsigned>(), n_tiles);
+            HIP_CHECK(hipGetLastError());
+            src ^= 1;
+            continue;
+        }
+        hipLaunchKernelGGL((k_rs_count<W, false>), dim3((unsigned)n_tiles), dim3(RS_T), 0, st, bufs[src], n, shift, end,
                            cnt.as<unsigned>(), n_tiles);
         HIP_CHECK(hipGetLastError());
         scan_exclusive<unsigned, unsigned>(c, cnt.as<unsigned>(), start.as<unsigned>(), table, (unsigned*)nullptr, st);
-        hipLaunchKernelGGL((k_rs_scatter<W>), dim3((unsigned)n_tiles), dim3(RS_T), 0, st, bufs[src], bufs[src ^ 1], n,
+        hipLaunchKernelGGL((k_rs_scatter<W, false>), dim3((unsigned)n_tiles), dim3(RS_T), 0, st, bufs[src], bufs[src ^ 1], n,
                            shift, end, (const unsigned*)start.as<unsigned>(), n_tiles);
         HIP_CHECK(hipGetLastError());
         src ^= 1;
@@ -414,24 +448,6 @@ void sort_keys(Ctx& c, uint64_t* in, uint64_t* out, int64_t n, int words, int be
         sort_keys_w<2>(c, in, out, n, begin_bit, end_bit, st);
     else
         throw inval_error("keys of 1 or 2 words");
-}
-
-// keys_in sorted into keys_out (keys_in is left in an unspecified order)
-void sort_u64_into(Ctx& c, uint64_t* keys_in, uint64_t* keys_out, int64_t n, int end_bit, hipStream_t st)
-{
-    sort_keys_w<1>(c, keys_in, keys_out, n, 0, end_bit, st);
-}
-
-void sort_u64(Ctx& c, uint64_t* keys, int64_t n, int end_bit, hipStream_t st)
-{
-    if (n <= 1) return;
-    if (n <= SMALL_WORDS) {   // in place: the workgroup holds every key in LDS
-        sort_keys_w<1>(c, keys, keys, n, 0, end_bit, st);
-        return;
-    }
-    Scratch tmp(c, sizeof(uint64_t) * (size_t)n, st);
-    sort_keys_w<1>(c, keys, tmp.as<uint64_t>(), n, 0, end_bit, st);
-    HIP_CHECK(hipMemcpyAsync(keys, tmp.p, sizeof(uint64_t) * (size_t)n, hipMemcpyDeviceToDevice, st));
 }
 
 // --------------------------------------------------------------------------
@@ -480,11 +496,6 @@ void unique_keys(Ctx& c, const uint64_t* in, uint64_t* out, int64_t n, int words
                                (const uint8_t*)flag.as<uint8_t>(), (const int64_t*)off.as<int64_t>(), out);
         HIP_CHECK(hipGetLastError());
     }
-}
-
-void unique_u64(Ctx& c, const uint64_t* in, uint64_t* out, int64_t n, int64_t* d_count, hipStream_t st)
-{
-    unique_keys(c, in, out, n, 1, d_count, st);
 }
 
 }  // namespace rt

@@ -1,0 +1,54 @@
+"""The scene build at the edges of its tiles: the node boxes (one workgroup per
+2048 leaves, the nodes above by leaf range) and the surface tables (lanes over
+a surface's triangles) give the walk that testing every triangle gives."""
+import numpy as np
+import pytest
+
+from paper_2402_13034_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2402_13034_amd import risrt
+    with risrt.Context(0) as c:
+        yield c
+
+
+def _trimmed(n_tri, sub):
+    """The lab room cut at n_tri triangles (whole surfaces renumbered)."""
+    p = synth.lab_room(nx=4, ny=4, sub=sub, n_rays=20_000, order=2)
+    sc = p.scene
+    assert sc.n_tri >= n_tri
+    surf = np.unique(sc.surf[:n_tri], return_inverse=True)[1].astype(np.int32)
+    p.scene = synth.Scene(sc.V, sc.T[:n_tri].copy(), sc.refl_re[:n_tri].copy(), sc.refl_im[:n_tri].copy(), surf)
+    return p
+
+
+# one tile less a leaf, a full one, one leaf and some leaves into the next, a third tile of one leaf; surfaces of
+# 18, 72 and 162 triangles (below, above and over twice a wave)
+@pytest.mark.parametrize("n_tri,sub", [(2, 3), (1908, 3), (2047, 6), (2048, 6), (2049, 6), (4097, 6), (5000, 9),
+                                       (17000, 9)])
+def test_build_equals_brute_force(ctx, n_tri, sub):
+    from paper_2402_13034_amd import risrt
+    prob = _trimmed(n_tri, sub)
+    print("case build", n_tri, sub, flush=True)
+    outs = []
+    for brute in (0, risrt.FLAG_BRUTE_FORCE):
+        scene, ris = risrt.upload_problem(ctx, prob)
+        ch, _ = risrt.trace_problem(ctx, prob, scene, ris,
+                                    flags=risrt.FLAG_KEEP_HITS | risrt.FLAG_KEEP_PATHS | brute)
+        E, H = ctx.channel_read(ch)
+        p = ctx.paths_read(ch)
+        outs.append((ctx.hits_read(ch, 0, 2), ctx.hits_read(ch, 1, 2), E, H, p["env"], p["ris_valid"]))
+        for h in (ch, scene, ris):
+            ctx.destroy(h)
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+    # the reflection triangle of every path: the grid lists against the oracle's scan of the whole surface
+    from oracle import oracle as O
+    with O.accelerated():
+        ref = O.trace(prob)
+    assert np.array_equal(outs[0][4]["tri"][:, :2], ref["env_tri"][:, :2])
+    assert np.array_equal(outs[0][5], ref["ris_valid"])

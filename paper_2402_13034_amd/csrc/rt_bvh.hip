@@ -1,17 +1,35 @@
-// Scene upload and linear BVH build on the device.
+// Scene upload and BVH build on the device.
 //
-// LBVH after Karras, "Maximizing Parallelism in the Construction of BVHs,
-// Octrees, and k-d Trees" (HPG 2012): 30-bit Morton codes of triangle
-// centroids with the triangle index appended (unique 62-bit keys), radix
-// sort, one thread per internal node finds its key range and split, then the
-// node boxes: bottom-up within tiles of leaves, by leaf range above them.
-// Node boxes are inflated so that the FP32 slab test is conservative with
+// Two trees over the same leaves:
+//
+//  * The linear BVH after Karras, "Maximizing Parallelism in the Construction
+//    of BVHs, Octrees, and k-d Trees" (HPG 2012): 63-bit Morton codes of
+//    triangle centroids with the triangle index as tie-break, radix sort, one
+//    thread per internal node finds its key range and split.  Its depth is the
+//    one a scene reports and is limited by, and the counting builds walk it
+//    (lbvh_nodes gives it its boxes then).
+//  * The tree every other walk takes: a linear BVH of each surface's triangles
+//    (Morton order within the surface), and above the surfaces' subtrees a
+//    binned surface-area split of their boxes.  Triangles of one surface are
+//    coplanar, so its subtree's boxes are flat, while a Morton order over the
+//    whole scene mixes triangles of different faces in one box: half the nodes
+//    visited (lab room: 41 -> 24 in relative box area, a wave of discovery rays
+//    visits 11 instead of 19 four-wide nodes per bounce, the path kernels run
+//    239 + 201 instead of 397 + 387 us; office floor 188 -> 99, 41 -> 26,
+//    discovery 8.6 + 11.6 instead of 11.4 + 15.8 ms).  Scenes of more than RT_TOP_MAX surfaces (the split runs in one
+//    workgroup), or where that tree came out deeper than the traversal stacks
+//    hold, take the linear BVH of the whole scene for it.
+//
+// Node boxes are computed bottom-up within tiles of leaves and by leaf range
+// above them, and are inflated so that the FP32 slab test is conservative with
 // respect to the exact ray/triangle formula.
 //
-// Layouts (leaf slot = rank of the triangle's key):
+// Layouts (leaf slot = rank of the triangle by surface, then Morton code):
 //   tri4  [3 * n]: (v0.xyz, id), (e1.xyz, surface), (e2.xyz, 0)
-//   nodes [4 * (n - 1)]: (loL.xyz, childL), (hiL.xyz, childR), (loR.xyz, -), (hiR.xyz, -)
-//   child >= 0: internal node; child < 0: leaf slot ~child.
+//   nodes [4 * ..]: (loL.xyz, childL), (hiL.xyz, childR), (loR.xyz, -), (hiR.xyz, -)
+//   child >= 0: internal node; child < 0: leaf slot ~child.  Nodes 0..n-2 are
+//   Karras nodes over the slots (those that span several surfaces are not
+//   reached), n-1.. the nodes above the surfaces.
 // Surfaces: s_tris groups triangle indices by surface (ascending), s_ptr the
 // CSR offsets, s_plane the plane of each surface's lowest-numbered triangle.
 #pragma clang fp contract(off)
@@ -170,23 +188,46 @@ __global__ void k_morton(const float4* cent, const unsigned* bounds, int64_t nt,
     keys[2 * t + 1] = (expand21(q[0]) << 2) | (expand21(q[1]) << 1) | expand21(q[2]);
 }
 
-struct Box6 {
-    float lo[3], hi[3];
-};
+// Keys of the leaf slots from the triangles in Morton order: word 1 surface
+// (21 bits) above the code's upper 43 bits, word 0 its lower 20 bits above the
+// triangle index (29 bits).  Sorted stably on the surface bits alone.  Without
+// surfaces above the Morton order (plain, or too many of them) they are all 0.
+constexpr int RT_TOP_MAX = 8192;   // surfaces the split above them takes
+constexpr uint64_t RT_KEY_TRI = (1ull << 29) - 1;
+constexpr int RT_KEY_SURF_SHIFT = 43;   // in word 1
+__global__ void k_slot_keys(const uint64_t* keys, const int32_t* surf, int64_t nt, const int32_t* n_surf_p, int plain,
+                            uint64_t* out)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nt) return;
+    const uint64_t t = keys[2 * i], code = keys[2 * i + 1];
+    const int32_t sf = surf[t];
+    const uint64_t sc = plain || *n_surf_p > RT_TOP_MAX ? 0ull : (uint64_t)(sf < 0 ? 0 : (sf >= nt ? nt - 1 : sf));
+    out[2 * i] = ((code & 0xfffffull) << 29) | t;
+    out[2 * i + 1] = (sc << RT_KEY_SURF_SHIFT) | (code >> 20);
+}
+
+// Is there a tree above the surfaces' subtrees?  (Every id used: an unused one
+// is reported after the build.)
+__device__ __forceinline__ bool top_used(int n_surf, int seen, int plain)
+{
+    return !plain && n_surf >= 2 && n_surf <= RT_TOP_MAX && seen == n_surf;
+}
 
 __device__ __forceinline__ int64_t clamp_index(int32_t v, int64_t n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
 
 // Leaf data in sorted order.  Box padding: 1e-5 of the scene extent + 1e-6 m
 // + 1e-5 |x| (indices are clamped: malformed input is reported after the build).
 __global__ void k_leaves(const uint64_t* keys, const float* V, const int32_t* T, const int32_t* surf, int64_t nv,
-                         int64_t nt, const unsigned* bounds, float4* tri4, float* lbox)
+                         int64_t nt, const unsigned* bounds, float4* tri4, float* lbox, int32_t* tslot)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nt) return;
     float ext = 0.0f;
     for (int k = 0; k < 3; ++k) ext = fmaxf(ext, ord2f(bounds[9 + k]) - ord2f(bounds[6 + k]));
     const float pad = 1e-5f * ext + 1e-6f;
-    int32_t t = (int32_t)keys[2 * i];   // word 0 of the sorted key: the triangle index
+    const int32_t t = (int32_t)(keys[2 * i] & RT_KEY_TRI);   // low bits of word 0: the triangle index
+    tslot[t] = (int32_t)i;
     const float* a = V + 3 * clamp_index(T[3 * t + 0], nv);
     const float* b = V + 3 * clamp_index(T[3 * t + 1], nv);
     const float* c = V + 3 * clamp_index(T[3 * t + 2], nv);
@@ -206,23 +247,31 @@ __global__ void k_leaves(const uint64_t* keys, const float* V, const int32_t* T,
 constexpr int RT_REFIT_TILE = 2048;
 static_assert((RT_REFIT_TILE & (RT_REFIT_TILE - 1)) == 0, "tiles are found by division");
 
-// One thread per internal node: children, parent links, the leaf range below
-// the node; the nodes whose leaves span several refit tiles are listed (in no
-// fixed order) for k_refit_cross.
-__global__ void k_karras(const uint64_t* keys, int64_t n, int32_t* child, int32_t* parent_int,
-                         int32_t* parent_leaf, int2* range, int32_t* cross, int32_t* n_cross)
+// One thread per internal node and tree (blockIdx.y 0: the slots' tree, 1: the
+// scene's Morton tree): children and parent links; for the slots' tree also the
+// leaf range below the node, and the nodes whose leaves span several refit
+// tiles are listed (in no fixed order) for k_refit_cross.
+struct KarrasOut {
+    const uint64_t* keys;
+    int32_t* child;
+    int32_t* parent_int;
+    int32_t* parent_leaf;
+};
+__global__ void k_karras(KarrasOut slots, KarrasOut morton, int64_t n, int2* range, int32_t* cross, int32_t* n_cross)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n - 1) return;
-    if (i == 0) parent_int[0] = -1;   // the root; every other node and every leaf gets its parent below
+    const KarrasOut o = blockIdx.y == 0 ? slots : morton;
+    if (i == 0) o.parent_int[0] = -1;   // the root; every other node and every leaf gets its parent below
     int32_t cl, cr, first, last;
-    lbvh_node<2>(keys, n, i, &cl, &cr, &first, &last);
-    if (cl < 0) parent_leaf[~cl] = (int32_t)i;
-    else parent_int[cl] = (int32_t)i;
-    if (cr < 0) parent_leaf[~cr] = (int32_t)i;
-    else parent_int[cr] = (int32_t)i;
-    child[2 * i] = cl;
-    child[2 * i + 1] = cr;
+    lbvh_node<2>(o.keys, n, i, &cl, &cr, &first, &last);
+    if (cl >= 0) o.parent_int[cl] = (int32_t)i;
+    if (cr >= 0) o.parent_int[cr] = (int32_t)i;
+    o.child[2 * i] = cl;
+    o.child[2 * i + 1] = cr;
+    if (blockIdx.y != 0) return;
+    if (cl < 0) o.parent_leaf[~cl] = (int32_t)i;
+    if (cr < 0) o.parent_leaf[~cr] = (int32_t)i;
     range[i] = make_int2(first, last);
     if (first / RT_REFIT_TILE != last / RT_REFIT_TILE) cross[atomicAdd(n_cross, 1)] = (int32_t)i;
 }
@@ -381,21 +430,483 @@ __global__ __launch_bounds__(256) void k_refit_cross(const int32_t* cross, const
     }
 }
 
-// 4-wide nodes: every internal node of even depth lists its grandchildren
-// (a leaf child stands for itself).  Boxes are copied from the binary nodes.
-// Also the tree depth: the deepest leaf lies one below the deepest internal
-// node (a broken parent chain gives 2^20).
+// --------------------------------------------------------------------------
+// The tree above the surfaces: binned surface-area splits (Wald, "On fast
+// Construction of SAH-based Bounding Volume Hierarchies", RT 2007: bins along
+// the centroids' extent, cost = area x triangles on either side).  A wave
+// takes a range of surfaces: lane l weighs the split q % 10 + 1 of TOP_BINS
+// bins along axis q / 10, q = l % 32 (30 of 32 lanes), the two halves of the
+// wave take alternate surfaces, so one pass over the range prices all 30
+// splits with no atomics and no bin memory.  The work is small and serial
+// (about 20 instructions per surface and level, then a chain of reductions
+// per node), so what bounds it is latency: the boxes stay in LDS where they
+// fit (up to TOP_RES surfaces).  Ranges are split level by level in one
+// workgroup, large ones by all its waves together: up to TOP_LEAF surfaces to
+// the end, beyond until they hold at most TOP_LEAF, and those go one workgroup
+// each over the device: 106 surfaces 67 us, 1566 surfaces 175 + 116 us.
+// A range split before position m makes node base + m - 1 (every position
+// splits once), so the numbering needs no counter.
+// --------------------------------------------------------------------------
+constexpr int TOP_BINS = 11, TOP_LEAF = 256, TOP_T = 1024, TOP_RES = 2048, TOP_FT = 512;
+constexpr int TOP_Q = TOP_LEAF / 2;   // ranges of a level: of two surfaces and more, or of more than TOP_LEAF
+static_assert(RT_TOP_MAX / (TOP_LEAF + 1) <= TOP_Q, "a level's ranges fit the queue");
+
+struct TopOut {
+    float4* nodes;
+    int32_t* child;
+    int32_t* parent_int;
+    int32_t* root;
+    int64_t base;      // node index of split position 1
+};
+
+// child `ref` of side `side` of node `parent` (-1: the root)
+__device__ __forceinline__ void top_link(const TopOut& o, int parent, int side, int ref)
+{
+    if (parent < 0) {
+        *o.root = ref;
+    } else {
+        o.child[2 * (int64_t)parent + side] = ref;
+        ((int32_t*)o.nodes)[16 * (int64_t)parent + 4 * side + 3] = ref;
+    }
+    if (ref >= 0) o.parent_int[ref] = parent;
+}
+
+// The surfaces' boxes as two float4 each: lo.xyz and the triangle count, hi.xyz
+// and the subtree's reference (in LDS or global memory; the functions that take
+// them are inlined, so each use has its own kind of load).
+struct TopBoxes {
+    const float4* p;
+    __device__ __forceinline__ float4 get(int i) const { return p[i]; }
+};
+
+// one lane's price of its split: boxes and triangle counts left and right
+struct TopAcc {
+    float l[6], r[6], wl, wr;
+};
+__device__ __forceinline__ void top_clear(TopAcc& a)
+{
+    for (int k = 0; k < 3; ++k) {
+        a.l[k] = a.r[k] = 3e38f;
+        a.l[3 + k] = a.r[3 + k] = -3e38f;
+    }
+    a.wl = a.wr = 0.0f;
+}
+__device__ __forceinline__ void top_merge(TopAcc& a, const TopAcc& b)
+{
+    for (int k = 0; k < 3; ++k) {
+        a.l[k] = fminf(a.l[k], b.l[k]);
+        a.r[k] = fminf(a.r[k], b.r[k]);
+        a.l[3 + k] = fmaxf(a.l[3 + k], b.l[3 + k]);
+        a.r[3 + k] = fmaxf(a.r[3 + k], b.r[3 + k]);
+    }
+    a.wl += b.wl;
+    a.wr += b.wr;
+}
+// the other half of the wave's prices of the same splits
+__device__ __forceinline__ void top_merge_halves(TopAcc& a)
+{
+    TopAcc o;
+    for (int k = 0; k < 6; ++k) {
+        o.l[k] = __shfl_xor(a.l[k], 32, 64);
+        o.r[k] = __shfl_xor(a.r[k], 32, 64);
+    }
+    o.wl = __shfl_xor(a.wl, 32, 64);
+    o.wr = __shfl_xor(a.wr, 32, 64);
+    top_merge(a, o);
+}
+// Bin coordinate of a box along an axis: left of split s if below s.  `c`: the
+// extent of the doubled centres, three minima, three maxima.
+struct TopAxis {
+    int axis;
+    float c0, scale;
+    __device__ __forceinline__ TopAxis(int a, const float* c) : axis(a)
+    {
+        c0 = a == 0 ? c[0] : a == 1 ? c[1] : c[2];
+        const float ext = (a == 0 ? c[3] : a == 1 ? c[4] : c[5]) - c0;
+        scale = ext > 0.0f ? (float)TOP_BINS / ext : 0.0f;
+    }
+    __device__ __forceinline__ float bin(float4 lo, float4 hi) const
+    {
+        const float v = axis == 0 ? lo.x + hi.x : axis == 1 ? lo.y + hi.y : lo.z + hi.z;
+        return (v - c0) * scale;
+    }
+};
+
+// extent of the doubled centres over positions first, first + step, ... below b of every lane
+__device__ __forceinline__ void top_extent(const TopBoxes sb, const uint16_t* idx, int first, int b, int step, float* c)
+{
+    for (int k = 0; k < 3; ++k) {
+        c[k] = 3e38f;
+        c[3 + k] = -3e38f;
+    }
+    for (int i = first; i < b; i += step) {
+        const int s = idx[i];
+        const float4 lo = sb.get(2 * s), hi = sb.get(2 * s + 1);
+        const float v[3] = {lo.x + hi.x, lo.y + hi.y, lo.z + hi.z};
+        for (int k = 0; k < 3; ++k) {
+            c[k] = fminf(c[k], v[k]);
+            c[3 + k] = fmaxf(c[3 + k], v[k]);
+        }
+    }
+    for (int k = 0; k < 3; ++k) {
+        c[k] = -wave_max(-c[k]);
+        c[3 + k] = wave_max(c[3 + k]);
+    }
+}
+
+// every lane's price of its split over positions [a, b) in chunks of 64 taken `stride` apart
+__device__ __forceinline__ void top_price(const TopBoxes sb, const uint16_t* idx, int a, int b, int stride,
+                                          const float* c, TopAcc& acc)
+{
+    const int lane = threadIdx.x & 63, q = lane & 31, half = lane >> 5;
+    const TopAxis ax(min(q / 10, 2), c);
+    const float split = (float)(q % 10 + 1);
+    top_clear(acc);
+    for (int i0 = a; i0 < b; i0 += stride) {
+        const int n = min(64, b - i0);
+        // eight surfaces at a time, their reads in flight together (past the end: the last one, counted nowhere)
+        for (int j0 = half; j0 < n; j0 += 8) {
+            float4 lo[4], hi[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int s = idx[i0 + min(j0 + 2 * u, n - 1)];
+                lo[u] = sb.get(2 * s);
+                hi[u] = sb.get(2 * s + 1);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const bool in = j0 + 2 * u < n, below = ax.bin(lo[u], hi[u]) < split;
+                const bool left = in && below, right = in && !below;
+                const float m[6] = {lo[u].x, lo[u].y, lo[u].z, hi[u].x, hi[u].y, hi[u].z};
+                for (int k = 0; k < 3; ++k) {
+                    acc.l[k] = fminf(acc.l[k], left ? m[k] : 3e38f);
+                    acc.r[k] = fminf(acc.r[k], right ? m[k] : 3e38f);
+                    acc.l[3 + k] = fmaxf(acc.l[3 + k], left ? m[3 + k] : -3e38f);
+                    acc.r[3 + k] = fmaxf(acc.r[3 + k], right ? m[3 + k] : -3e38f);
+                }
+                acc.wl += left ? lo[u].w : 0.0f;
+                acc.wr += right ? lo[u].w : 0.0f;
+            }
+        }
+    }
+}
+
+// the node of split position m: its children's boxes and its link (lane 0)
+__device__ __forceinline__ void top_node(const TopOut& o, int m, int parent, int side, const float* l, const float* r)
+{
+    if ((threadIdx.x & 63) != 0) return;
+    const int id = (int)(o.base + m - 1);
+    float* nd = (float*)(o.nodes + 4 * (int64_t)id);   // the .w words are links
+    for (int k = 0; k < 3; ++k) {
+        nd[k] = l[k];
+        nd[4 + k] = l[3 + k];
+        nd[8 + k] = r[k];
+        nd[12 + k] = r[3 + k];
+    }
+    nd[11] = nd[15] = 0.0f;
+    top_link(o, parent, side, id);
+}
+
+// A range of two surfaces (about a third of all ranges): nothing to choose.
+__device__ __forceinline__ void top_pair(const TopBoxes sb, const uint16_t* idx, int a, int parent, int side,
+                                         const TopOut& o)
+{
+    const int s0 = idx[a], s1 = idx[a + 1];
+    const float4 l0 = sb.get(2 * s0), h0 = sb.get(2 * s0 + 1), l1 = sb.get(2 * s1), h1 = sb.get(2 * s1 + 1);
+    const float l[6] = {l0.x, l0.y, l0.z, h0.x, h0.y, h0.z}, r[6] = {l1.x, l1.y, l1.z, h1.x, h1.y, h1.z};
+    top_node(o, a + 1, parent, side, l, r);
+    if ((threadIdx.x & 63) == 0) {
+        const int id = (int)(o.base + a);
+        top_link(o, id, 0, __float_as_int(h0.w));
+        top_link(o, id, 1, __float_as_int(h1.w));
+    }
+}
+
+// One range [a, b) from its prices (halves merged): choose the cheapest split,
+// partition idx stably, write the node's boxes and its link.  Returns the
+// split position (strictly inside; the middle where no split has surfaces on
+// both sides).  All lanes of one wave.
+__device__ __forceinline__ int top_split(const TopBoxes sb, uint16_t* idx, uint16_t* tmp, int a, int b, int parent,
+                                         int side, const float* c, const TopAcc& acc, const TopOut& o)
+{
+    const int lane = threadIdx.x & 63, q = lane & 31;
+    auto area = [](const float* m) {
+        const float x = m[3] - m[0], y = m[4] - m[1], z = m[5] - m[2];
+        return x * y + y * z + z * x;
+    };
+    const float none = 3e38f;
+    float cost = q < 30 && acc.wl > 0.0f && acc.wr > 0.0f ? area(acc.l) * acc.wl + area(acc.r) * acc.wr : none;
+    if (!(cost < none)) cost = none;
+    const float best = -wave_max(-cost);
+    const bool by_price = best < none;
+    const int who = __ffsll((long long)__ballot(cost == best)) - 1;   // ties: the first split
+    const TopAxis ax(min((who & 31) / 10, 2), c);
+    const float split = (float)((who & 31) % 10 + 1);
+    int m = a + (b - a) / 2;
+    float l[6], r[6];
+    if (by_price) {
+        // stable partition: lefts move down in place, rights wait in tmp (the same positions, so that
+        // ranges split at the same time do not meet)
+        int nl = 0, nr = 0;
+        for (int i0 = a; i0 < b; i0 += 64) {
+            const bool in = i0 + lane < b;
+            const uint16_t s = in ? idx[i0 + lane] : (uint16_t)0;
+            const bool left = in && ax.bin(sb.get(2 * s), sb.get(2 * s + 1)) < split;
+            const unsigned long long ml = __ballot(left), mr = __ballot(in && !left);
+            const unsigned long long lt = (1ull << lane) - 1ull;
+            if (left) idx[a + nl + __popcll(ml & lt)] = s;
+            if (in && !left) tmp[a + nr + __popcll(mr & lt)] = s;
+            nl += (int)__popcll(ml);
+            nr += (int)__popcll(mr);
+        }
+        m = a + nl;
+        for (int i = lane; i < nr; i += 64) idx[m + i] = tmp[a + i];
+        for (int k = 0; k < 6; ++k) {
+            l[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(acc.l[k]), who));
+            r[k] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(acc.r[k]), who));
+        }
+    } else {
+        TopAcc t;
+        top_clear(t);
+        for (int i = a + lane; i < b; i += 64) {
+            const int s = idx[i];
+            const float4 lo = sb.get(2 * s), hi = sb.get(2 * s + 1);
+            const bool left = i < m;
+            const float v[6] = {lo.x, lo.y, lo.z, hi.x, hi.y, hi.z};
+            for (int k = 0; k < 3; ++k) {
+                t.l[k] = fminf(t.l[k], left ? v[k] : 3e38f);
+                t.r[k] = fminf(t.r[k], left ? 3e38f : v[k]);
+                t.l[3 + k] = fmaxf(t.l[3 + k], left ? v[3 + k] : -3e38f);
+                t.r[3 + k] = fmaxf(t.r[3 + k], left ? -3e38f : v[3 + k]);
+            }
+        }
+        for (int k = 0; k < 3; ++k) {
+            l[k] = -wave_max(-t.l[k]);
+            r[k] = -wave_max(-t.r[k]);
+            l[3 + k] = wave_max(t.l[3 + k]);
+            r[3 + k] = wave_max(t.r[3 + k]);
+        }
+    }
+    top_node(o, m, parent, side, l, r);
+    return m;
+}
+
+// A workgroup's shared state: up to CAP surfaces, the boxes of RES, T threads.
+template <int CAP, int RES, int T, int Q>
+struct TopShared {
+    static constexpr int NW = T / 64;
+    uint16_t idx[CAP], tmp[CAP];
+    float4 box[2 * RES];
+    TopAcc part[NW][32];
+    float ext[NW][6];
+    int4 queue[2][Q];
+    int nq[2], nfin;
+};
+
+// A barrier that orders LDS alone: the nodes written to memory are not read again here, and waiting for those
+// stores at every level would cost more than the level.
+__device__ __forceinline__ void top_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The range in queue[0] split level by level until its parts hold at most `leaf` surfaces.
+template <class Shared>
+__device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n, int leaf, int4* fin, const TopOut& o)
+{
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    constexpr int NW = Shared::NW, T = NW * 64;
+    // a part of a split range: split again, left to a wave, or one surface (its link)
+    auto hand_on = [&](int a, int b, int parent, int side, int to) {
+        if (b - a == 1)
+            top_link(o, parent, side, __float_as_int(sb.get(2 * sh.idx[a] + 1).w));
+        else if (b - a > leaf)
+            sh.queue[to][atomicAdd(&sh.nq[to], 1)] = make_int4(a, b, parent, side);
+        else
+            fin[atomicAdd(&sh.nfin, 1)] = make_int4(a, b, parent, side);
+    };
+    for (int cur = 0;; cur ^= 1) {
+        const int cnt = sh.nq[cur];
+        if (cnt == 0) break;
+        // few ranges: all waves price each together
+        const bool together = cnt <= 4 && n > 128 * cnt;
+        for (int e = together ? 0 : wave; e < cnt; e += together ? 1 : NW) {
+            const int4 it = sh.queue[cur][e];
+            if (it.y - it.x == 2) {
+                if (!together || wave == 0) top_pair(sb, sh.idx, it.x, it.z, it.w, o);
+                continue;
+            }
+            // one copy of the code for both (a cold instruction cache costs more than the arithmetic)
+            float c[6];
+            TopAcc acc;
+            top_extent(sb, sh.idx, it.x + (together ? (int)threadIdx.x : lane), it.y, together ? T : 64, c);
+            if (together) {
+                if (lane == 0)
+                    for (int k = 0; k < 6; ++k) sh.ext[wave][k] = c[k];
+                top_barrier();
+#pragma unroll 1
+                for (int w = 0; w < NW; ++w)
+                    for (int k = 0; k < 3; ++k) {
+                        c[k] = fminf(c[k], sh.ext[w][k]);
+                        c[3 + k] = fmaxf(c[3 + k], sh.ext[w][3 + k]);
+                    }
+            }
+            top_price(sb, sh.idx, it.x + (together ? 64 * wave : 0), it.y, together ? T : 64, c, acc);
+            top_merge_halves(acc);
+            if (together) {
+                if (lane < 32) sh.part[wave][lane] = acc;
+                top_barrier();
+                if (wave == 0) {
+#pragma unroll 1
+                    for (int w = 1; w < NW; ++w) top_merge(acc, sh.part[w][lane & 31]);
+                }
+            }
+            if (!together || wave == 0) {
+                const int m = top_split(sb, sh.idx, sh.tmp, it.x, it.y, it.z, it.w, c, acc, o);
+                if (lane == 0) {
+                    const int id = (int)(o.base + m - 1);
+                    hand_on(it.x, m, id, 0, cur ^ 1);
+                    hand_on(m, it.y, id, 1, cur ^ 1);
+                }
+            }
+            if (together) top_barrier();
+        }
+        top_barrier();
+        if (threadIdx.x == 0) sh.nq[cur] = 0;
+        top_barrier();
+    }
+}
+
+// Upper levels, one workgroup: the surfaces' subtree boxes into sb, ranges
+// split until they hold at most `leaf` surfaces; those go to fin (start, end,
+// parent, side) and the surfaces' order to order_out.
+__global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const int32_t* n_surf_p,
+                                                     const int32_t* seen_p, const int2* range, const float* lbox,
+                                                     float4* sb, int32_t* order_out, int4* fin, int32_t* n_fin,
+                                                     TopOut o)
+{
+    __shared__ TopShared<RT_TOP_MAX, TOP_RES, TOP_T, TOP_Q> sh;
+    const int n = *n_surf_p;
+    if (!top_used(n, *seen_p, 0)) return;   // the same for every thread
+    const bool resident = n <= TOP_RES;
+    const int leaf = n <= TOP_LEAF ? 1 : TOP_LEAF;
+    for (int s = threadIdx.x; s < n; s += TOP_T) {
+        // the surface's leaves are slots a..b-1; its subtree's node has index a or b - 1
+        const int a = s_ptr[s], b = s_ptr[s + 1];
+        float4 lo, hi;
+        int ref;
+        if (b - a == 1) {
+            ref = ~a;
+            const float* x = lbox + 6 * (int64_t)a;
+            lo = make_float4(x[0], x[1], x[2], 1.0f);
+            hi = make_float4(x[3], x[4], x[5], 0.0f);
+        } else {
+            const int2 ra = range[a];
+            ref = ra.x == a && ra.y == b - 1 ? a : b - 1;
+            const float4* nd = o.nodes + 4 * (int64_t)ref;
+            const float4 l0 = nd[0], l1 = nd[1], r0 = nd[2], r1 = nd[3];
+            lo = make_float4(fminf(l0.x, r0.x), fminf(l0.y, r0.y), fminf(l0.z, r0.z), (float)(b - a));
+            hi = make_float4(fmaxf(l1.x, r1.x), fmaxf(l1.y, r1.y), fmaxf(l1.z, r1.z), 0.0f);
+        }
+        hi.w = __int_as_float(ref);
+        if (leaf > 1) {
+            sb[2 * s] = lo;
+            sb[2 * s + 1] = hi;
+        }
+        if (resident) {
+            sh.box[2 * s] = lo;
+            sh.box[2 * s + 1] = hi;
+        }
+        sh.idx[s] = (uint16_t)s;
+    }
+    if (threadIdx.x == 0) {
+        sh.nq[0] = 1;
+        sh.nq[1] = 0;
+        sh.nfin = 0;
+        sh.queue[0][0] = make_int4(0, n, -1, 0);
+    }
+    __syncthreads();
+    if (resident)
+        top_levels(sh, TopBoxes{sh.box}, n, leaf, fin, o);
+    else
+        top_levels(sh, TopBoxes{sb}, n, leaf, fin, o);
+    if (leaf > 1)
+        for (int i = threadIdx.x; i < n; i += TOP_T) order_out[i] = sh.idx[i];
+    if (threadIdx.x == 0) *n_fin = sh.nfin;
+}
+
+// Lower levels: one workgroup per range of at most TOP_LEAF surfaces, split to the end.
+__global__ __launch_bounds__(TOP_FT) void k_top_finish(const int32_t* n_surf_p, const int32_t* seen_p,
+                                                       const float4* sb, const int32_t* order, const int4* fin,
+                                                       const int32_t* n_fin, TopOut o)
+{
+    __shared__ TopShared<TOP_LEAF, TOP_LEAF, TOP_FT, TOP_Q> sh;
+    if (!top_used(*n_surf_p, *seen_p, 0) || (int)blockIdx.x >= *n_fin) return;   // the same for every thread
+    const int4 root = fin[blockIdx.x];
+    const int a0 = root.x, cnt = root.y - a0;
+    if ((int)threadIdx.x < cnt) {
+        const int s = order[a0 + threadIdx.x];
+        sh.idx[threadIdx.x] = (uint16_t)threadIdx.x;
+        sh.box[2 * threadIdx.x] = sb[2 * s];
+        sh.box[2 * threadIdx.x + 1] = sb[2 * s + 1];
+    }
+    if (threadIdx.x == 0) {
+        sh.nq[0] = 1;
+        sh.nq[1] = 0;
+        sh.queue[0][0] = make_int4(0, cnt, root.z, root.w);
+    }
+    __syncthreads();
+    TopOut here = o;
+    here.base = o.base + a0;   // positions within the range; node indices take the range's start again
+    top_levels(sh, TopBoxes{sh.box}, cnt, 1, nullptr, here);
+}
+
+// 4-wide nodes: every reached internal node of even depth lists its
+// grandchildren (a leaf child stands for itself).  Boxes are copied from the
+// binary nodes.  Also the tree depth: the deepest leaf lies one below the
+// deepest internal node (a broken parent chain gives 2^20).
+// blockIdx.y 1: the Morton tree's depth, and its leaf links turned into slots.
+struct MortonTree {
+    const uint64_t* keys;
+    const int32_t* parent_int;
+    const int32_t* tslot;      // slot of each triangle
+    int32_t* child;
+    int32_t* maxd;
+};
 __global__ void k_node4(const int32_t* child, const int32_t* parent_int, const float4* nodes, const float4* tri4,
-                        int64_t ni, float4* node4, int32_t* maxd)
+                        const uint64_t* slot_keys, const int2* range, const int32_t* n_surf_p, const int32_t* seen_p,
+                        int plain, int64_t ni, int64_t ni_all, float4* node4, int32_t* maxd, MortonTree mt)
 {
     const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool live = n < ni;
+    const bool second = blockIdx.y != 0;
+    const int32_t* up = second ? mt.parent_int : parent_int;
+    bool live = n < ni;
+    if (!second && top_used(*n_surf_p, *seen_p, plain)) {
+        if (live) {   // a node over several surfaces is replaced by the tree above them
+            const int2 r = range[n];
+            live = slot_keys[2 * (int64_t)r.x + 1] >> RT_KEY_SURF_SHIFT ==
+                   slot_keys[2 * (int64_t)r.y + 1] >> RT_KEY_SURF_SHIFT;
+        } else {
+            live = n < ni + *n_surf_p - 1;
+        }
+    }
+    const int64_t lim = second ? ni : ni_all;
     int d = 0;
-    int32_t p = live ? parent_int[n] : -1;
-    for (; p >= 0 && p < ni && d < 4096; p = parent_int[p]) ++d;
+    int32_t p = live ? up[n] : -1;
+    for (; p >= 0 && p < lim && d < 4096; p = up[p]) ++d;
     const unsigned dl = !live ? 0u : (p != -1 ? (1u << 20) : (unsigned)d + 1u);
     const unsigned dm = wave_umax(dl);
-    if ((threadIdx.x & 63) == 0 && dm > 0) atomicMax(maxd, (int32_t)dm);
+    if ((threadIdx.x & 63) == 0 && dm > 0) atomicMax(second ? mt.maxd : maxd, (int32_t)dm);
+    if (second) {
+        if (live)
+            for (int side = 0; side < 2; ++side) {
+                const int32_t c = mt.child[2 * n + side];
+                if (c < 0) mt.child[2 * n + side] = ~mt.tslot[mt.keys[2 * (int64_t)(~c)]];
+            }
+        return;
+    }
     if (!live || (d & 1)) return;
     float lo[4][3], hi[4][3];
     int32_t ref[4];
@@ -639,8 +1150,111 @@ void scene_normals(Ctx& c, Scene& s, hipStream_t st)
     HIP_CHECK(hipGetLastError());
 }
 
-void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T, int64_t nt,
-                 const int32_t* surf, const float* rr, const float* ri, hipStream_t st)
+// Boxes of the scene's Morton tree for a counting walk (nodes as SceneView
+// lays them out, root 0), made on `st` when one is asked for: leaf boxes from
+// the nodes that hold them, then the leaf-to-root walk with device-wide
+// arrival counts (fences at every level: slow, and only taken here).
+__global__ void k_leaf_boxes(const float4* nodes, int64_t n_nodes, int64_t nt, float* lbox)
+{
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= n_nodes) return;
+    for (int side = 0; side < 2; ++side) {
+        const int32_t ref = ((const int32_t*)nodes)[16 * n + 4 * side + 3];
+        if (ref >= 0 || ~ref >= nt) continue;
+        const float4 l = nodes[4 * n + 2 * side], h = nodes[4 * n + 2 * side + 1];
+        float* b = lbox + 6 * (int64_t)(~ref);
+        b[0] = l.x;
+        b[1] = l.y;
+        b[2] = l.z;
+        b[3] = h.x;
+        b[4] = h.y;
+        b[5] = h.z;
+    }
+}
+
+__global__ void k_parents(const int32_t* child, int64_t ni, int32_t* parent_int, int32_t* parent_leaf)
+{
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n >= ni) return;
+    if (n == 0) parent_int[0] = -1;
+    for (int side = 0; side < 2; ++side) {
+        const int32_t c = child[2 * n + side];
+        if (c < 0)
+            parent_leaf[~c] = (int32_t)n;
+        else
+            parent_int[c] = (int32_t)n;
+    }
+}
+
+__device__ __forceinline__ void load_box(int32_t c, const float* lbox, const float* ibox, float* b)
+{
+    const volatile float* src = c < 0 ? (const volatile float*)(lbox + 6 * (int64_t)(~c))
+                                      : (const volatile float*)(ibox + 6 * (int64_t)c);
+    for (int k = 0; k < 6; ++k) b[k] = src[k];
+}
+
+__global__ void k_refit(const int32_t* child, const int32_t* parent_int, const int32_t* parent_leaf,
+                        const float* lbox, float* ibox, int32_t* flags, float4* nodes, int64_t n)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    int32_t p = parent_leaf[i];
+    while (p >= 0 && p < n - 1) {
+        __threadfence();
+        int old = __hip_atomic_fetch_add(&flags[p], 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if (old == 0) return;
+        int32_t cl = child[2 * p], cr = child[2 * p + 1];
+        float bl[6], br[6];
+        load_box(cl, lbox, ibox, bl);
+        load_box(cr, lbox, ibox, br);
+        nodes[4 * (int64_t)p + 0] = make_float4(bl[0], bl[1], bl[2], __int_as_float(cl));
+        nodes[4 * (int64_t)p + 1] = make_float4(bl[3], bl[4], bl[5], __int_as_float(cr));
+        nodes[4 * (int64_t)p + 2] = make_float4(br[0], br[1], br[2], 0.0f);
+        nodes[4 * (int64_t)p + 3] = make_float4(br[3], br[4], br[5], 0.0f);
+        volatile float* dst = ibox + 6 * (int64_t)p;
+        for (int k = 0; k < 3; ++k) {
+            dst[k] = fminf(bl[k], br[k]);
+            dst[3 + k] = fmaxf(bl[3 + k], br[3 + k]);
+        }
+        __threadfence();
+        p = parent_int[p];
+    }
+}
+
+__global__ void k_zero_i32(int32_t* p, int64_t n)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
+void lbvh_nodes(Ctx& c, const Scene& s, Scratch& nodes, hipStream_t st)
+{
+    const int64_t nt = s.n_tri, ni = nt - 1;
+    if (ni <= 0) return;
+    const int B = 256;
+    nodes = Scratch(c, sizeof(float4) * 4 * (size_t)ni, st);
+    Scratch lbox(c, sizeof(float) * 6 * (size_t)nt, st), ibox(c, sizeof(float) * 6 * (size_t)ni, st),
+        pint(c, sizeof(int32_t) * (size_t)ni, st), pleaf(c, sizeof(int32_t) * (size_t)nt, st),
+        flags(c, sizeof(int32_t) * (size_t)ni, st);
+    hipLaunchKernelGGL(k_zero_i32, dim3(blocks_for(ni, B)), dim3(B), 0, st, flags.as<int32_t>(), ni);
+    HIP_CHECK(hipGetLastError());
+    // every leaf is an entry of a node below the surfaces' roots, or of one above them
+    const int64_t n_nodes = ni + (s.root >= ni ? s.n_surf - 1 : 0);
+    hipLaunchKernelGGL(k_leaf_boxes, dim3(blocks_for(n_nodes, B)), dim3(B), 0, st, s.nodes.as<float4>(), n_nodes, nt,
+                       lbox.as<float>());
+    HIP_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(k_parents, dim3(blocks_for(ni, B)), dim3(B), 0, st, s.lbvh_child.as<int32_t>(), ni,
+                       pint.as<int32_t>(), pleaf.as<int32_t>());
+    HIP_CHECK(hipGetLastError());
+    hipLaunchKernelGGL(k_refit, dim3(blocks_for(nt, B)), dim3(B), 0, st, s.lbvh_child.as<int32_t>(),
+                       pint.as<int32_t>(), pleaf.as<int32_t>(), lbox.as<float>(), ibox.as<float>(),
+                       flags.as<int32_t>(), nodes.as<float4>(), nt);
+    HIP_CHECK(hipGetLastError());
+}
+
+// plain: no tree above the surfaces (one linear BVH over the whole scene)
+static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T, int64_t nt,
+                           const int32_t* surf, const float* rr, const float* ri, bool plain, hipStream_t st)
 {
     s.n_tri = nt;
     if (nt == 0) {
@@ -649,6 +1263,8 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
         return;
     }
     if (nt >= (int64_t)1 << 29) throw inval_error("too many triangles (at most 2^29 - 1)");
+    // node indices stay below 2^29 with the tree above the surfaces too
+    if (nt + RT_TOP_MAX >= (int64_t)1 << 29) plain = true;
     // inputs in device memory are read in place (the build is complete before the call returns);
     // host arrays are staged
     Scratch stage_buf[5];
@@ -671,7 +1287,8 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
     s.surf = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
     s.tri4 = Scratch(c, sizeof(float4) * 3 * (size_t)nt, st);
     Scratch cent(c, sizeof(float4) * (size_t)nt, st);
-    // control block: bounds[12] unsigned, bad, maxdepth, n_surf, seen, nodes spanning several refit tiles
+    // control block: bounds[12] unsigned, bad, depth of the Morton tree, n_surf, seen, nodes spanning several
+    // refit tiles, depth of the walked tree, its root, ranges left by k_top_split
     Scratch ctl(c, 64 * sizeof(int32_t), st);
     unsigned* bounds = ctl.as<unsigned>();
     int32_t* bad = ctl.as<int32_t>() + 12;
@@ -679,6 +1296,9 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
     int32_t* nsurf = ctl.as<int32_t>() + 14;
     int32_t* seen = ctl.as<int32_t>() + 15;
     int32_t* ncross = ctl.as<int32_t>() + 16;
+    int32_t* wmaxd = ctl.as<int32_t>() + 17;
+    int32_t* troot = ctl.as<int32_t>() + 18;
+    int32_t* nfin = ctl.as<int32_t>() + 19;
     hipLaunchKernelGGL(k_ctl_init, dim3(1), dim3(64), 0, st, bounds);
     HIP_CHECK(hipGetLastError());
     const int B = 256;
@@ -694,21 +1314,50 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
                        keys_raw.as<uint64_t>(), s.box.as<float>());
     HIP_CHECK(hipGetLastError());
     sort_keys(c, keys_raw.as<uint64_t>(), keys.as<uint64_t>(), nt, 2, 64, 127, st);
+    // surfaces (tables sized for the largest valid count, n_surf <= n_tri)
+    int sbits = 1;
+    while (((int64_t)1 << sbits) < nt) ++sbits;
+    {
+        // the keys come in triangle order and the sort is stable: the surface bits decide alone
+        Scratch sorted(c, sizeof(uint64_t) * (size_t)nt, st);
+        sort_keys(c, skeys.as<uint64_t>(), sorted.as<uint64_t>(), nt, 1, 32, 32 + sbits, st);
+        std::swap(skeys, sorted);
+    }
+    s.s_ptr = Scratch(c, sizeof(int32_t) * (size_t)(nt + 1), st);
+    s.s_tris = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
+    s.s_plane = Scratch(c, sizeof(double) * 4 * (size_t)nt, st);
+    s.s_box = Scratch(c, sizeof(double) * 6 * (size_t)nt, st);
+    hipLaunchKernelGGL(k_surf_csr, dim3(blocks_for(nt, B)), dim3(B), 0, st, skeys.as<uint64_t>(), nt, nsurf,
+                       s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), seen);
+    HIP_CHECK(hipGetLastError());
+    // leaf slots: by surface, then Morton code
+    Scratch slots(c, 2 * sizeof(uint64_t) * (size_t)nt, st), tslot(c, sizeof(int32_t) * (size_t)nt, st);
+    hipLaunchKernelGGL(k_slot_keys, dim3(blocks_for(nt, B)), dim3(B), 0, st, keys.as<uint64_t>(), s.surf.as<int32_t>(),
+                       nt, nsurf, plain ? 1 : 0, keys_raw.as<uint64_t>());
+    HIP_CHECK(hipGetLastError());
+    int tbits = 0;   // surfaces take part up to RT_TOP_MAX of them
+    while (tbits < sbits && (1 << tbits) < RT_TOP_MAX) ++tbits;
+    sort_keys(c, keys_raw.as<uint64_t>(), slots.as<uint64_t>(), nt, 2, 64 + RT_KEY_SURF_SHIFT,
+              64 + RT_KEY_SURF_SHIFT + tbits, st);
     Scratch lbox(c, sizeof(float) * 6 * (size_t)nt, st);
-    hipLaunchKernelGGL(k_leaves, dim3(blocks_for(nt, B)), dim3(B), 0, st, keys.as<uint64_t>(), dV, dT,
-                       s.surf.as<int32_t>(), nv, nt, bounds, s.tri4.as<float4>(), lbox.as<float>());
+    hipLaunchKernelGGL(k_leaves, dim3(blocks_for(nt, B)), dim3(B), 0, st, slots.as<uint64_t>(), dV, dT,
+                       s.surf.as<int32_t>(), nv, nt, bounds, s.tri4.as<float4>(), lbox.as<float>(),
+                       tslot.as<int32_t>());
     HIP_CHECK(hipGetLastError());
 
     if (nt >= 2) {
-        int64_t ni = nt - 1;
-        s.nodes = Scratch(c, sizeof(float4) * 4 * (size_t)ni, st);
+        const int64_t ni = nt - 1;
+        const int64_t ni_all = ni + (plain ? 0 : std::min<int64_t>(nt, RT_TOP_MAX) - 1);
+        s.nodes = Scratch(c, sizeof(float4) * 4 * (size_t)ni_all, st);
+        s.lbvh_child = Scratch(c, sizeof(int32_t) * 2 * (size_t)ni, st);
         const int64_t n_tiles = (nt + RT_REFIT_TILE - 1) / RT_REFIT_TILE;
-        Scratch child(c, sizeof(int32_t) * 2 * (size_t)ni, st), pint(c, sizeof(int32_t) * (size_t)ni, st),
+        Scratch child(c, sizeof(int32_t) * 2 * (size_t)ni_all, st), pint(c, sizeof(int32_t) * (size_t)ni_all, st),
             pleaf(c, sizeof(int32_t) * (size_t)nt, st), range(c, sizeof(int2) * (size_t)ni, st),
             cross(c, sizeof(int32_t) * (size_t)(n_tiles > 1 ? ni : 1), st),
-            tbox(c, sizeof(float) * 6 * (size_t)n_tiles, st);
-        hipLaunchKernelGGL(k_karras, dim3(blocks_for(ni, B)), dim3(B), 0, st, keys.as<uint64_t>(), nt,
-                           child.as<int32_t>(), pint.as<int32_t>(), pleaf.as<int32_t>(), range.as<int2>(),
+            tbox(c, sizeof(float) * 6 * (size_t)n_tiles, st), mpint(c, sizeof(int32_t) * (size_t)ni, st);
+        const KarrasOut ko{slots.as<uint64_t>(), child.as<int32_t>(), pint.as<int32_t>(), pleaf.as<int32_t>()};
+        const KarrasOut km{keys.as<uint64_t>(), s.lbvh_child.as<int32_t>(), mpint.as<int32_t>(), nullptr};
+        hipLaunchKernelGGL(k_karras, dim3(blocks_for(ni, B), 2), dim3(B), 0, st, ko, km, nt, range.as<int2>(),
                            cross.as<int32_t>(), ncross);
         HIP_CHECK(hipGetLastError());
         hipLaunchKernelGGL(k_refit_tiles, dim3((unsigned)n_tiles), dim3(1024), 0, st, child.as<int32_t>(),
@@ -721,31 +1370,29 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
                                lbox.as<float>(), tbox.as<float>(), s.nodes.as<float4>(), bad);
             HIP_CHECK(hipGetLastError());
         }
-        s.node4 = Scratch(c, sizeof(float4) * 8 * (size_t)ni, st);
-        hipLaunchKernelGGL(k_node4, dim3(blocks_for(ni, B)), dim3(B), 0, st, child.as<int32_t>(), pint.as<int32_t>(),
-                           s.nodes.as<float4>(), s.tri4.as<float4>(), ni, s.node4.as<float4>(), maxd);
+        if (!plain) {
+            const int64_t ns = std::min<int64_t>(nt, RT_TOP_MAX);
+            Scratch sb(c, sizeof(float4) * 2 * (size_t)ns, st), order(c, sizeof(int32_t) * (size_t)ns, st),
+                fin(c, sizeof(int4) * (size_t)ns, st);
+            const TopOut to{s.nodes.as<float4>(), child.as<int32_t>(), pint.as<int32_t>(), troot, ni};
+            hipLaunchKernelGGL(k_top_split, dim3(1), dim3(TOP_T), 0, st, s.s_ptr.as<int32_t>(), nsurf, seen,
+                               range.as<int2>(), lbox.as<float>(), sb.as<float4>(), order.as<int32_t>(),
+                               fin.as<int4>(), nfin, to);
+            HIP_CHECK(hipGetLastError());
+            hipLaunchKernelGGL(k_top_finish, dim3((unsigned)std::max<int64_t>(1, ns / 2)), dim3(TOP_FT), 0, st, nsurf, seen,
+                               sb.as<float4>(),
+                               order.as<int32_t>(), fin.as<int4>(), nfin, to);
+            HIP_CHECK(hipGetLastError());
+        }
+        s.node4 = Scratch(c, sizeof(float4) * 8 * (size_t)ni_all, st);
+        const MortonTree mt{keys.as<uint64_t>(), mpint.as<int32_t>(), tslot.as<int32_t>(), s.lbvh_child.as<int32_t>(),
+                            maxd};
+        hipLaunchKernelGGL(k_node4, dim3(blocks_for(ni_all, B), 2), dim3(B), 0, st, child.as<int32_t>(),
+                           pint.as<int32_t>(), s.nodes.as<float4>(), s.tri4.as<float4>(), slots.as<uint64_t>(),
+                           range.as<int2>(), nsurf, seen, plain ? 1 : 0, ni, ni_all, s.node4.as<float4>(), wmaxd, mt);
         HIP_CHECK(hipGetLastError());
-        s.root = 0;
-    } else {
-        s.root = ~0;
     }
 
-    // surfaces (tables sized for the largest valid count, n_surf <= n_tri)
-    {
-        // the keys come in triangle order and the sort is stable: the surface bits decide alone
-        int sbits = 1;
-        while (((int64_t)1 << sbits) < nt) ++sbits;
-        Scratch sorted(c, sizeof(uint64_t) * (size_t)nt, st);
-        sort_keys(c, skeys.as<uint64_t>(), sorted.as<uint64_t>(), nt, 1, 32, 32 + sbits, st);
-        std::swap(skeys, sorted);
-    }
-    s.s_ptr = Scratch(c, sizeof(int32_t) * (size_t)(nt + 1), st);
-    s.s_tris = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
-    s.s_plane = Scratch(c, sizeof(double) * 4 * (size_t)nt, st);
-    s.s_box = Scratch(c, sizeof(double) * 6 * (size_t)nt, st);
-    hipLaunchKernelGGL(k_surf_csr, dim3(blocks_for(nt, B)), dim3(B), 0, st, skeys.as<uint64_t>(), nt, nsurf,
-                       s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), seen);
-    HIP_CHECK(hipGetLastError());
     s.g_axes = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
     s.g_frame = Scratch(c, sizeof(double) * 4 * (size_t)nt, st);
     s.g_cnt = Scratch(c, sizeof(int32_t) * RT_SGRID_CELLS * (size_t)nt, st);
@@ -757,8 +1404,8 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
                        s.g_tris.as<int32_t>(), bad);
     HIP_CHECK(hipGetLastError());
     // one read-back: input checks, tree checks, surface count
-    int64_t hq[2];
-    read_i64s((const int64_t*)(ctl.as<int32_t>() + 12), hq, 2, st);
+    int64_t hq[4];
+    read_i64s((const int64_t*)(ctl.as<int32_t>() + 12), hq, 4, st);
     const int32_t badv = (int32_t)(hq[0] & 0xffffffff), depth = (int32_t)(hq[0] >> 32);
     const int32_t n_surf = (int32_t)(hq[1] & 0xffffffff), n_seen = (int32_t)(hq[1] >> 32);
     if (badv & 1) throw inval_error("triangle vertex index out of range");
@@ -774,6 +1421,20 @@ void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T,
                                      "0.1 mm from the plane of the surface's first triangle)");
     s.max_depth = depth;
     s.n_surf = n_surf;
+    const int32_t wdepth = (int32_t)(hq[2] >> 32);
+    const bool top = !plain && n_surf >= 2 && n_surf <= RT_TOP_MAX;
+    s.walk_depth = wdepth;
+    s.root = nt < 2 ? ~0 : top ? (int32_t)(hq[3] & 0xffffffff) : 0;
+    if (top && (s.root < nt - 1 || s.root >= nt - 1 + n_surf - 1 || wdepth >= (1 << 20)))
+        throw hip_error("BVH build produced an inconsistent tree");
+}
+
+void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T, int64_t nt,
+                 const int32_t* surf, const float* rr, const float* ri, hipStream_t st)
+{
+    build_scene_as(c, s, V, nv, T, nt, surf, rr, ri, false, st);
+    // deeper than the stacks hold (chains of surfaces nested in one another): the linear BVH, whose depth was checked
+    if (s.walk_depth > RT_STACK - 1) build_scene_as(c, s, V, nv, T, nt, surf, rr, ri, true, st);
 }
 
 }  // namespace rt

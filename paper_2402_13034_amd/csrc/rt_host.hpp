@@ -125,7 +125,9 @@ struct Scene {
     hipStream_t ready_st = nullptr;   // the stream `ready` was recorded on
     int64_t n_tri = 0, n_surf = 0;
     int32_t root = 0;
-    int32_t max_depth = 0;
+    int32_t max_depth = 0;    // of the scene's Morton tree (the depth a scene reports)
+    int32_t walk_depth = 0;   // of the tree in nodes / node4
+    Scratch lbvh_child;       // int32 [2 (n_tri - 1)]: the Morton tree, leaves as slots (lbvh_nodes)
     Scratch tri4, nodes, node4, v64, refl, surf, s_ptr, s_tris, s_plane, s_box, t_proj, t_axes;
     Scratch mat;   // float2 per triangle (eps_r, sigma), empty until set
     Scratch nrm;   // 3 doubles per triangle: unit normal, computed with the materials
@@ -232,6 +234,8 @@ void scan_i64(Ctx& c, const int64_t* in, int64_t* out, int64_t n, hipStream_t st
 // ---- scene build ----
 void build_scene(Ctx& c, Scene& s, const float* V, int64_t nv, const int32_t* T, int64_t nt,
                  const int32_t* surf, const float* rr, const float* ri, hipStream_t st);
+// Nodes (with boxes) of the scene's Morton tree for the counting builds, on `st`.
+void lbvh_nodes(Ctx& c, const Scene& s, Scratch& nodes, hipStream_t st);
 // Unit normals of the scene's triangles (FP64) into s.nrm, on `st`.
 void scene_normals(Ctx& c, Scene& s, hipStream_t st);
 

@@ -1328,7 +1328,10 @@ struct Cands {
     }
 };
 
-static int stack_depth_for(const Scene& s, bool brute) { return (brute || s.max_depth < 31) ? 32 : 64; }
+static int stack_depth_for(const Scene& s, bool brute)
+{
+    return (brute || std::max(s.max_depth, s.walk_depth) < 31) ? 32 : 64;
+}
 
 struct PathSet {
     int64_t n = 0;
@@ -1714,6 +1717,14 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     unsigned long long* d_disc = d_ctr;
     unsigned long long* d_legs = d_ctr + 1;
     unsigned long long* d_work = d_ctr + 8;
+    // the counting builds walk the scene's Morton tree
+    SceneView svc = sv;
+    Scratch lbvh;
+    if (count_work && !brute && sv.n_tri > 1) {
+        lbvh_nodes(c, *a.scene, lbvh, st);
+        svc.nodes = lbvh.as<float4>();
+        svc.root = 0;
+    }
     ch.E_env = Scratch(c, sizeof(float2) * (size_t)R, st);
     Scratch uptr, useq;
     if (a.ris) uptr = Scratch(c, sizeof(int64_t) * (size_t)(R + 1), st);
@@ -1760,8 +1771,8 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
         HIP_CHECK(hipStreamWaitEvent(bu.st, fork.e, 0));
     }
     // 1-3: candidates
-    cand_phase_a<KM>(c, sv, stk, a, brute, exhaustive, keep_hits, ch, bt, d_disc);
-    if (two) cand_phase_a<KM>(c, sv, stk, a, brute, exhaustive, keep_hits, ch, bu, d_disc);
+    cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, bt, d_disc);
+    if (two) cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, bu, d_disc);
     // the receivers in Morton order of their positions, for the geometry kernel
     // (queued behind the Tx discovery; the centre branch waits for it below)
     if (R >= ((int64_t)1 << RX_IDX_BITS)) throw inval_error("too many receivers");
@@ -1785,7 +1796,7 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
         while (n < 0) {
             br.table_level += 1;
             HIP_CHECK(hipMemsetAsync(br.d_app, 0, 2 * sizeof(unsigned long long), br.st));
-            cand_phase_a<KM>(c, sv, stk, a, brute, exhaustive, keep_hits, ch, br, d_dummy);
+            cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, br, d_dummy);
             n = cand_count(c, br, exhaustive);
         }
         return n;
@@ -1912,7 +1923,7 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
         if (threads > 0) {
             if (count_work && !brute && !keep_paths && !keep_cir) {
                 SEL_STK(stk, hipLaunchKernelGGL((k_ris<false, false, STK, true, false, KM>), dim3(nblk(threads, RIS_B)),
-                                                dim3(RIS_B), 0, sr, sv, a.tc, rv, txm.as<TxmRec>(), a.rx_dev, R,
+                                                dim3(RIS_B), 0, sr, svc, a.tc, rv, txm.as<TxmRec>(), a.rx_dev, R,
                                                 uptr.as<int64_t>(), useq.as<int32_t>(), order.as<uint64_t>(), n_mchunk, ch.H.as<float2>(),
                                                 ch.ris_valid.as<uint8_t>(), (float2*)nullptr, (double*)nullptr, d_legs,
                                                 d_work, d_ctr + 14));

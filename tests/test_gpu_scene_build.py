@@ -1,6 +1,8 @@
 """The scene build at the edges of its tiles: the node boxes (one workgroup per
-2048 leaves, the nodes above by leaf range) and the surface tables (lanes over
-a surface's triangles) give the walk that testing every triangle gives."""
+2048 leaves, the nodes above by leaf range), the tree above the surfaces (one
+workgroup, then one per 256 surfaces; boxes in LDS up to 2048; none above 8192)
+and the surface tables (lanes over a surface's triangles) give the walk that
+testing every triangle gives."""
 import numpy as np
 import pytest
 
@@ -52,3 +54,43 @@ def test_build_equals_brute_force(ctx, n_tri, sub):
         ref = O.trace(prob)
     assert np.array_equal(outs[0][4]["tri"][:, :2], ref["env_tri"][:, :2])
     assert np.array_equal(outs[0][5], ref["ris_valid"])
+
+
+# every triangle a surface of its own: the surface counts at which the tree above them changes its way
+@pytest.mark.parametrize("n_surf", [2, 3, 256, 257, 2048, 2049, 8192, 8193])
+def test_tree_above_surfaces(ctx, n_surf):
+    from paper_2402_13034_amd import risrt
+    p = _trimmed(n_surf, 7)
+    p.order = 1
+    p.n_rays = 4_000
+    p.scene.surf = np.arange(n_surf, dtype=np.int32)
+    print("case surfaces", n_surf, flush=True)
+    outs = []
+    for brute in (0, risrt.FLAG_BRUTE_FORCE):
+        scene, ris = risrt.upload_problem(ctx, p)
+        ch, st = risrt.trace_problem(ctx, p, scene, ris, flags=risrt.FLAG_KEEP_HITS | risrt.FLAG_KEEP_PATHS | brute)
+        E, H = ctx.channel_read(ch)
+        outs.append((ctx.hits_read(ch, 0, 1), ctx.hits_read(ch, 1, 1), E, H, ctx.paths_read(ch)["ris_valid"]))
+        for h in (ch, scene, ris):
+            ctx.destroy(h)
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
+def test_counting_walk_is_the_morton_tree(ctx):
+    """The counting builds walk the scene's Morton tree, whose boxes are made
+    for them: the same hits and fields, and work that does not change between
+    a scene and the same one rebuilt."""
+    from paper_2402_13034_amd import risrt
+    p = _trimmed(5000, 6)
+    got = []
+    for flags in (0, risrt.FLAG_COUNT_WORK, risrt.FLAG_COUNT_WORK):
+        scene, ris = risrt.upload_problem(ctx, p)
+        ch, st = risrt.trace_problem(ctx, p, scene, ris, flags=flags)
+        got.append((ctx.channel_read(ch), st["ris_work"] + st["discovery_work"], st["leg_segments"]))
+        for h in (ch, scene, ris):
+            ctx.destroy(h)
+    for g in got[1:]:
+        assert np.array_equal(g[0][0], got[0][0][0]) and np.array_equal(g[0][1], got[0][0][1])
+        assert g[2] == got[0][2]
+    assert got[1][1] == got[2][1] and min(got[1][1]) > 0

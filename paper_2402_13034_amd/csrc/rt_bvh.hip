@@ -77,7 +77,7 @@ __global__ __launch_bounds__(PREP_B) void k_scene_prep(const float* V, const int
                                                        const float* rr, const float* ri, int64_t nv, int64_t nt,
                                                        double* v64, float2* refl, int32_t* surf, float4* cent,
                                                        uint64_t* skeys, unsigned* bounds, int32_t* bad,
-                                                       int32_t* n_surf, double* proj, int32_t* axes)
+                                                       int32_t* n_surf, double* proj, int32_t* axes, double* edge)
 {
     __shared__ unsigned red[PREP_B / 64][13];
     unsigned mn[6], mx[6];   // minima and maxima of the centroids (0..2) and the vertices (3..5)
@@ -106,7 +106,12 @@ __global__ __launch_bounds__(PREP_B) void k_scene_prep(const float* V, const int
                 mx[3 + k] = max(mx[3 + k], u);
             }
         }
-        triangle_projection(w, proj + 6 * t, axes + t);
+        double q6[6];
+        int32_t ax;
+        triangle_projection(w, q6, &ax);
+        for (int k = 0; k < 6; ++k) proj[6 * t + k] = q6[k];
+        axes[t] = ax;
+        triangle_edges(q6, ax, edge + RT_EDGE * t);
         refl[t] = make_float2(rr[t], ri[t]);
         const int32_t sf = surf_in[t];
         surf[t] = sf;
@@ -1004,7 +1009,7 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
          s += (int)(gridDim.x * (blockDim.x >> 6))) {
         const int b = s_ptr[s], e = s_ptr[s + 1];
         if (b >= e) {   // an unused id (reported as invalid)
-            if (lane < 4) s_plane[4 * (int64_t)s + lane] = 0.0;
+            if (lane < RT_PLANE) s_plane[RT_PLANE * (int64_t)s + lane] = 0.0;
             if (lane < 6) s_box[6 * (int64_t)s + lane] = lane < 3 ? 1e300 : -1e300;
             if (lane == 0) g_axes[s] = -1;
             if (lane < RT_SGRID_CELLS) g_cnt[(int64_t)s * RT_SGRID_CELLS + lane] = 0;
@@ -1052,11 +1057,14 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
         if (lane == 0) {
             if (!(nlen > 0.0)) atomicOr(bad, 32);
             if (any_off) atomicOr(bad, 16);
-            double* pl = s_plane + 4 * (int64_t)s;
+            double* pl = s_plane + RT_PLANE * (int64_t)s;
+            const double nn = n0 * n0 + n1 * n1 + n2 * n2;
             pl[0] = n0;
             pl[1] = n1;
             pl[2] = n2;
             pl[3] = dpl;
+            pl[4] = nn;
+            pl[5] = 1.0 / nn;
             for (int k = 0; k < 3; ++k) {
                 s_box[6 * (int64_t)s + k] = lo[k];
                 s_box[6 * (int64_t)s + 3 + k] = hi[k];
@@ -1281,8 +1289,8 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     const float* dI = (const float*)input(ri, sizeof(float) * (size_t)nt, 4);
 
     s.v64 = Scratch(c, sizeof(double) * 9 * (size_t)nt, st);
-    s.t_proj = Scratch(c, sizeof(double) * 6 * (size_t)nt, st);
-    s.t_axes = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
+    s.t_edge = Scratch(c, sizeof(double) * RT_EDGE * (size_t)nt, st);
+    Scratch t_proj(c, sizeof(double) * 6 * (size_t)nt, st), t_axes(c, sizeof(int32_t) * (size_t)nt, st);
     s.refl = Scratch(c, sizeof(float2) * (size_t)nt, st);
     s.surf = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
     s.tri4 = Scratch(c, sizeof(float4) * 3 * (size_t)nt, st);
@@ -1305,8 +1313,8 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     Scratch skeys(c, sizeof(uint64_t) * (size_t)nt, st);
     hipLaunchKernelGGL(k_scene_prep, dim3(std::min<unsigned>(blocks_for(nt, PREP_B), PREP_BLOCKS)), dim3(PREP_B), 0, st,
                        dV, dT, dS, dR, dI, nv, nt, s.v64.as<double>(), s.refl.as<float2>(), s.surf.as<int32_t>(),
-                       cent.as<float4>(), skeys.as<uint64_t>(), bounds, bad, nsurf, s.t_proj.as<double>(),
-                       s.t_axes.as<int32_t>());
+                       cent.as<float4>(), skeys.as<uint64_t>(), bounds, bad, nsurf, t_proj.as<double>(),
+                       t_axes.as<int32_t>(), s.t_edge.as<double>());
     HIP_CHECK(hipGetLastError());
     s.box = Scratch(c, 6 * sizeof(float), st);
     Scratch keys_raw(c, 2 * sizeof(uint64_t) * (size_t)nt, st), keys(c, 2 * sizeof(uint64_t) * (size_t)nt, st);
@@ -1325,7 +1333,7 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     }
     s.s_ptr = Scratch(c, sizeof(int32_t) * (size_t)(nt + 1), st);
     s.s_tris = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
-    s.s_plane = Scratch(c, sizeof(double) * 4 * (size_t)nt, st);
+    s.s_plane = Scratch(c, sizeof(double) * RT_PLANE * (size_t)nt, st);
     s.s_box = Scratch(c, sizeof(double) * 6 * (size_t)nt, st);
     hipLaunchKernelGGL(k_surf_csr, dim3(blocks_for(nt, B)), dim3(B), 0, st, skeys.as<uint64_t>(), nt, nsurf,
                        s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), seen);
@@ -1398,8 +1406,8 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     s.g_cnt = Scratch(c, sizeof(int32_t) * RT_SGRID_CELLS * (size_t)nt, st);
     s.g_tris = Scratch(c, sizeof(int32_t) * RT_SGRID_CELLS * (size_t)nt, st);
     hipLaunchKernelGGL(k_surf_tables, dim3(std::min<unsigned>(blocks_for(nt, 4), 2048)), dim3(256), 0, st,
-                       s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), s.v64.as<double>(), s.t_proj.as<double>(),
-                       s.t_axes.as<int32_t>(), nsurf, s.s_plane.as<double>(), s.s_box.as<double>(),
+                       s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), s.v64.as<double>(), t_proj.as<double>(),
+                       t_axes.as<int32_t>(), nsurf, s.s_plane.as<double>(), s.s_box.as<double>(),
                        s.g_axes.as<int32_t>(), s.g_frame.as<double>(), s.g_cnt.as<int32_t>(),
                        s.g_tris.as<int32_t>(), bad);
     HIP_CHECK(hipGetLastError());

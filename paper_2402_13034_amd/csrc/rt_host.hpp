@@ -128,7 +128,7 @@ struct Scene {
     int32_t max_depth = 0;    // of the scene's Morton tree (the depth a scene reports)
     int32_t walk_depth = 0;   // of the tree in nodes / node4
     Scratch lbvh_child;       // int32 [2 (n_tri - 1)]: the Morton tree, leaves as slots (lbvh_nodes)
-    Scratch tri4, nodes, node4, v64, refl, surf, s_ptr, s_tris, s_plane, s_box, t_proj, t_axes;
+    Scratch tri4, nodes, node4, v64, refl, surf, s_ptr, s_tris, s_plane, s_box, t_edge;
     Scratch mat;   // float2 per triangle (eps_r, sigma), empty until set
     Scratch nrm;   // 3 doubles per triangle: unit normal, computed with the materials
     Scratch g_axes, g_frame, g_cnt, g_tris;
@@ -151,8 +151,7 @@ struct Scene {
         v.s_tris = s_tris.as<int32_t>();
         v.s_plane = s_plane.as<double>();
         v.s_box = s_box.as<double>();
-        v.t_proj = t_proj.as<double>();
-        v.t_axes = t_axes.as<int32_t>();
+        v.t_edge = t_edge.as<double>();
         v.g_axes = g_axes.as<int32_t>();
         v.g_frame = g_frame.as<double>();
         v.g_cnt = g_cnt.as<int32_t>();

@@ -15,6 +15,8 @@
 #include <stdexcept>
 #include <string>
 
+#include "rt_fp64_core.hpp"
+
 #define RT_MAX_K 5            // largest reflection order (keys of two 64-bit words above 3)
 #define RT_KM_SMALL 3        // orders up to this use one-word keys and the smaller kernel instances
 #define RT_STACK 64          // BVH traversal stack entries per lane (LDS)
@@ -52,10 +54,9 @@ struct SceneView {
     const int32_t* surf;   // per triangle
     const int32_t* s_ptr;  // n_surf + 1
     const int32_t* s_tris; // triangles grouped by surface, ascending
-    const double* s_plane; // 4 per surface: n (not unit), c = n . v0 of its first triangle
+    const double* s_plane; // RT_PLANE per surface: n (not unit), c = n . v0 of its first triangle, n . n, 1 / (n . n)
     const double* s_box;   // 6 per surface: lo, hi (inflated by 1e-9 m)
-    const double* t_proj;  // 6 per triangle: a, b, c projected (counter-clockwise), see contains_proj
-    const int32_t* t_axes; // per triangle: i0 | i1 << 2, 16 if degenerate
+    const double* t_edge;  // RT_EDGE per triangle: the edge functions of the containment test, see triangle_edges
     // containment grid per surface (RT_SGRID x RT_SGRID cells over the surface box in the
     // projection all its triangles share; g_axes -1: no grid, scan every triangle)
     const int32_t* g_axes;   // per surface
@@ -64,6 +65,8 @@ struct SceneView {
     const int32_t* g_tris;   // cell (c) of surface sf lists from s_ptr[sf] * cells + c * n_tris(sf)
 };
 
+#define RT_PLANE 6
+#define RT_EDGE 16
 #define RT_SGRID 4
 #define RT_SGRID_CELLS (RT_SGRID * RT_SGRID)
 
@@ -142,6 +145,33 @@ __device__ __forceinline__ bool mt_hit(float ox, float oy, float oz, float dx, f
     return true;
 }
 
+// May mt_hit accept, by its numerators alone (no division)?  Each bound leaves
+// at least 1e-4 relative (the formula's rounding is below 1e-6), and a value
+// rejected for its sign is at least 1e-20 of the determinant, far above where
+// its quotient could round to zero; so a false answer means mt_hit is false.
+__device__ __forceinline__ bool mt_maybe(float ox, float oy, float oz, float dx, float dy, float dz, float4 a,
+                                         float4 b, float4 c)
+{
+#pragma clang fp contract(off)
+    const float e1x = b.x, e1y = b.y, e1z = b.z;
+    const float e2x = c.x, e2y = c.y, e2z = c.z;
+    const float px = dy * e2z - dz * e2y;
+    const float py = dz * e2x - dx * e2z;
+    const float pz = dx * e2y - dy * e2x;
+    const float det = e1x * px + e1y * py + e1z * pz;
+    const float sx = ox - a.x;
+    const float sy = oy - a.y;
+    const float sz = oz - a.z;
+    const unsigned sg = __float_as_uint(det) & 0x80000000u;
+    const float un = __uint_as_float(__float_as_uint(sx * px + sy * py + sz * pz) ^ sg);   // u |det|
+    const float lo = fabsf(det) * -1e-20f, hi = fabsf(det) * 1.0001f;
+    const float qx = sy * e1z - sz * e1y;
+    const float qy = sz * e1x - sx * e1z;
+    const float qz = sx * e1y - sy * e1x;
+    const float vn = __uint_as_float(__float_as_uint(dx * qx + dy * qy + dz * qz) ^ sg);   // v |det|
+    return !(un < lo || un > hi || vn < lo || un + vn > hi);
+}
+
 __device__ __forceinline__ void reflect32(float4 b, float4 c, float& dx, float& dy, float& dz)
 {
 #pragma clang fp contract(off)
@@ -154,6 +184,14 @@ __device__ __forceinline__ void reflect32(float4 b, float4 c, float& dx, float& 
     dx = dx - k * nx;
     dy = dy - k * ny;
     dz = dz - k * nz;
+}
+
+// FP64 a / b, and L = sqrt(x) with il = 1 / L, from the hardware's estimates
+// (rt_fp64_core.hpp; 8 instead of 11 and 16 instead of 33 instructions).
+__device__ __forceinline__ double div_fast(double a, double b) { return div_refine(a, b, __builtin_amdgcn_rcp(b)); }
+__device__ __forceinline__ void sqrt_inv(double x, double& L, double& il)
+{
+    sqrt_refine(x, __builtin_amdgcn_rsq(fmax(x, 1e-300)), &L, &il);
 }
 
 // Work counters of the counting build of a kernel (node visits, triangle
@@ -341,11 +379,11 @@ __device__ bool leg_blocked(const SceneView& s, const double* A, const double* B
 {
 #pragma clang fp contract(off)
     double w0 = B[0] - A[0], w1 = B[1] - A[1], w2 = B[2] - A[2];
-    double L = sqrt(w0 * w0 + w1 * w1 + w2 * w2);
+    double L, il;
+    sqrt_inv(w0 * w0 + w1 * w1 + w2 * w2, L, il);
     float tmin = (float)RT_EPS;
     float tmax = (float)(L - RT_EPS);
     if (!(tmax > tmin)) return false;
-    const double il = 1.0 / L;
     return any_hit<BRUTE, CNT>(s, (float)A[0], (float)A[1], (float)A[2], (float)(w0 * il), (float)(w1 * il),
                                (float)(w2 * il), tmin, tmax, sa, sb, stack, stride, wc);
 }
@@ -633,6 +671,22 @@ __device__ int closest_hit_wave4(const SceneView& s, bool active, float ox, floa
 #define RT_TUBE_FRONT 128
 #define RT_TUBE_CAND 128
 
+// Maximum over the 64 lanes of a wave (every lane active) of values >= 0 as
+// their bits (a NaN comes out as the largest), with DPP lane moves: butterflies
+// inside rows of 16, then the row broadcasts of the 64-wide wave; lane 63 ends
+// with the maximum.
+__device__ __forceinline__ float wave_max_pos(float v)
+{
+    unsigned x = __float_as_uint(v);
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xF, 0xF, true));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));
+    return __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)x, 63));
+}
+
 // Maximum over the 64 lanes of a wave (every lane active), with DPP lane
 // moves: butterflies inside rows of 16, then the row broadcasts of the
 // 64-wide wave; lane 63 ends with the maximum.
@@ -652,7 +706,8 @@ __device__ __forceinline__ float wave_max(float v)
 // entries tagged with their leg (3 bits above a 29-bit node or slot index),
 // so the wave walks the levels of the tree once for up to KM + 1 legs.
 // lb: the wave's leg rays in LDS, [leg][7][64] = ox, oy, oz, dx, dy, dz, tmax;
-// tube: 8 floats per leg in LDS; front: 2 x RT_TUBE_FRONT ints, cand:
+// end: the last leg's end point (the receiver, the same for every lane);
+// tube: 3 float4 per leg in LDS; front: 2 x RT_TUBE_FRONT ints, cand:
 // RT_TUBE_CAND ints, wstack: RT_STACK4 ints (fallback), all per wave;
 // seq: the slot's surfaces (wave-uniform), k its order; ok: the lane's path
 // is still valid.  Returns the lane's bit set of blocked legs, plus
@@ -687,74 +742,83 @@ __device__ __forceinline__ int leg_surface_b(const int* seq, int j, int k)
 
 template <int KM>
 __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool ok, int k, const int* seq,
-                                                      const float* lb, float* tube, int* front, int* cand,
-                                                      int* wstack)
+                                                      const float* lb, const float* end, float4* tube, int* front,
+                                                      int* cand, int* wstack)
 {
     static_assert(KM + 1 <= 8, "three bits of leg index");
     const int lane = threadIdx.x & 63;
     const float tmin = (float)RT_EPS;
     unsigned blocked = 0;
     if (s.n_tri == 0 || __ballot(ok) == 0ull) return 0;
-    const unsigned exact = 1u << 16;   // a tube radius not representable: exact walk
+    // Path vertices of the first valid lane (the central path) and the largest
+    // distance of any lane's from them, vertex j in lane j: per vertex one wave
+    // maximum of squares; the tubes' constants follow in lanes 0..k at once.
+    // (Per leg, with both end points, square roots and constants computed by
+    // every lane, the set-up took 75 vector instructions a leg; 30 so, and 45 a
+    // slot.)
+    const int lead = __ffsll((long long)__ballot(ok)) - 1;
     unsigned live = 0;   // legs with a searching lane (uniform)
+    float vx = 0.0f, vy = 0.0f, vz = 0.0f, vd = 0.0f;
 #pragma unroll
-    for (int j = 0; j <= KM; ++j) {
-        if (j > k) break;
-        const float* r0 = lb + j * 7 * 64 + lane;
-        const float ox = r0[0], oy = r0[64], oz = r0[128], dx = r0[192], dy = r0[256], dz = r0[320], tmax = r0[384];
-        const bool searching = ok && tmax > tmin;
-        const unsigned long long act = __ballot(searching);
-        if (act == 0ull) continue;
-        live |= 1u << j;
-        // end points and distances in FP32: their rounding (a few 1e-7 relative) is far inside
-        // the margin (1e-4 relative on r, 1e-4 m + 4e-6 x the coordinates' scale)
-        const float ax = __builtin_fmaf(tmin, dx, ox), ay = __builtin_fmaf(tmin, dy, oy), az = __builtin_fmaf(tmin, dz, oz);
-        const float bx = __builtin_fmaf(tmax, dx, ox), by = __builtin_fmaf(tmax, dy, oy), bz = __builtin_fmaf(tmax, dz, oz);
-        const int lead = __ffsll((long long)act) - 1;
-        const float cax = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ax), lead));
-        const float cay = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ay), lead));
-        const float caz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(az), lead));
-        const float cbx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bx), lead));
-        const float cby = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(by), lead));
-        const float cbz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bz), lead));
-        const float da = sqrtf((ax - cax) * (ax - cax) + (ay - cay) * (ay - cay) + (az - caz) * (az - caz));
-        const float db = sqrtf((bx - cbx) * (bx - cbx) + (by - cby) * (by - cby) + (bz - cbz) * (bz - cbz));
-        const float scale = fmaxf(fmaxf(fabsf(cax), fmaxf(fabsf(cay), fabsf(caz))),
-                                  fmaxf(fabsf(cbx), fmaxf(fabsf(cby), fabsf(cbz)))) + fabsf(tmax);
-        const float r = wave_max(searching ? fmaxf(da, db) * 1.0001f + 1e-4f + 4e-6f * scale : 0.0f);
-        // central ray with hardware reciprocals (1 ulp): their error is inside the margin too
-        RayBox crb;
-        {
-            float ex = cbx - cax, ey = cby - cay, ez = cbz - caz;
-            ex = fabsf(ex) < 1e-30f ? copysignf(1e-30f, ex) : ex;
-            ey = fabsf(ey) < 1e-30f ? copysignf(1e-30f, ey) : ey;
-            ez = fabsf(ez) < 1e-30f ? copysignf(1e-30f, ez) : ez;
-            crb.ix = __builtin_amdgcn_rcpf(ex);
-            crb.iy = __builtin_amdgcn_rcpf(ey);
-            crb.iz = __builtin_amdgcn_rcpf(ez);
-            crb.oix = cax * crb.ix;
-            crb.oiy = cay * crb.iy;
-            crb.oiz = caz * crb.iz;
+    for (int j = 0; j <= KM + 1; ++j) {
+        if (j > k + 1) break;
+        float cx, cy, cz, d2 = 0.0f;
+        if (j <= k) {
+            const float* r0 = lb + j * 7 * 64 + lane;
+            const float ox = r0[0], oy = r0[64], oz = r0[128];
+            live |= __ballot(ok && r0[384] > tmin) ? 1u << j : 0u;
+            cx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ox), lead));
+            cy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(oy), lead));
+            cz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(oz), lead));
+            const float ax = ox - cx, ay = oy - cy, az = oz - cz;
+            d2 = wave_max_pos(ok ? __builtin_fmaf(ax, ax, __builtin_fmaf(ay, ay, az * az)) : 0.0f);
+        } else {
+            cx = end[0];
+            cy = end[1];
+            cz = end[2];
         }
-        if (!(r < 1e30f)) live |= exact;   // not representable: exact walk below
-        if (lane == 0) {
-            float* t = tube + 8 * j;
-            t[0] = crb.ix;
-            t[1] = crb.iy;
-            t[2] = crb.iz;
-            t[3] = crb.oix;
-            t[4] = crb.oiy;
-            t[5] = crb.oiz;
-            t[6] = r;
-        }
+        vx = lane == j ? cx : vx;
+        vy = lane == j ? cy : vy;
+        vz = lane == j ? cz : vz;
+        vd = lane == j ? d2 : vd;
     }
     if (live == 0) return 0;
+    bool overflow;
+    {
+        // the leg's end: the next lane's vertex (row_shl:1)
+        const float wx = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(vx), 0x101, 0xF, 0xF, true));
+        const float wy = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(vy), 0x101, 0xF, 0xF, true));
+        const float wz = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(vz), 0x101, 0xF, 0xF, true));
+        const float wd = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(vd), 0x101, 0xF, 0xF, true));
+        float ex = wx - vx, ey = wy - vy, ez = wz - vz;
+        // every lane's ray runs from its own vertex to its next one (direction and length in FP32): within the
+        // larger of the two distances of the central leg, plus a margin for the FP32 representation of the rays,
+        // the triangle test and the slab test: 1e-4 relative, 1e-4 m, 4e-6 of the coordinates' and leg's scale
+        const float dev = __builtin_amdgcn_sqrtf(fmaxf(vd, wd));
+        const float scale = fmaxf(fmaxf(fabsf(vx), fmaxf(fabsf(vy), fabsf(vz))),
+                                  fmaxf(fabsf(wx), fmaxf(fabsf(wy), fabsf(wz)))) +
+                            fabsf(ex) + fabsf(ey) + fabsf(ez) + 2.0f * dev;
+        const float r = dev * 1.0002f + 1e-4f + 4e-6f * scale;
+        // central ray with hardware reciprocals (1 ulp): their error is inside the margin too
+        ex = fabsf(ex) < 1e-30f ? copysignf(1e-30f, ex) : ex;
+        ey = fabsf(ey) < 1e-30f ? copysignf(1e-30f, ey) : ey;
+        ez = fabsf(ez) < 1e-30f ? copysignf(1e-30f, ez) : ez;
+        const float ix = __builtin_amdgcn_rcpf(ex), iy = __builtin_amdgcn_rcpf(ey), iz = __builtin_amdgcn_rcpf(ez);
+        // a radius that is not representable: exact walk below
+        overflow = __ballot(lane <= k && !(r < 1e30f)) != 0ull;
+        if (lane <= k) {
+            tube[3 * lane] = make_float4(ix, iy, iz, r);
+            tube[3 * lane + 1] = make_float4(vx * ix, vy * iy, vz * iz,
+                                             __int_as_float(leg_surface_a<KM>(seq, lane)));
+            tube[3 * lane + 2].x = __int_as_float(leg_surface_b<KM>(seq, lane, k));
+        }
+    }
     int nc = 0;
-    bool overflow = (live & exact) != 0;
     if (!overflow) {
         if (s.root < 0) {
+            const int sf = __float_as_int(s.tri4[3 * (~s.root) + 1].w);
             for (int j = 0; j <= k; ++j)
-                if (live & (1u << j)) {
+                if ((live & (1u << j)) && sf != leg_surface_a<KM>(seq, j) && sf != leg_surface_b<KM>(seq, j, k)) {
                     if (lane == 0) cand[nc] = tube_entry(~s.root, j);
                     ++nc;
                 }
@@ -774,22 +838,21 @@ __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool o
                     const bool valid = slot < nf;
                     const unsigned v = valid ? (unsigned)fin[slot] : 0u;
                     const int n = (int)(v & RT_TUBE_IDX_MASK), j = (int)(v >> RT_TUBE_TAG_SHIFT);
-                    const float* t = tube + 8 * j;
+                    const float4 t0 = tube[3 * j], t1 = tube[3 * j + 1];
                     RayBox crb;
-                    crb.ix = t[0];
-                    crb.iy = t[1];
-                    crb.iz = t[2];
-                    crb.oix = t[3];
-                    crb.oiy = t[4];
-                    crb.oiz = t[5];
-                    const float r = t[6];
-                    const float* q = (const float*)(s.node4 + 8 * n);
+                    crb.ix = t0.x;
+                    crb.iy = t0.y;
+                    crb.iz = t0.z;
+                    crb.oix = t1.x;
+                    crb.oiy = t1.y;
+                    crb.oiz = t1.z;
+                    const float r = t0.w;
+                    const float* q = (const float*)(s.node4 + 8 * (int64_t)n);
                     const int ref = __float_as_int(q[24 + e]);
                     // a leaf of one of the leg's end-point surfaces is never a candidate of that leg
                     const int lsf = __float_as_int(q[28 + e]);
-                    const int sa = leg_surface_a<KM>(seq, j);
-                    const int sb = leg_surface_b<KM>(seq, j, k);
-                    const bool skip = lsf >= 0 && (lsf == sa || lsf == sb);
+                    const bool skip = lsf >= 0 && (lsf == __float_as_int(t1.w) ||
+                                                   lsf == __float_as_int(tube[3 * j + 2].x));
                     const bool hit = valid && ref != RT_NODE4_EMPTY && !skip &&
                                      slab1(q[e] - r, q[4 + e] + r, q[8 + e] - r, q[12 + e] + r, q[16 + e] - r,
                                            q[20 + e] + r, crb, -1e-3f, 1.001f);
@@ -833,17 +896,16 @@ __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool o
     for (int i = 0; i < nc; ++i) {
         const unsigned v = (unsigned)__builtin_amdgcn_readfirstlane(cand[i]);
         const int slot = (int)(v & RT_TUBE_IDX_MASK), j = (int)(v >> RT_TUBE_TAG_SHIFT);
-        const float4 a = s.tri4[3 * slot], b = s.tri4[3 * slot + 1], c = s.tri4[3 * slot + 2];
-        const int sf = __float_as_int(b.w);
-        const int sa = j == 0 ? -1 : seq[j - 1];
-        const int sb = j == k ? -1 : seq[j];
-        if (sf == sa || sf == sb) continue;
+        const float4* tp = s.tri4 + 3 * (int64_t)slot;
+        const float4 a = tp[0], b = tp[1], c = tp[2];
         const float* r0 = lb + j * 7 * 64 + lane;
         const float tmax = r0[384];
-        if (ok && tmax > tmin && !(blocked & (1u << j))) {
-            float t;
-            if (mt_hit(r0[0], r0[64], r0[128], r0[192], r0[256], r0[320], a, b, c, tmin, tmax, t)) blocked |= 1u << j;
-        }
+        const float ox = r0[0], oy = r0[64], oz = r0[128], dx = r0[192], dy = r0[256], dz = r0[320];
+        const bool open = ok && tmax > tmin && !(blocked & (1u << j));
+        // most candidates are missed by every lane: decided without the division
+        if (__ballot(open && mt_maybe(ox, oy, oz, dx, dy, dz, a, b, c)) == 0ull) continue;
+        float t;
+        if (open && mt_hit(ox, oy, oz, dx, dy, dz, a, b, c, tmin, tmax, t)) blocked |= 1u << j;
     }
     return blocked;
 }
@@ -907,25 +969,56 @@ __device__ inline void triangle_projection(const double* v, double* out, int32_t
     *axes = (area == 0.0) ? 16 : (i0 | (i1 << 2));
 }
 
+// Edge functions of the containment test, from the projection: per edge the
+// lexicographically smaller end point and the edge vector from it, negated
+// where the test negates (exact either way), so that one formula
+//   w = dx (py - by) - dy (px - bx)
+// gives the test's value; and per edge the threshold it must exceed: 0, or,
+// for a top-left edge (0 counts as inside), the largest negative number.  The
+// test is then three edge functions of five operations and a compare; derived
+// from the vertices at every test it was some 75 vector instructions.
+// [0] the axis the projection drops (as an integer), then per edge bx, by, dx,
+// dy and the threshold (infinite for a degenerate triangle).
+__device__ inline void triangle_edges(const double* q6, int32_t axes, double* out)
+{
+#pragma clang fp contract(off)
+    const int i0 = axes & 3;   // kept axes are drop + 1, drop + 2
+    const long long drop = (i0 + 2) % 3;
+    __builtin_memcpy(&out[0], &drop, 8);
+    for (int i = 0; i < 3; ++i) {
+        // edges b c, c a, a b
+        const int u = (i + 1) % 3, v = (i + 2) % 3;
+        const double sx = q6[2 * u], sy = q6[2 * u + 1], ex = q6[2 * v], ey = q6[2 * v + 1];
+        const bool s_first = (sx < ex) || (sx == ex && sy < ey);
+        out[5 * i + 1] = s_first ? sx : ex;
+        out[5 * i + 2] = s_first ? sy : ey;
+        out[5 * i + 3] = s_first ? ex - sx : -(sx - ex);
+        out[5 * i + 4] = s_first ? ey - sy : -(sy - ey);
+        out[5 * i + 5] = (axes & 16) ? __builtin_inf() : (top_left(sx, sy, ex, ey) ? -4.9406564584124654e-324 : 0.0);
+    }
+}
+
 // p on the triangle's plane inside triangle t?  Half-open top-left rule in
 // the triangle's projection: a point on an edge belongs to the triangle only
 // if that edge is top-left, so a point on an edge shared by two coplanar
 // triangles belongs to exactly one of them.
-__device__ inline bool contains_proj(const SceneView& s, int t, const double* p)
+// UNIFORM: the same triangle for every lane of the wave, all its edges at once
+// (scalar loads); else edge by edge, so that a lane whose point is outside the
+// first reads half the record.
+template <bool UNIFORM>
+__device__ __forceinline__ bool contains_proj(const SceneView& s, int t, const double* p)
 {
 #pragma clang fp contract(off)
-    const int ax = s.t_axes[t];
-    if (ax & 16) return false;
-    const double* q6 = s.t_proj + 6 * t;
-    const double a0 = q6[0], a1 = q6[1], b0 = q6[2], b1 = q6[3], c0 = q6[4], c1 = q6[5];
-    const double q0 = p[ax & 3], q1 = p[(ax >> 2) & 3];
-    double w0 = edge2(b0, b1, c0, c1, q0, q1);
-    double w1 = edge2(c0, c1, a0, a1, q0, q1);
-    double w2 = edge2(a0, a1, b0, b1, q0, q1);
-    bool in0 = (w0 > 0.0) || (w0 == 0.0 && top_left(b0, b1, c0, c1));
-    bool in1 = (w1 > 0.0) || (w1 == 0.0 && top_left(c0, c1, a0, a1));
-    bool in2 = (w2 > 0.0) || (w2 == 0.0 && top_left(a0, a1, b0, b1));
-    return in0 && in1 && in2;
+    const double* e = s.t_edge + RT_EDGE * (int64_t)t;
+    const int drop = ((const int*)e)[0];
+    const double px = p[0], py = p[1], pz = p[2];
+    const double q0 = drop == 0 ? py : drop == 1 ? pz : px;
+    const double q1 = drop == 0 ? pz : drop == 1 ? px : py;
+    const double w0 = e[3] * (q1 - e[2]) - e[4] * (q0 - e[1]);
+    if (!UNIFORM && !(w0 > e[5])) return false;
+    const double w1 = e[8] * (q1 - e[7]) - e[9] * (q0 - e[6]);
+    const double w2 = e[13] * (q1 - e[12]) - e[14] * (q0 - e[11]);
+    return w0 > e[5] && w1 > e[10] && w2 > e[15];
 }
 
 __device__ __forceinline__ double plane_side(const double* pl, const double* p)
@@ -943,35 +1036,36 @@ template <bool CNT = false>
 __device__ inline int surface_contains(const SceneView& s, int sf, const double* p, WorkCount* wc = nullptr)
 {
     const double* bx = s.s_box + 6 * sf;
-    if (p[0] < bx[0] || p[1] < bx[1] || p[2] < bx[2] || p[0] > bx[3] || p[1] > bx[4] || p[2] > bx[5])
-        return -1;
+    const double px = p[0], py = p[1], pz = p[2];
+    if (px < bx[0] || py < bx[1] || pz < bx[2] || px > bx[3] || py > bx[4] || pz > bx[5]) return -1;
     const int gax = CNT ? -1 : s.g_axes[sf];
     if (gax >= 0) {
         const double* fr = s.g_frame + 4 * sf;
-        const int cell = sgrid_index(p[gax & 3], fr[0], fr[2]) * RT_SGRID + sgrid_index(p[(gax >> 2) & 3], fr[1], fr[3]);
+        const double u = (gax & 3) == 0 ? px : (gax & 3) == 1 ? py : pz;
+        const double v = (gax >> 2) == 0 ? px : (gax >> 2) == 1 ? py : pz;
+        const int cell = sgrid_index(u, fr[0], fr[2]) * RT_SGRID + sgrid_index(v, fr[1], fr[3]);
         const int b = s.s_ptr[sf];
         const int64_t beg = (int64_t)b * RT_SGRID_CELLS + (int64_t)cell * (s.s_ptr[sf + 1] - b);
         const int cnt = s.g_cnt[sf * RT_SGRID_CELLS + cell];
         for (int j = 0; j < cnt; ++j) {
             const int t = s.g_tris[beg + j];
-            if (contains_proj(s, t, p)) return t;
+            if (contains_proj<false>(s, t, p)) return t;
         }
         return -1;
     }
     for (int j = s.s_ptr[sf]; j < s.s_ptr[sf + 1]; ++j) {
         int t = s.s_tris[j];
         if (CNT) wc->contain++;
-        if (contains_proj(s, t, p)) return t;
+        if (contains_proj<false>(s, t, p)) return t;
     }
     return -1;
 }
 
-// Mirror p in plane pl (n, c).
+// Mirror p in plane pl (n, c, n . n and its reciprocal): p - (2 side / n . n) n.
 __device__ __forceinline__ void mirror(const double* pl, const double* p, double* out)
 {
 #pragma clang fp contract(off)
-    double nn = pl[0] * pl[0] + pl[1] * pl[1] + pl[2] * pl[2];
-    double f = 2.0 * plane_side(pl, p) / nn;
+    const double f = div_by(2.0 * plane_side(pl, p), pl[4], pl[5]);
     out[0] = p[0] - f * pl[0];
     out[1] = p[1] - f * pl[1];
     out[2] = p[2] - f * pl[2];
@@ -990,11 +1084,11 @@ __device__ inline bool image_backtrace(const SceneView& s, const int* seq, int k
 #pragma unroll
     for (int i = KM; i >= 1; --i) {
         if (i > k) continue;
-        const double* pl = s.s_plane + 4 * seq[i - 1];
+        const double* pl = s.s_plane + RT_PLANE * seq[i - 1];
         double w0 = Q[0] - I[i][0], w1 = Q[1] - I[i][1], w2 = Q[2] - I[i][2];
         double den = pl[0] * w0 + pl[1] * w1 + pl[2] * w2;
         if (den == 0.0) return false;
-        double sp = (pl[3] - (pl[0] * I[i][0] + pl[1] * I[i][1] + pl[2] * I[i][2])) / den;
+        double sp = div_fast(pl[3] - (pl[0] * I[i][0] + pl[1] * I[i][1] + pl[2] * I[i][2]), den);
         if (!(sp > 0.0 && sp < 1.0)) return false;
         double p[3] = {I[i][0] + sp * w0, I[i][1] + sp * w1, I[i][2] + sp * w2};
         int t = surface_contains(s, seq[i - 1], p);
@@ -1006,7 +1100,7 @@ __device__ inline bool image_backtrace(const SceneView& s, const int* seq, int k
 #pragma unroll
     for (int i = 0; i < KM; ++i) {
         if (i >= k) break;
-        const double* pl = s.s_plane + 4 * seq[i];
+        const double* pl = s.s_plane + RT_PLANE * seq[i];
         double prev[3], next[3];
         for (int q = 0; q < 3; ++q) {
             prev[q] = i == 0 ? I[0][q] : P[i > 0 ? i - 1 : 0][q];

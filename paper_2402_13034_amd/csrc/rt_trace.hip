@@ -385,7 +385,7 @@ __global__ void k_cand_prep(const uint64_t* keys, int64_t n, SceneView s, double
         cseq[KM * c + j] = seq[j];
         if (j < k) {
             double o[3];
-            mirror(s.s_plane + 4 * seq[j], I, o);
+            mirror(s.s_plane + RT_PLANE * seq[j], I, o);
             I[0] = o[0];
             I[1] = o[1];
             I[2] = o[2];
@@ -628,6 +628,29 @@ __device__ __forceinline__ double seg_len(const double* a, const double* b)
     return sqrt(w0 * w0 + w1 * w1 + w2 * w2);
 }
 
+// Reflection points of a cell whose geometry k_geo_mask accepted: the
+// back-trace of image_backtrace without its tests (they have passed; the
+// triangles are looked up for the paths whose legs are clear).
+template <int KM>
+__device__ __forceinline__ void cell_points(const SceneView& s, const int* seq, int k, const double* img,
+                                            const double* X, double (*P)[3])
+{
+#pragma clang fp contract(off)
+    double Q[3] = {X[0], X[1], X[2]};
+#pragma unroll
+    for (int i = KM; i >= 1; --i) {
+        if (i > k) continue;
+        const double* pl = s.s_plane + RT_PLANE * (int64_t)seq[i - 1];
+        const double* I = img + 3 * (i - 1);
+        const double w0 = Q[0] - I[0], w1 = Q[1] - I[1], w2 = Q[2] - I[2];
+        const double den = pl[0] * w0 + pl[1] * w1 + pl[2] * w2;
+        const double sp = div_fast(pl[3] - (pl[0] * I[0] + pl[1] * I[1] + pl[2] * I[2]), den);
+        P[i - 1][0] = Q[0] = I[0] + sp * w0;
+        P[i - 1][1] = Q[1] = I[1] + sp * w1;
+        P[i - 1][2] = Q[2] = I[2] + sp * w2;
+    }
+}
+
 template <bool BRUTE, bool FIELD, int STK, int KM>
 __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, TraceConst tc, double sx, double sy,
                                                  double sz, const double* rx, const uint64_t* cells, int64_t n,
@@ -646,8 +669,12 @@ __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, Trace
         int tri[KM];
 #pragma unroll
         for (int j = 0; j < KM; ++j) tri[j] = -1;
-        int k;
-        bool ok = geo_path<KM>(s, cv, c, S, X, P, tri, k);
+        int sq[KM];
+#pragma unroll
+        for (int j = 0; j < KM; ++j) sq[j] = cv.seq[KM * c + j];
+        const int k = cv.k[c];
+        cell_points<KM>(s, sq, k, cv.img + 3 * KM * c, X, P);
+        bool ok = true;
         float Ft = 1.0f, Fr = 1.0f;
         double V[KM + 2][3];
         path_points<KM>(S, P, X, k, V);
@@ -662,9 +689,6 @@ __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, Trace
             const bool on_r = pattern_gate_amp(tc.rxa.pattern, tc.rxa.param, vl, tc.rxa.axis, tc.rxa.axis_norm, Fr);
             ok = on_t && on_r;
         }
-        int sq[KM];
-#pragma unroll
-        for (int j = 0; j < KM; ++j) sq[j] = cv.seq[KM * c + j];
 #pragma unroll
         for (int j = 0; j <= KM; ++j) {
             if (j > k || !ok) break;
@@ -674,6 +698,10 @@ __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, Trace
             ++nseg;
             if (leg_blocked<BRUTE>(s, V[j], V[j + 1], sa, sb, stack + threadIdx.x, LEG_B)) ok = false;
         }
+        if (ok)
+#pragma unroll
+            for (int j = 0; j < KM; ++j)
+                if (j < k) tri[j] = surface_contains(s, sq[j], P[j]);
         valid[i] = ok ? 1 : 0;
         PathRec<KM> pr;
         pr.rx = (int32_t)r;
@@ -1050,16 +1078,16 @@ __device__ inline bool image_backtrace_hint(const SceneView& s, const int* seq, 
 #pragma unroll
     for (int i = KM; i >= 1; --i) {
         if (i > k) continue;
-        const double* pl = s.s_plane + 4 * seq[i - 1];
+        const double* pl = s.s_plane + RT_PLANE * seq[i - 1];
         double w0 = Q[0] - I[i][0], w1 = Q[1] - I[i][1], w2 = Q[2] - I[i][2];
         double den = pl[0] * w0 + pl[1] * w1 + pl[2] * w2;
         if (den == 0.0) return false;
-        double sp = (pl[3] - (pl[0] * I[i][0] + pl[1] * I[i][1] + pl[2] * I[i][2])) / den;
+        double sp = div_fast(pl[3] - (pl[0] * I[i][0] + pl[1] * I[i][1] + pl[2] * I[i][2]), den);
         if (!(sp > 0.0 && sp < 1.0)) return false;
         double p[3] = {I[i][0] + sp * w0, I[i][1] + sp * w1, I[i][2] + sp * w2};
         int h = hint[i - 1];
         if (CNT && h >= 0) wc->contain++;
-        int t = (h >= 0 && contains_proj(s, h, p)) ? h : surface_contains<CNT>(s, seq[i - 1], p, wc);
+        int t = (h >= 0 && contains_proj<true>(s, h, p)) ? h : surface_contains<CNT>(s, seq[i - 1], p, wc);
         if (t < 0) return false;
         tri[i - 1] = t;
         P[i - 1][0] = p[0]; P[i - 1][1] = p[1]; P[i - 1][2] = p[2];
@@ -1068,7 +1096,7 @@ __device__ inline bool image_backtrace_hint(const SceneView& s, const int* seq, 
 #pragma unroll
     for (int i = 0; i < KM; ++i) {
         if (i >= k) break;
-        const double* pl = s.s_plane + 4 * seq[i];
+        const double* pl = s.s_plane + RT_PLANE * seq[i];
         double prev[3], next[3];
         for (int q = 0; q < 3; ++q) {
             prev[q] = i == 0 ? I[0][q] : P[i > 0 ? i - 1 : 0][q];
@@ -1102,7 +1130,7 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
     // per-wave frontier and candidate lists of the tube walk
     __shared__ int tfront[RIS_B / 64][2 * RT_TUBE_FRONT];
     __shared__ int tcand[RIS_B / 64][RT_TUBE_CAND];
-    __shared__ float ttube[RIS_B / 64][8 * (KM + 1)];
+    __shared__ float4 ttube[RIS_B / 64][3 * (KM + 1)];
     constexpr int US = useq_stride(KM);
     static_assert(RT_STACK4 >= STK, "wave stack");
     WorkCount wc;
@@ -1169,7 +1197,7 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
                     I[0][2] = E[2];
 #pragma unroll
                     for (int j = 0; j < KM; ++j)
-                        if (j < k) mirror(s.s_plane + 4 * seq[j], I[j], I[j + 1]);
+                        if (j < k) mirror(s.s_plane + RT_PLANE * seq[j], I[j], I[j + 1]);
                     if (ok) ok = image_backtrace_hint<CNT, KM>(s, seq, hint, k, I, X, P, tri, &wc);
                 }
                 float Fout = 0.0f, Fr = 0.0f;
@@ -1195,14 +1223,14 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
                         const double* A = j == 0 ? E : P[j - 1];
                         const double* B = j == k ? X : P[j];
                         double w0 = B[0] - A[0], w1 = B[1] - A[1], w2 = B[2] - A[2];
-                        double L = sqrt(w0 * w0 + w1 * w1 + w2 * w2);
+                        double L, il;   // the leg ray's direction as leg_blocked forms it
+                        sqrt_inv(w0 * w0 + w1 * w1 + w2 * w2, L, il);
                         if (FRES) Lk[j] = L;
                         Dr += L;
                         float* lb = &legbuf[wib][j][0][lane];
                         lb[0 * 64] = (float)A[0];
                         lb[1 * 64] = (float)A[1];
                         lb[2 * 64] = (float)A[2];
-                        const double il = 1.0 / L;   // the leg ray's direction as leg_blocked forms it
                         lb[3 * 64] = (float)(w0 * il);
                         lb[4 * 64] = (float)(w1 * il);
                         lb[5 * 64] = (float)(w2 * il);
@@ -1261,7 +1289,8 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
                 }
             } else {
                 // every leg at once; legs are counted as the sequential test would (up to the first blocked one)
-                const unsigned res = legs_blocked_tube<KM>(s, ok, k, seq, &legbuf[wib][0][0][0], ttube[wib],
+                const float end[3] = {(float)X[0], (float)X[1], (float)X[2]};
+                const unsigned res = legs_blocked_tube<KM>(s, ok, k, seq, &legbuf[wib][0][0][0], end, ttube[wib],
                                                        tfront[wib], tcand[wib], my_stack);
                 n_fallback += (res & RT_TUBE_FELL_BACK) ? 1u : 0u;   // same on every lane
                 const unsigned bl = res & ~RT_TUBE_FELL_BACK;

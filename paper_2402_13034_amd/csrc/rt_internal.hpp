@@ -652,6 +652,113 @@ __device__ int closest_hit_wave4(const SceneView& s, bool active, float ox, floa
     return slot_best;
 }
 
+// v of a quad's four lanes, or-ed (quad_perm [1,0,3,2], then [2,3,0,1])
+__device__ __forceinline__ int quad_or(int v)
+{
+    v |= __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, true);
+    return v | __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, true);
+}
+
+// Closest hit with four lanes per ray, lane e of a quad testing entry e of the
+// 4-wide node its ray is at (16 rays walk on their own in a wave).  A leaf
+// entry that is hit is tested at once, the four of a node side by side; the
+// inner entries that are hit are ordered by distance within the quad, the
+// nearest is visited next and the others wait on the quad's stack in LDS with
+// their distances (entries that the best hit has passed are dropped unvisited).
+// For rays too sparse to share nodes, where closest_hit_wave4 visits the union
+// of 64 rays' nodes.  The answer is the same: the lowest (t, triangle id) over
+// every triangle but skip_tri with tmin < t; the same on the four lanes.
+// st: this quad's stack, `stride` int2 between its entries.
+__device__ __forceinline__ int closest_hit_quad(const SceneView& s, bool active, float ox, float oy, float oz,
+                                                float dx, float dy, float dz, float tmin, int skip_tri, int2* st,
+                                                int stride, float& t_best, int& id_best)
+{
+    const float inf = __builtin_inff();
+    const int e = threadIdx.x & 3;
+    t_best = inf;
+    id_best = 0x7fffffff;
+    int slot_best = -1;
+    // a leaf entry's triangle, then the best of the quad
+    auto leaf = [&](bool test, int slot) {
+        float t = inf;
+        int id = 0x7fffffff;
+        if (test) {
+            const float4* tp = s.tri4 + 3 * (int64_t)slot;
+            const float4 a = tp[0], b = tp[1], c = tp[2];
+            id = __float_as_int(a.w);
+            float th;
+            if (id != skip_tri && mt_hit(ox, oy, oz, dx, dy, dz, a, b, c, tmin, inf, th))
+                t = th;
+            else
+                id = 0x7fffffff;
+        }
+        auto take = [&](float to, int ido, int so) {
+            const bool better = to < t || (to == t && ido < id);
+            t = better ? to : t;
+            id = better ? ido : id;
+            slot = better ? so : slot;
+        };
+        take(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0xB1, 0xF, 0xF, true)),
+             __builtin_amdgcn_update_dpp(0, id, 0xB1, 0xF, 0xF, true),
+             __builtin_amdgcn_update_dpp(0, slot, 0xB1, 0xF, 0xF, true));
+        take(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(t), 0x4E, 0xF, 0xF, true)),
+             __builtin_amdgcn_update_dpp(0, id, 0x4E, 0xF, 0xF, true),
+             __builtin_amdgcn_update_dpp(0, slot, 0x4E, 0xF, 0xF, true));
+        if (t < t_best || (t == t_best && id < id_best)) {
+            t_best = t;
+            id_best = id;
+            slot_best = slot;
+        }
+    };
+    if (s.n_tri == 0) return -1;
+    if (s.root < 0) {
+        leaf(active && e == 0, ~s.root);
+        return slot_best;
+    }
+    const RayBox rb = make_raybox(ox, oy, oz, dx, dy, dz);
+    int node = s.root, sp = 0;
+    bool walking = active;
+    while (__ballot(walking) != 0ull) {
+        bool hit = false, inner = false;
+        int ref = 0;
+        float tn = inf;
+        if (walking) {
+            const float* q = (const float*)(s.node4 + 8 * (int64_t)node) + e;
+            ref = __float_as_int(q[24]);
+            hit = slab1t(q[0], q[4], q[8], q[12], q[16], q[20], rb, tmin, t_best, tn) && ref != RT_NODE4_EMPTY;
+        }
+        if (__ballot(hit && ref < 0) != 0ull) leaf(hit && ref < 0, ~ref);
+        inner = hit && ref >= 0 && tn <= t_best;
+        // rank among the quad's inner hits by (distance, entry)
+        const int k = inner ? __float_as_int(tn) : 0x7f800000;   // distances are positive: bits order as they do
+        const int k0 = __builtin_amdgcn_update_dpp(0, k, 0x00, 0xF, 0xF, true);
+        const int k1 = __builtin_amdgcn_update_dpp(0, k, 0x55, 0xF, 0xF, true);
+        const int k2 = __builtin_amdgcn_update_dpp(0, k, 0xAA, 0xF, 0xF, true);
+        const int k3 = __builtin_amdgcn_update_dpp(0, k, 0xFF, 0xF, 0xF, true);
+        const int rank = (k0 < k || (k0 == k && 0 < e)) + (k1 < k || (k1 == k && 1 < e)) +
+                         (k2 < k || (k2 == k && 2 < e)) + (k3 < k);
+        const int n = (k0 < 0x7f800000) + (k1 < 0x7f800000) + (k2 < 0x7f800000) + (k3 < 0x7f800000);
+        if (inner && rank > 0) st[(sp + n - 1 - rank) * stride] = make_int2(ref, k);
+        const int near = quad_or(inner && rank == 0 ? ref : 0);
+        if (walking) {
+            node = near;
+            sp += n > 0 ? n - 1 : 0;
+            if (n == 0) {   // nothing below: the nearest waiting entry that the best hit has not passed
+                walking = false;
+                while (sp > 0) {
+                    const int2 top = st[--sp * stride];
+                    if (__int_as_float(top.y) <= t_best) {
+                        node = top.x;
+                        walking = true;
+                        break;
+                    }
+                }
+            }
+        }
+    }
+    return slot_best;
+}
+
 // --------------------------------------------------------------------------
 // Tube walk for a wave of nearly parallel segments (the legs of one slot for
 // 64 RIS elements).  Every lane's tested segment o + t d, t in [tmin, tmax],

@@ -313,6 +313,92 @@ __global__ __launch_bounds__(DISC_B) void k_discover(SceneView s, double sx, dou
     }
 }
 
+// Discovery with four lanes per ray (closest_hit_quad), for rays that are
+// sparse against the triangles.  Otherwise as k_discover: the same rows, hits,
+// keys and counts; a ray's key equal to that of the ray four lanes to the left
+// is inserted there.  DQ_STK: stack entries per ray.
+template <int STK, int KM>
+__global__ __launch_bounds__(DISC_B) void k_discover_quad(SceneView s, double sx, double sy, double sz,
+                                                          const int32_t* perm, const int32_t* off, int64_t rows,
+                                                          int hemi, double hx, double hy, double hz, int K,
+                                                          int32_t* hits, unsigned long long* segs,
+                                                          unsigned long long* table, uint64_t mask,
+                                                          uint64_t max_probe, int* overflow)
+{
+    constexpr int W = KM > RT_KM_SMALL ? 2 : 1;
+    constexpr int DQ_STK = 3 * (STK / 2) + 4;   // a 4-wide node leaves at most three entries behind per two levels
+    __shared__ int2 stack[DQ_STK * (DISC_B / 4)];
+    const int64_t t = ((int64_t)blockIdx.x * DISC_B + threadIdx.x) >> 2;
+    const int e = threadIdx.x & 3;
+    unsigned nseg = 0;
+    uint64_t keys[KM], keys1[KM];
+#pragma unroll
+    for (int q = 0; q < KM; ++q) keys[q] = keys1[q] = 0ull;
+    const int64_t ch = t / RT_FIB_CHUNK;
+    const int64_t i = ch * RT_FIB_CHUNK + perm[(off[ch] + (int)(t % RT_FIB_CHUNK)) % RT_FIB_CHUNK];
+    double d64[3] = {0.0, 0.0, 1.0};
+    bool alive = i < rows;
+    if (alive) {
+        fib_dir(i, rows, d64);
+        alive = hemi ? (d64[0] * hx + d64[1] * hy + d64[2] * hz) > 0.0 : true;
+    }
+    const bool alive0 = alive;
+    float ox = (float)sx, oy = (float)sy, oz = (float)sz;
+    float dx = (float)d64[0], dy = (float)d64[1], dz = (float)d64[2];
+    int skip = -1;
+    uint64_t acc = 0, acc1 = 0;
+    int hid[KM];
+#pragma unroll
+    for (int q = 0; q < KM; ++q) hid[q] = -1;
+    int2* st = stack + (threadIdx.x >> 2);
+    for (int b = 0; b < K; ++b) {
+        if (__ballot(alive) == 0ull) break;
+        float tt;
+        int id;
+        if (alive && e == 0) ++nseg;
+        const int slot =
+            closest_hit_quad(s, alive, ox, oy, oz, dx, dy, dz, (float)RT_EPS, skip, st, DISC_B / 4, tt, id);
+        alive = alive && slot >= 0;
+        if (alive) {
+            const float4 tb = s.tri4[3 * (int64_t)slot + 1], tc = s.tri4[3 * (int64_t)slot + 2];
+            const uint64_t field = (uint64_t)(__float_as_int(tb.w) + 1);
+            if (W == 1 || b < 3)
+                acc |= field << (RT_KEY_BITS * b);
+            else
+                acc1 |= field << (RT_KEY_BITS * (b - 3));
+#pragma unroll
+            for (int q = 0; q < KM; ++q) {
+                hid[q] = b == q ? id : hid[q];
+                keys[q] = b == q ? acc : keys[q];
+                if (W == 2) keys1[q] = b == q ? acc1 : keys1[q];
+            }
+            const float px = ox + tt * dx, py = oy + tt * dy, pz = oz + tt * dz;
+            reflect32(tb, tc, dx, dy, dz);
+            ox = px;
+            oy = py;
+            oz = pz;
+            skip = id;
+        }
+    }
+    if (hits && alive0 && e == 0)
+#pragma unroll
+        for (int b = 0; b < KM; ++b)
+            if (b < K) hits[i * K + b] = hid[b];
+#pragma unroll
+    for (int b = 0; b < KM; ++b) {
+        const uint64_t left = __shfl_up(keys[b], 4, 64);
+        const uint64_t left1 = W == 2 ? __shfl_up(keys1[b], 4, 64) : 0ull;
+        const bool first = (threadIdx.x & 63) < 4 || left != keys[b] || (W == 2 && left1 != keys1[b]);
+        if (b < K && e == 0 && keys[b] != 0ull && first) {
+            if (W == 1)
+                hash_insert(table, mask, max_probe, keys[b], overflow);
+            else
+                hash_insert2(table, mask, max_probe, keys[b], keys1[b], overflow);
+        }
+    }
+    wave_count_add(segs, nseg);
+}
+
 // --------------------------------------------------------------------------
 // 2. candidate keys: surface ids + 1, 21 bits per bounce; 0 = none
 // --------------------------------------------------------------------------
@@ -1493,6 +1579,21 @@ static void prepare_table(Ctx& c, const TraceArgs& a, Branch& br, hipStream_t st
     HIP_CHECK(hipMemsetAsync(br.table.p, 0, br.table.bytes, st));
 }
 
+// Four lanes per ray (k_discover_quad) instead of a wave walking for 64 rays?
+// The wave walk visits the union of its rays' nodes, one after the other: with
+// few rays against the triangles that is many times a ray's own nodes, and the
+// launch has too few waves to hide the chain.  Its time falls with the rays'
+// density, that of the quads grows with the rays (1.3 ns a ray and bounce pair).
+// Both sources, us, wave / quad: 10^4 rays and 200 000 triangles 1204 / 76;
+// 10^5 and 49 000 747 / 203, and 1908 283 / 191 (order 3), and 848 115 / 187;
+// 2 10^5 and 17 000 317 / 336, and 49 000 708 / 347; 4 10^5 and 49 000 478 /
+// 642, and 200 000 1629 / 672; 10^6 and 1.08 million 2614 / 4086.  The line
+// between them runs near 4000 n_tri^0.4 rays, and below 5 10^5.
+static bool sparse_rays(int64_t n_rays, int64_t n_tri)
+{
+    return n_tri >= 64 && n_rays <= 500000 && (double)n_rays <= 4000.0 * std::pow((double)n_tri, 0.4);
+}
+
 template <int KM>
 static void cand_phase_a(Ctx& c, const SceneView& sv, int stk, const TraceArgs& a, bool brute, bool exhaustive,
                          bool keep_hits, Channel& ch, Branch& br, unsigned long long* d_segs)
@@ -1541,13 +1642,22 @@ static void cand_phase_a(Ctx& c, const SceneView& sv, int stk, const TraceArgs& 
         const int64_t n_launch = (rows + RT_FIB_CHUNK - 1) / RT_FIB_CHUNK * RT_FIB_CHUNK;
         const bool count = (a.tc.flags & 16) != 0 && !brute;
         if (br.ev_disc[0]) HIP_CHECK(hipEventRecord(br.ev_disc[0], st));
-        SEL_BOOL(brute, BR, SEL_BOOL(count, CN,
-                 SEL_STK(stk, hipLaunchKernelGGL((k_discover<BR, STK, KM, CN>), dim3(nblk(n_launch, DISC_B)),
-                                                 dim3(DISC_B), 0, st, sv, src[0], src[1], src[2], perm, off, rows,
-                                                 hemi_n ? 1 : 0, hemi_n ? hemi_n[0] : 0.0, hemi_n ? hemi_n[1] : 0.0,
-                                                 hemi_n ? hemi_n[2] : 0.0, K, keep_hits ? hits.as<int32_t>() : nullptr,
-                                                 d_segs, table.as<unsigned long long>(), (uint64_t)(cap - 1), max_probe,
-                                                 (int*)(br.d_app + 1), br.d_work))));
+        if (!brute && !count && sparse_rays(a.n_rays, sv.n_tri)) {
+            SEL_STK(stk, hipLaunchKernelGGL((k_discover_quad<STK, KM>), dim3(nblk(4 * n_launch, DISC_B)), dim3(DISC_B),
+                                            0, st, sv, src[0], src[1], src[2], perm, off, rows, hemi_n ? 1 : 0,
+                                            hemi_n ? hemi_n[0] : 0.0, hemi_n ? hemi_n[1] : 0.0,
+                                            hemi_n ? hemi_n[2] : 0.0, K, keep_hits ? hits.as<int32_t>() : nullptr,
+                                            d_segs, table.as<unsigned long long>(), (uint64_t)(cap - 1), max_probe,
+                                            (int*)(br.d_app + 1)));
+        } else {
+            SEL_BOOL(brute, BR, SEL_BOOL(count, CN,
+                     SEL_STK(stk, hipLaunchKernelGGL((k_discover<BR, STK, KM, CN>), dim3(nblk(n_launch, DISC_B)),
+                                                     dim3(DISC_B), 0, st, sv, src[0], src[1], src[2], perm, off, rows,
+                                                     hemi_n ? 1 : 0, hemi_n ? hemi_n[0] : 0.0, hemi_n ? hemi_n[1] : 0.0,
+                                                     hemi_n ? hemi_n[2] : 0.0, K, keep_hits ? hits.as<int32_t>() : nullptr,
+                                                     d_segs, table.as<unsigned long long>(), (uint64_t)(cap - 1), max_probe,
+                                                     (int*)(br.d_app + 1), br.d_work))));
+        }
         HIP_CHECK(hipGetLastError());
         if (br.ev_disc[1]) HIP_CHECK(hipEventRecord(br.ev_disc[1], st));
     }

@@ -77,6 +77,29 @@ def test_tree_above_surfaces(ctx, n_surf):
         assert np.array_equal(a, b)
 
 
+# either side of the line between four lanes per ray and a wave per 64 rays, at orders of one- and two-word keys
+@pytest.mark.parametrize("n_tri,n_rays,order", [(63, 3_000, 2), (64, 3_000, 2), (1908, 50_000, 3), (1908, 90_000, 3),
+                                                (1908, 20_000, 5), (1, 500, 1)])
+def test_discovery_lanes_per_ray(ctx, n_tri, n_rays, order):
+    from paper_2402_13034_amd import risrt
+    p = _trimmed(max(n_tri, 2), 3)
+    if n_tri == 1:
+        p.scene = synth.Scene(p.scene.V, p.scene.T[:1].copy(), p.scene.refl_re[:1].copy(), p.scene.refl_im[:1].copy(),
+                              np.zeros(1, np.int32))
+    p.order, p.n_rays = order, n_rays
+    print("case discovery", n_tri, n_rays, order, flush=True)
+    outs = []
+    for brute in (0, risrt.FLAG_BRUTE_FORCE):
+        scene, ris = risrt.upload_problem(ctx, p)
+        ch, st = risrt.trace_problem(ctx, p, scene, ris, flags=risrt.FLAG_KEEP_HITS | brute)
+        outs.append((ctx.hits_read(ch, 0, order), ctx.hits_read(ch, 1, order), ctx.candidates_read(ch, 0),
+                     ctx.candidates_read(ch, 1), st["discovery_segments"], *ctx.channel_read(ch)))
+        for h in (ch, scene, ris):
+            ctx.destroy(h)
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
+
+
 def test_counting_walk_is_the_morton_tree(ctx):
     """The counting builds walk the scene's Morton tree, whose boxes are made
     for them: the same hits and fields, and work that does not change between

@@ -151,6 +151,37 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_tiles(const In* in, int64_t n, 
         *total = (tile_off ? tile_off[blockIdx.x] : (Out)0) + tot;
 }
 
+// Up to SCAN_ONE_MAX values in one workgroup that carries its sum from one
+// stretch of 8192 to the next: one launch of 5 us where the three of the tiled
+// scan take 14 (a receiver grid's counts; 4096 values).
+constexpr int SCAN_ONE_T = 1024;
+constexpr int64_t SCAN_ONE_MAX = 32768;
+template <class In, class Out>
+__global__ __launch_bounds__(SCAN_ONE_T) void k_scan_one(const In* in, int64_t n, Out* out, Out* total)
+{
+    __shared__ Out wsum[SCAN_ONE_T / 64];
+    Out carry = 0;
+    for (int64_t b0 = 0; b0 < n; b0 += SCAN_ONE_T * SCAN_IPT) {
+        const int64_t base = b0 + (int64_t)threadIdx.x * SCAN_IPT;
+        Out v[SCAN_IPT];
+        Out s = 0;
+#pragma unroll
+        for (int j = 0; j < SCAN_IPT; ++j) {
+            v[j] = base + j < n ? (Out)in[base + j] : (Out)0;
+            s += v[j];
+        }
+        Out tot;
+        Out run = carry + block_exclusive_add<Out, SCAN_ONE_T>(s, wsum, &tot);
+        carry += tot;
+#pragma unroll
+        for (int j = 0; j < SCAN_IPT; ++j) {
+            if (base + j < n) out[base + j] = run;
+            run += v[j];
+        }
+    }
+    if (total && threadIdx.x == 0) *total = carry;
+}
+
 template <class In, class Out>
 static void scan_exclusive(Ctx& c, const In* in, Out* out, int64_t n, Out* d_total, hipStream_t st)
 {
@@ -162,6 +193,11 @@ static void scan_exclusive(Ctx& c, const In* in, Out* out, int64_t n, Out* d_tot
     if (nb == 1) {
         hipLaunchKernelGGL((k_scan_tiles<In, Out>), dim3(1), dim3(SCAN_T), 0, st, in, n, (const Out*)nullptr, out,
                            d_total);
+        HIP_CHECK(hipGetLastError());
+        return;
+    }
+    if (n <= SCAN_ONE_MAX) {
+        hipLaunchKernelGGL((k_scan_one<In, Out>), dim3(1), dim3(SCAN_ONE_T), 0, st, in, n, out, d_total);
         HIP_CHECK(hipGetLastError());
         return;
     }
@@ -179,9 +215,33 @@ void scan_flags(Ctx& c, const uint8_t* flags, int64_t* offsets, int64_t n, int64
     scan_exclusive<uint8_t, int64_t>(c, flags, offsets, n, d_total, st);
 }
 
-void scan_i64(Ctx& c, const int64_t* in, int64_t* out, int64_t n, hipStream_t st)
+void scan_i64(Ctx& c, const int64_t* in, int64_t* out, int64_t n, int64_t* d_total, hipStream_t st)
 {
-    scan_exclusive<int64_t, int64_t>(c, in, out, n, (int64_t*)nullptr, st);
+    scan_exclusive<int64_t, int64_t>(c, in, out, n, d_total, st);
+}
+
+// ctr, a and b cleared in one launch (a few kilobytes to a few megabytes; three
+// fills before the first kernel of a trace otherwise)
+__global__ __launch_bounds__(256) void k_clear3(uint64_t* p0, int64_t n0, uint64_t* p1, int64_t n1, uint64_t* p2,
+                                                int64_t n2)
+{
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n0 + n1 + n2; i += (int64_t)gridDim.x * 256) {
+        if (i < n0)
+            p0[i] = 0ull;
+        else if (i < n0 + n1)
+            p1[i - n0] = 0ull;
+        else
+            p2[i - n0 - n1] = 0ull;
+    }
+}
+
+void clear3(uint64_t* p0, int64_t n0, uint64_t* p1, int64_t n1, uint64_t* p2, int64_t n2, hipStream_t st)
+{
+    const int64_t n = n0 + n1 + n2;
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_clear3, dim3(nblocks(n, 256) < 2048u ? nblocks(n, 256) : 2048u), dim3(256), 0, st, p0, n0, p1,
+                       n1, p2, n2);
+    HIP_CHECK(hipGetLastError());
 }
 
 // --------------------------------------------------------------------------

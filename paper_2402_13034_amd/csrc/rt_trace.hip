@@ -568,21 +568,30 @@ __global__ __launch_bounds__(TC_B) void k_table_compact2(const unsigned long lon
     }
 }
 
-// Sort keys of the receivers: the 42-bit Morton code of the position (14 bits
+// Sort keys of the receivers: the Morton code of the position (up to 14 bits
 // per axis over the scene's box, clamped to it) above the 22-bit index.  A
-// scene without triangles has no box (null): every code is 0.
+// scene without triangles has no box (null): every code is 0.  The order only
+// groups the work, so it takes two bits per axis more than a square grid of R
+// receivers has (24 bits for 64 x 64, three sort passes instead of six).
 constexpr int RX_IDX_BITS = 22;
-__global__ void k_rx_keys(const double* rx, int64_t R, const float* box, uint64_t* keys)
+static int rx_axis_bits(int64_t R)
+{
+    int lg = 0;
+    while (((int64_t)1 << lg) < R) ++lg;
+    return std::min(14, (lg + 1) / 2 + 2);
+}
+__global__ void k_rx_keys(const double* rx, int64_t R, const float* box, int bits, uint64_t* keys)
 {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= R) return;
+    const float cells = (float)(1 << bits);
     uint64_t code = 0;
     for (int k = 0; k < 3 && box; ++k) {
         const float lo = box[k], ext = box[3 + k] - box[k];
         float u = ext > 0.0f ? ((float)rx[3 * r + k] - lo) / ext : 0.5f;
         u = fminf(fmaxf(u, 0.0f), 1.0f);
-        const unsigned q = (unsigned)fminf(u * 16384.0f, 16383.0f);
-        for (int b = 0; b < 14; ++b) code |= (uint64_t)((q >> b) & 1u) << (3 * b + 2 - k);
+        const unsigned q = (unsigned)fminf(u * cells, cells - 1.0f);
+        for (int b = 0; b < bits; ++b) code |= (uint64_t)((q >> b) & 1u) << (3 * b + 2 - k);
     }
     keys[r] = code << RX_IDX_BITS | (uint64_t)r;
 }
@@ -741,11 +750,11 @@ template <bool BRUTE, bool FIELD, int STK, int KM>
 __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, TraceConst tc, double sx, double sy,
                                                  double sz, const double* rx, const uint64_t* cells, int64_t n,
                                                  uint8_t* valid, float2* amp, double* len, PathRec<KM>* recs,
-                                                 unsigned long long* segs)
+                                                 unsigned long long* segs, unsigned long long* n_valid)
 {
     __shared__ int stack[STK * LEG_B];
     int64_t i = (int64_t)blockIdx.x * LEG_B + threadIdx.x;
-    unsigned nseg = 0;
+    unsigned nseg = 0, nval = 0;
     if (i < n) {
         const uint64_t cell = cells[i];
         const int64_t r = (int64_t)(cell / (uint64_t)cv.n), c = (int64_t)(cell - (uint64_t)r * cv.n);
@@ -789,6 +798,7 @@ __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, Trace
             for (int j = 0; j < KM; ++j)
                 if (j < k) tri[j] = surface_contains(s, sq[j], P[j]);
         valid[i] = ok ? 1 : 0;
+        nval = ok ? 1 : 0;
         PathRec<KM> pr;
         pr.rx = (int32_t)r;
         pr.cand = (int32_t)c;
@@ -835,6 +845,7 @@ __global__ __launch_bounds__(LEG_B) void k_paths(SceneView s, CandView cv, Trace
         }
     }
     wave_count_add(segs, nseg);
+    if (FIELD) wave_count_add(n_valid, nval);
 }
 
 // E_env[r] = sum of emitted paths of receiver r (FP64): one wave per
@@ -889,60 +900,73 @@ __global__ void k_env_compact(const PathRec<KM>* recs, CandView cv, const uint8_
     out[off2[i]] = e;
 }
 
-// valid centre sequences of order >= 1
-template <int KM>
-__global__ void k_u_flags(const PathRec<KM>* recs, const uint8_t* valid, int64_t n, uint8_t* f2)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    f2[i] = (valid[i] && recs[i].k >= 1) ? 1 : 0;
-}
-
 // Rows of useq_stride(KM) = 2 KM + 2 ints: rx, surfaces s_0..s_{KM-1},
 // triangles t_0..t_{KM-1} reached from the centre, 0.
 constexpr int useq_stride(int KM) { return 2 * KM + 2; }
 
+// The centre branch's valid sequences of order >= 1, by receiver (one wave
+// each, its records in candidate order): their number (entry R is 0), and the
+// receiver's place in the launch order of the per-element kernel, heaviest
+// first (the longest waves start first and short ones fill the tail): key =
+// inverted cost (slots weighted by legs, 20 bits) above the receiver index.
+// Bound by launches (4-8 us each, a read of 24 bytes a record): by receiver it
+// is this, a scan of R + 1 counts and k_u_emit, where flags, their scan, the
+// rows, the pointers and the order from the rows were seven launches; with the
+// receivers' order off the Tx stream a map of 61 x 91 receivers in 1 cm steps went from 720 to
+// 554 us, a box of 12 triangles from 411 to 356.
 template <int KM>
-__global__ void k_u_compact(const PathRec<KM>* recs, CandView cv, const uint8_t* f2, const int64_t* off2, int64_t n,
-                            int32_t* useq)
+__global__ void k_u_count(const int64_t* rstart, const PathRec<KM>* recs, const uint8_t* valid, int64_t R,
+                          int64_t* cnt, uint64_t* keys)
+{
+    const int64_t r = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (r > R) return;
+    int n = 0, legs = 0;
+    if (r < R)
+        for (int64_t i = rstart[r] + lane; i < rstart[r + 1]; i += 64)
+            if (valid[i] && recs[i].k >= 1) {
+                ++n;
+                legs += recs[i].k + 1;
+            }
+    for (int o = 32; o > 0; o >>= 1) {
+        n += __shfl_xor(n, o, 64);
+        legs += __shfl_xor(legs, o, 64);
+    }
+    if (lane != 0) return;
+    cnt[r] = n;
+    if (r < R) {
+        const uint64_t cost = 1 + (uint64_t)legs;   // the direct slot: one leg
+        keys[r] = ((0xFFFFFull - (cost < 0xFFFFFull ? cost : 0xFFFFFull)) << 32) | (uint64_t)r;
+    }
+}
+
+// their rows, receiver r's from uptr[r] on
+template <int KM>
+__global__ void k_u_emit(const int64_t* rstart, const PathRec<KM>* recs, CandView cv, const uint8_t* valid, int64_t R,
+                         const int64_t* uptr, int32_t* useq)
 {
     constexpr int US = useq_stride(KM);
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || !f2[i]) return;
-    int64_t o = off2[i];
-    useq[US * o + 0] = recs[i].rx;
-    for (int j = 0; j < KM; ++j) {
-        useq[US * o + 1 + j] = cv.seq[KM * recs[i].cand + j];
-        useq[US * o + 1 + KM + j] = recs[i].tri[j];
-    }
-    useq[US * o + US - 1] = 0;
-}
-
-__global__ void k_uptr_dev(const int64_t* rstart, int64_t n_rec, const int64_t* off2, const int64_t* total2,
-                           int64_t R, int64_t* uptr)
-{
-    int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r > R) return;
-    int64_t a = rstart[r];
-    uptr[r] = (r < R && a < n_rec) ? off2[a] : *total2;
-}
-
-// Launch order of the per-element kernel, heaviest receiver first (the
-// longest waves start first and short ones fill the tail): key = inverted
-// cost (slots weighted by legs, 20 bits) above the receiver index.
-template <int KM>
-__global__ void k_ris_order(const int64_t* uptr, const int32_t* useq, int64_t R, uint64_t* keys)
-{
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t r = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     if (r >= R) return;
-    int64_t cost = 1;   // the direct slot: one leg
-    for (int64_t u = uptr[r]; u < uptr[r + 1]; ++u) {
-        const int32_t* row = useq + useq_stride(KM) * u;
-        cost += 2;   // k + 1 legs, k >= 1
-        for (int j = 1; j < KM; ++j) cost += row[1 + j] >= 0;
+    int64_t o = uptr[r];
+    const int64_t e = rstart[r + 1];
+    for (int64_t i0 = rstart[r]; i0 < e; i0 += 64) {
+        const int64_t i = i0 + lane;
+        const bool take = i < e && valid[i] && recs[i].k >= 1;
+        const unsigned long long m = __ballot(take);
+        if (take) {
+            int32_t* row = useq + US * (o + __popcll(m & ((1ull << lane) - 1ull)));
+            row[0] = (int32_t)r;
+#pragma unroll
+            for (int j = 0; j < KM; ++j) {
+                row[1 + j] = cv.seq[KM * (int64_t)recs[i].cand + j];
+                row[1 + KM + j] = recs[i].tri[j];
+            }
+            row[US - 1] = 0;
+        }
+        o += __popcll(m);
     }
-    const uint64_t c = (uint64_t)(cost < 0xFFFFF ? cost : 0xFFFFF);
-    keys[r] = ((0xFFFFFull - c) << 32) | (uint64_t)r;
 }
 
 // --------------------------------------------------------------------------
@@ -1549,7 +1573,7 @@ static inline int key_end_bit(int K) { return K > RT_KM_SMALL ? 64 + RT_KEY_BITS
 // occupied slots compacted behind a leading 0 (the empty sequence); the
 // count is left in d_app[0] (overflow flag in d_app[1]).  Exhaustive mode:
 // every surface sequence, sorted and de-duplicated (count in d_cnt).
-// The hash set of a branch's phase A, allocated and cleared on `st`: probe
+// The hash set of a branch's phase A, allocated on `st` (not cleared): probe
 // runs of at most 256 (an overflow makes the caller repeat with the next
 // level): first a set of at least 4x the last call's unique count, then 2^20
 // slots, then at least 2 x (keys + 1) slots, at most 2^27, with unbounded
@@ -1576,7 +1600,6 @@ static void prepare_table(Ctx& c, const TraceArgs& a, Branch& br, hipStream_t st
     br.cap = cap;
     br.max_probe = br.table_level == 2 ? (uint64_t)(cap - 1) : (uint64_t)255;
     br.table = Scratch(c, sizeof(unsigned long long) * (size_t)key_words(a.tc.K) * (size_t)cap, st);
-    HIP_CHECK(hipMemsetAsync(br.table.p, 0, br.table.bytes, st));
 }
 
 // Four lanes per ray (k_discover_quad) instead of a wave walking for 64 rays?
@@ -1631,7 +1654,10 @@ static void cand_phase_a(Ctx& c, const SceneView& sv, int stk, const TraceArgs& 
         hipLaunchKernelGGL(k_fill_neg, dim3(nblk(rows * K, 256)), dim3(256), 0, st, hits.as<int32_t>(), rows * K);
         HIP_CHECK(hipGetLastError());
     }
-    if (!br.table.p) prepare_table(c, a, br, st);
+    if (!br.table.p) {
+        prepare_table(c, a, br, st);
+        clear3(br.table.as<uint64_t>(), (int64_t)(br.table.bytes / 8), nullptr, 0, nullptr, 0, st);
+    }
     Scratch table = std::move(br.table);
     table.st = st;   // released on the branch's stream after its last reader
     const int64_t cap = br.cap;
@@ -1745,13 +1771,13 @@ static void geo_launch(Ctx& c, const SceneView& sv, const TraceArgs& a, Branch& 
     hipLaunchKernelGGL(k_cell_count, dim3(nblk(R + 1, 4)), dim3(256), 0, st, br.mask.as<uint32_t>(), R, n_words,
                        cnt.as<int64_t>());
     HIP_CHECK(hipGetLastError());
-    scan_i64(c, cnt.as<int64_t>(), br.ps.rstart.as<int64_t>(), R + 1, st);
+    scan_i64(c, cnt.as<int64_t>(), br.ps.rstart.as<int64_t>(), R + 1, nullptr, st);
 }
 
 // the valid cells in (receiver, candidate) order, legs and field of each path
 template <int KM>
 static void paths_launch(Ctx& c, const SceneView& sv, int stk, const TraceArgs& a, bool brute, bool field,
-                         Branch& br, int64_t n, unsigned long long* d_segs)
+                         Branch& br, int64_t n, unsigned long long* d_segs, unsigned long long* d_valid)
 {
     hipStream_t st = br.st;
     PathSet& ps = br.ps;
@@ -1779,7 +1805,7 @@ static void paths_launch(Ctx& c, const SceneView& sv, int stk, const TraceArgs& 
                                                       st, sv, cv, a.tc, src[0], src[1], src[2], a.rx_dev,
                                                       ps.cells.as<uint64_t>(), n, ps.valid.as<uint8_t>(),
                                                       ps.amp.as<float2>(), ps.len.as<double>(),
-                                                      ps.recs.as<PathRec<KM>>(), d_segs))));
+                                                      ps.recs.as<PathRec<KM>>(), d_segs, d_valid))));
     HIP_CHECK(hipGetLastError());
 }
 
@@ -1851,7 +1877,6 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     // 16 incoming sequences, 17 incoming element paths
     // 18-20, 21-23: node visits, triangle tests, segments of the counting discovery build (Tx, centre)
     Scratch ctr(c, 8 * 24, st);
-    HIP_CHECK(hipMemsetAsync(ctr.p, 0, 8 * 24, st));
     unsigned long long* d_ctr = ctr.as<unsigned long long>();
     unsigned long long* d_disc = d_ctr;
     unsigned long long* d_legs = d_ctr + 1;
@@ -1899,32 +1924,36 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
             bu.ev_disc[1] = ev_d[3].e;
         }
     }
-    // both hash sets are cleared here, ahead of either discovery (a clear queued
+    // the counters and both hash sets are cleared here, ahead of either discovery (a clear queued
     // behind the other branch's discovery waits for free compute units)
     if (!exhaustive) {
         prepare_table(c, a, bt, st);
         if (two) prepare_table(c, a, bu, st);
     }
-    if (two) {
-        HIP_CHECK(hipEventRecord(fork.e, st));
-        HIP_CHECK(hipStreamWaitEvent(bu.st, fork.e, 0));
+    clear3(ctr.as<uint64_t>(), 24, bt.table.as<uint64_t>(), (int64_t)(bt.table.bytes / 8), bu.table.as<uint64_t>(),
+           (int64_t)(bu.table.bytes / 8), st);
+    SideStream side_in(c);   // the receivers' order, then the field reaching the elements
+    HIP_CHECK(hipEventRecord(fork.e, st));
+    if (two) HIP_CHECK(hipStreamWaitEvent(bu.st, fork.e, 0));
+    // the receivers in Morton order of their positions, for the geometry kernel: on a stream of
+    // its own ahead of the discoveries (43-57 us of a lone workgroup behind the Tx one)
+    if (R >= ((int64_t)1 << RX_IDX_BITS)) throw inval_error("too many receivers");
+    HIP_CHECK(hipStreamWaitEvent(side_in.s, fork.e, 0));
+    Scratch rx_order(c, sizeof(uint64_t) * (size_t)(R > 0 ? R : 1), side_in.s);
+    Event rx_ready;
+    if (R > 0) {
+        Scratch rx_keys(c, sizeof(uint64_t) * (size_t)R, side_in.s);
+        const int bits = rx_axis_bits(R);
+        hipLaunchKernelGGL(k_rx_keys, dim3(nblk(R, 256)), dim3(256), 0, side_in.s, a.rx_dev, R, a.scene->box.as<float>(),
+                           bits, rx_keys.as<uint64_t>());
+        HIP_CHECK(hipGetLastError());
+        sort_keys(c, rx_keys.as<uint64_t>(), rx_order.as<uint64_t>(), R, 1, RX_IDX_BITS, RX_IDX_BITS + 3 * bits,
+                  side_in.s);
     }
+    HIP_CHECK(hipEventRecord(rx_ready.e, side_in.s));
     // 1-3: candidates
     cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, bt, d_disc);
     if (two) cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, bu, d_disc);
-    // the receivers in Morton order of their positions, for the geometry kernel
-    // (queued behind the Tx discovery; the centre branch waits for it below)
-    if (R >= ((int64_t)1 << RX_IDX_BITS)) throw inval_error("too many receivers");
-    Scratch rx_order(c, sizeof(uint64_t) * (size_t)(R > 0 ? R : 1), st);
-    Event rx_ready;
-    if (R > 0) {
-        Scratch rx_keys(c, sizeof(uint64_t) * (size_t)R, st);
-        hipLaunchKernelGGL(k_rx_keys, dim3(nblk(R, 256)), dim3(256), 0, st, a.rx_dev, R, a.scene->box.as<float>(),
-                           rx_keys.as<uint64_t>());
-        HIP_CHECK(hipGetLastError());
-        sort_keys(c, rx_keys.as<uint64_t>(), rx_order.as<uint64_t>(), R, 1, RX_IDX_BITS, 64, st);
-    }
-    HIP_CHECK(hipEventRecord(rx_ready.e, st));
     // Each branch goes on as soon as its own count is back, so the Tx branch
     // (launched first) does not wait for the centre branch's discovery.  An
     // overflow of a hash set repeats phase A with the next level (the
@@ -1943,6 +1972,8 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     const int64_t n_tx = cand_phase_b(c, a, exhaustive, bt, count_of(bt));
     tm.mark();   // 2
     // 4: geometry of every (receiver, candidate)
+    HIP_CHECK(hipStreamWaitEvent(st, rx_ready.e, 0));
+    rx_order.st = st;
     geo_launch<KM>(c, sv, a, bt, n_tx, rx_order.as<uint64_t>());
     const int64_t n_u0 = two ? cand_phase_b(c, a, exhaustive, bu, count_of(bu)) : 0;
     if (two) {
@@ -1956,7 +1987,6 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     RisView rv{};
     Scratch txm;
     Event in_fork, in_ready;
-    SideStream side_in(c);
     if (a.ris) {
         rv = make_ris_view(a);
         txm = Scratch(c, sizeof(TxmRec) * (size_t)rv.M, st);
@@ -1965,9 +1995,9 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     }
     // 5-6: legs and fields
     const int64_t g_tx = read_i64(bt.ps.rstart.as<int64_t>() + R, st);
-    paths_launch<KM>(c, sv, stk, a, brute, true, bt, g_tx, d_legs);
+    paths_launch<KM>(c, sv, stk, a, brute, true, bt, g_tx, d_legs, d_ctr + 13);
     const int64_t g_u = two ? read_i64(bu.ps.rstart.as<int64_t>() + R, bu.st) : 0;
-    if (two) paths_launch<KM>(c, sv, stk, a, brute, false, bu, g_u, d_legs);
+    if (two) paths_launch<KM>(c, sv, stk, a, brute, false, bu, g_u, d_legs, d_ctr + 13);
     if (a.ris) {
         ris_incident<KM>(c, sv, stk, a, brute, incoming, bt, rv, d_ctr, txm.as<TxmRec>(), side_in.s);
         HIP_CHECK(hipEventRecord(in_ready.e, side_in.s));
@@ -1981,9 +2011,9 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
                                ps.valid.as<uint8_t>(), ps.amp.as<float2>(), ch.E_env.as<float2>());
             HIP_CHECK(hipGetLastError());
         }
-        Scratch off2(c, sizeof(int64_t) * (size_t)(ps.n > 0 ? ps.n : 1), st);
-        scan_flags(c, ps.valid.as<uint8_t>(), off2.as<int64_t>(), ps.n, (int64_t*)(d_ctr + 13), st);
         if (keep_paths) {
+            Scratch off2(c, sizeof(int64_t) * (size_t)(ps.n > 0 ? ps.n : 1), st);
+            scan_flags(c, ps.valid.as<uint8_t>(), off2.as<int64_t>(), ps.n, (int64_t*)(d_ctr + 13), st);
             const int64_t n_env = read_i64((const int64_t*)(d_ctr + 13), st);
             ch.env = Scratch(c, sizeof(EnvRec) * (size_t)n_env, st);
             if (ps.n > 0) {
@@ -2001,28 +2031,30 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
             ch.env_len = std::move(ps.len);
         }
     }
-    // sequences valid from the RIS centre, grouped by receiver (centre branch)
+    // sequences valid from the RIS centre, grouped by receiver (centre branch), and the
+    // receivers' launch order (cost bits alone: the keys come in receiver order, the sort is stable)
     int64_t n_u = 0;
+    Scratch order;
     if (two) {
         PathSet& ps = bu.ps;
         hipStream_t su = bu.st;
-        Scratch f2(c, (size_t)(ps.n > 0 ? ps.n : 1), su), off2(c, sizeof(int64_t) * (size_t)(ps.n > 0 ? ps.n : 1), su);
-        if (ps.n > 0) {
-            hipLaunchKernelGGL(k_u_flags<KM>, dim3(nblk(ps.n, 256)), dim3(256), 0, su, ps.recs.as<PathRec<KM>>(),
-                               ps.valid.as<uint8_t>(), ps.n, f2.as<uint8_t>());
-            HIP_CHECK(hipGetLastError());
-        }
-        scan_flags(c, f2.as<uint8_t>(), off2.as<int64_t>(), ps.n, bu.d_cnt, su);
+        if (R >= ((int64_t)1 << 32)) throw inval_error("too many receivers");
+        Scratch cnt(c, sizeof(int64_t) * (size_t)(R + 1), su), cost(c, sizeof(uint64_t) * (size_t)(R > 0 ? R : 1), su);
+        order = Scratch(c, sizeof(uint64_t) * (size_t)(R > 0 ? R : 1), su);
+        hipLaunchKernelGGL(k_u_count<KM>, dim3(nblk(R + 1, 4)), dim3(256), 0, su, ps.rstart.as<int64_t>(),
+                           ps.recs.as<PathRec<KM>>(), ps.valid.as<uint8_t>(), R, cnt.as<int64_t>(),
+                           cost.as<uint64_t>());
+        HIP_CHECK(hipGetLastError());
+        scan_i64(c, cnt.as<int64_t>(), uptr.as<int64_t>(), R + 1, bu.d_cnt, su);
         // rows for every geometric path (an upper bound of the valid ones)
         useq = Scratch(c, sizeof(int32_t) * useq_stride(KM) * (size_t)(ps.n > 0 ? ps.n : 1), su);
-        if (ps.n > 0) {
-            hipLaunchKernelGGL(k_u_compact<KM>, dim3(nblk(ps.n, 256)), dim3(256), 0, su, ps.recs.as<PathRec<KM>>(),
-                               bu.cd.view(), f2.as<uint8_t>(), off2.as<int64_t>(), ps.n, useq.as<int32_t>());
+        if (R > 0) {
+            hipLaunchKernelGGL(k_u_emit<KM>, dim3(nblk(R, 4)), dim3(256), 0, su, ps.rstart.as<int64_t>(),
+                               ps.recs.as<PathRec<KM>>(), bu.cd.view(), ps.valid.as<uint8_t>(), R, uptr.as<int64_t>(),
+                               useq.as<int32_t>());
             HIP_CHECK(hipGetLastError());
+            sort_keys(c, cost.as<uint64_t>(), order.as<uint64_t>(), R, 1, 32, 52, su);
         }
-        hipLaunchKernelGGL(k_uptr_dev, dim3(nblk(R + 1, 128)), dim3(128), 0, su, ps.rstart.as<int64_t>(), ps.n,
-                           off2.as<int64_t>(), bu.d_cnt, R, uptr.as<int64_t>());
-        HIP_CHECK(hipGetLastError());
         if (keep_paths || keep_cir) n_u = read_i64(bu.d_cnt, su);
     }
     tm.mark();   // 3: the Tx branch's legs and field are queued on the caller's stream
@@ -2048,16 +2080,6 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
         int n_mchunk = (int)((M + 63) / 64);
         int64_t waves = R * n_mchunk;
         int64_t threads = waves * 64;
-        if (R >= ((int64_t)1 << 32)) throw inval_error("too many receivers");
-        Scratch order(c, sizeof(uint64_t) * (size_t)(R > 0 ? R : 1), sr);
-        if (R > 0) {
-            Scratch cost(c, sizeof(uint64_t) * (size_t)R, sr);
-            hipLaunchKernelGGL(k_ris_order<KM>, dim3(nblk(R, 256)), dim3(256), 0, sr, uptr.as<int64_t>(),
-                               useq.as<int32_t>(), R, cost.as<uint64_t>());
-            HIP_CHECK(hipGetLastError());
-            // the keys come in receiver order and the sort is stable: the cost bits decide alone
-            sort_keys(c, cost.as<uint64_t>(), order.as<uint64_t>(), R, 1, 32, 52, sr);
-        }
         tm.mark(true, sr);   // 5
         if (threads > 0) {
             if (count_work && !brute && !keep_paths && !keep_cir) {
@@ -2107,6 +2129,7 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
                            &bu.ps.amp, &bu.ps.len, &bu.ps.recs, &bu.ps.rstart})
             p->st = st;
         if (!keep_paths) useq.st = st;
+        order.st = st;
     }
     int64_t h[24];
     read_i64s((const int64_t*)d_ctr, h, 24, st);

@@ -15,13 +15,14 @@
 //   The epilogue adds E_env, scales, and writes E and/or P.
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "rt_host.hpp"
 
 namespace rt {
 
 static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
-static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
+__host__ __device__ static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 #define ETA0_F 376.99111843077515f  // 120 pi
 
@@ -31,6 +32,7 @@ static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * 
 constexpr int VT = 64;   // tile of receivers and of configurations
 constexpr int VK = 16;   // k tile
 constexpr int VN = 4;    // configurations of the narrow kernel (one per thread)
+constexpr int VNK = 64;  // its k tile
 
 // One complex multiply-add of the VALU sums, as four explicit FMAs in a fixed
 // order: both VALU kernels take it over the elements in increasing order, so
@@ -89,29 +91,36 @@ __global__ __launch_bounds__(256) void k_sum_valu(const float2* H, const float2*
 
 // Few configurations (C <= VN): a block takes 64 receivers x VN configurations,
 // one output per thread, so a one-configuration sum still spreads over R / 64
-// blocks instead of filling 1/64 of a square tile.
+// blocks instead of filling 1/64 of a square tile.  Bound by the latency of its
+// loads: a k tile of 64 has 16 in flight per thread and takes two stages for
+// 127 elements (4096 receivers x 127 elements, one configuration: 14 us, 17 with
+// eight stages of 16).
 __global__ __launch_bounds__(256) void k_sum_valu_narrow(const float2* H, const float2* G, const float2* Eenv,
                                                          int64_t R, int64_t M, int64_t C, float scale, float2* Eout,
                                                          float* Pout)
 {
-    __shared__ float2 sh[VK][VT + 1];
-    __shared__ float2 sg[VK][VN];
+    __shared__ float2 sh[VNK][VT + 1];
+    __shared__ float2 sg[VNK][VN];
     const int j = threadIdx.x & (VN - 1), i = threadIdx.x / VN;   // configuration, receiver in the tile
     const int64_t r0 = (int64_t)blockIdx.x * VT;
     float ar = 0.0f, ai = 0.0f;
-    for (int64_t k0 = 0; k0 < M; k0 += VK) {
-        for (int e = threadIdx.x; e < VK * VT; e += 256) {
-            const int rr = e / VK, kk = e % VK;   // consecutive threads: consecutive elements of a row
+    for (int64_t k0 = 0; k0 < M; k0 += VNK) {
+#pragma unroll
+        for (int q = 0; q < VNK * VT / 256; ++q) {
+            const int e = q * 256 + threadIdx.x;
+            const int rr = e / VNK, kk = e % VNK;   // consecutive threads: consecutive elements of a row
             const int64_t r = r0 + rr, m = k0 + kk;
             sh[kk][rr] = (r < R && m < M) ? H[r * M + m] : make_float2(0.0f, 0.0f);
         }
-        if (threadIdx.x < VK * VN) {
+        {
             const int kk = threadIdx.x / VN, cc = threadIdx.x % VN;
             const int64_t m = k0 + kk;
             sg[kk][cc] = (cc < C && m < M) ? G[m * C + cc] : make_float2(0.0f, 0.0f);
         }
         __syncthreads();
-        for (int kk = 0; kk < VK; ++kk) cmac(sh[kk][i], sg[kk][j], ar, ai);
+        const int64_t left = round_up(M - k0, VK);   // the zeros that the square tile adds, added here too
+        const int kn = (int)(left < VNK ? left : VNK);
+        for (int kk = 0; kk < kn; ++kk) cmac(sh[kk][i], sg[kk][j], ar, ai);
         __syncthreads();
     }
     const int64_t r = r0 + i;
@@ -165,35 +174,65 @@ __global__ void k_row_scale(const float2* H, int64_t R, int64_t M, int32_t* sexp
     if (lane == 0) sexp[r] = m > 0.0f ? 14 - ilogbf(m) : 0;
 }
 
-// A [rows_p x kp] row-major (k fastest); layout 1 = real Gamma, 2 = complex Gamma;
-// sexp: per-receiver scale exponents of the fp16 split (nullptr: bf16)
-__global__ void k_split_A(const float2* H, int64_t R, int64_t M, int layout, int64_t rows_p, int64_t kp,
-                          const int32_t* sexp, uint16_t* Ahi, uint16_t* Alo)
+// (the hardware's conversion to bf16, round to nearest even: one instruction for two)
+__device__ __forceinline__ uint16_t bf16_cvt(float v)
 {
-    int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= rows_p * kp) return;
-    int64_t row = idx / kp, k = idx - row * kp;
-    int64_t r = row >> 1;
-    int part = (int)(row & 1);
-    float v = 0.0f;
-    if (r < R) {
-        if (layout == 1) {
-            if (k < M) v = part == 0 ? H[r * M + k].x : H[r * M + k].y;
-        } else {
-            if (k < M) v = part == 0 ? H[r * M + k].x : H[r * M + k].y;
-            else if (k < 2 * M) v = part == 0 ? -H[r * M + k - M].y : H[r * M + k - M].x;
+    const __bf16 h = (__bf16)v;
+    uint16_t u;
+    __builtin_memcpy(&u, &h, 2);
+    return u;
+}
+template <bool F16>
+__device__ __forceinline__ void split_hi_lo(float v, uint16_t& hi, uint16_t& lo)
+{
+    if constexpr (F16) {
+        hi = f16_rne(v);
+        lo = f16_rne(v - f16_to_f(hi));
+    } else {
+        hi = bf16_cvt(v);
+        lo = bf16_cvt(v - bf16_to_f(hi));
+    }
+}
+
+// eight 16-bit values as the four words of a 16-byte vector
+__device__ __forceinline__ uint4 pack8(const uint16_t* h)
+{
+    return make_uint4(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16, h[4] | (uint32_t)h[5] << 16,
+                      h[6] | (uint32_t)h[7] << 16);
+}
+
+// A [rows_p x kp] row-major (k fastest); layout 1 = real Gamma, 2 = complex Gamma;
+// sexp: per-receiver scale exponents of the fp16 split (F16 only).  32 lanes
+// along a row, eight values and two 16-byte stores each: bound by the memory
+// (4 bytes written a value), where a thread and a 64-bit division per value
+// took 17 us for 4096 x 127 complex (12 now).
+constexpr int SA_ROWS = 8;   // rows of a workgroup
+template <bool F16>
+__global__ __launch_bounds__(256) void k_split_A(const float2* H, int64_t R, int64_t M, int layout, int64_t rows_p,
+                                                 int64_t kp, const int32_t* sexp, uint16_t* Ahi, uint16_t* Alo)
+{
+    const int64_t row = (int64_t)blockIdx.x * SA_ROWS + (threadIdx.x >> 5);
+    if (row >= rows_p) return;
+    const int64_t r = row >> 1;
+    const bool im = row & 1;
+    const int sx = F16 && r < R ? sexp[r] : 0;
+    const int64_t kend = r < R ? (layout == 1 ? M : 2 * M) : 0;
+    for (int64_t k0 = (threadIdx.x & 31) * 8; k0 < kp; k0 += 32 * 8) {
+        uint16_t hi[8], lo[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int64_t k = k0 + j;
+            float v = 0.0f;
+            if (k < kend) {
+                const float2 h = H[r * M + (k < M ? k : k - M)];
+                v = k < M ? (im ? h.y : h.x) : (im ? h.x : -h.y);
+            }
+            if (F16) v = ldexpf(v, sx);
+            split_hi_lo<F16>(v, hi[j], lo[j]);
         }
+        *(uint4*)&Ahi[row * kp + k0] = pack8(hi);
+        *(uint4*)&Alo[row * kp + k0] = pack8(lo);
     }
-    if (sexp) {
-        v = r < R ? ldexpf(v, sexp[r]) : 0.0f;
-        const uint16_t hi = f16_rne(v);
-        Ahi[idx] = hi;
-        Alo[idx] = f16_rne(v - f16_to_f(hi));
-        return;
-    }
-    uint16_t hi = bf16_rne(v);
-    Ahi[idx] = hi;
-    Alo[idx] = bf16_rne(v - bf16_to_f(hi));
 }
 
 // Bt [cols_p x kp] (k fastest) from Gamma [M x C] (c fastest): a 64 x 64
@@ -358,6 +397,164 @@ __global__ __launch_bounds__(256) void k_sum_mfma(const uint16_t* __restrict__ A
         }
 }
 
+// The same product on tiles of 64 receivers x 32 NB configurations (4 waves,
+// each 32 rows), for the sums whose large tiles would leave most CUs idle.
+// Gamma is read and split here (no split kernel, no buffer for it): a chunk of
+// 64 k is converted into LDS once per workgroup, 16-byte pieces at piece ^
+// (column & 7) so that neither its writes nor the fragment reads conflict; H's
+// rows come straight into LDS as in the large tiles, a chunk ahead.  The
+// products and their order are those of the large tiles, so the tile chosen
+// does not change a result.  Bound by
+// a chunk's chain of loads, conversion, barrier and products (0.8 us with one
+// workgroup a CU): 4096 x 127 x 37 complex 10 us where split and large tiles took
+// 25, 3000 x 331 x 333 28 us where they took 43.  H's fragments straight from
+// global memory (32 rows an instruction) kept the texture path busy: 13 and 31 us.
+constexpr int G2_STAGE_WAIT_0 = 0x0070;   // s_waitcnt vmcnt(0) lgkmcnt(0)
+constexpr int FK = 64;   // k of a chunk
+constexpr int FR = 64;   // receivers of a tile
+typedef __attribute__((address_space(3))) void lds_void;
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int few_swz(int r) { return (r ^ (r >> 3)) & 7; }
+
+template <int NB, int NT, bool F16>
+__global__ __launch_bounds__(256) void k_sum_few(const uint16_t* Ahi, const uint16_t* Alo, int64_t kp, const float2* G,
+                                                 int M, int kend, const float2* __restrict__ Eenv,
+                                                 const int32_t* __restrict__ sexp, int64_t R, int C, float scale,
+                                                 float2* Eout, float* Pout, unsigned n_tm)
+{
+    constexpr int FN = 32 * NB;
+    // two stages of A [hi | lo], separate arrays so that a read of one never waits for the loads into the other
+    __shared__ __attribute__((aligned(1024))) uint16_t sA0[4 * FR * FK];
+    __shared__ __attribute__((aligned(1024))) uint16_t sA1[4 * FR * FK];
+    __shared__ __attribute__((aligned(16))) uint16_t sB[2][FN * FK];
+    __shared__ __attribute__((aligned(16))) uint16_t sL[NT == 3 ? 2 : 1][NT == 3 ? FN * FK : 8];
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6, lane = tid & 63;
+    const int64_t tile0 = (int64_t)(blockIdx.x % n_tm) * (2 * FR), row0 = tile0 + wave * 32;
+    const int col0 = (int)(blockIdx.x / n_tm) * FN;
+    // A: a wave's own 32 rows, eight rows of 128 bytes a load
+    const __amdgpu_buffer_rsrc_t rAh =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(Ahi + tile0 * kp), (short)0, (int)(4 * FR * kp), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rAl =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(Alo + tile0 * kp), (short)0, (int)(4 * FR * kp), 0x00020000);
+    int aoff[4];
+    for (int q = 0; q < 4; ++q) {
+        const int r = wave * 32 + q * 8 + (lane >> 3);
+        aoff[q] = (int)(r * kp + ((lane & 7) ^ few_swz(r)) * 8) * 2;
+    }
+    auto load_a = [&](uint16_t* st, int k0) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint16_t* d = st + (wave * 32 + q * 8) * FK;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rAh, (lds_void*)d, 16, aoff[q], k0 * 2, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rAl, (lds_void*)(d + 2 * FR * FK), 16, aoff[q], k0 * 2, 0, 0);
+        }
+    };
+    // Row k of B is the real part of Gamma's row k, from M on (complex Gamma)
+    // the imaginary part of row k - M: byte k * rowb + 8 column, less `wrap`
+    // from M on.  Rows past the last one are past the buffer and read as 0.
+    // A thread takes NB columns by eight k.
+    const int bc = (tid & 31) * NB, bg = tid >> 5;
+    const unsigned rowb = 8u * (unsigned)C;
+    const unsigned wrap = kend > M ? rowb * (unsigned)M - 4u : 0u;
+    const unsigned bcol = 8u * (unsigned)(col0 + bc < C ? col0 + bc : C - 1);
+    const __amdgpu_buffer_rsrc_t rG =
+        __builtin_amdgcn_make_buffer_rsrc((void*)G, (short)0, (int)(rowb * (unsigned)M), 0x00020000);
+    float b[NB][8];
+    auto load_b = [&](int k0) {
+        const int kg = k0 + bg * 8;
+        unsigned o = bcol + rowb * (unsigned)kg;
+#pragma unroll
+        for (int j = 0; j < 8; ++j, o += rowb) {
+            const int oj = (int)(kg + j >= M ? o - wrap : o);
+            if constexpr (NB == 1) {
+                b[0][j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rG, oj, 0, 0));
+            } else {
+                const auto v = __builtin_amdgcn_raw_buffer_load_b96(rG, oj, 0, 0);
+                b[0][j] = __uint_as_float(v[0]);
+                b[1][j] = __uint_as_float(v[2]);
+            }
+        }
+    };
+    f32x16 acc[NB];
+    for (int j = 0; j < NB; ++j)
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.0f;
+    // one chunk (the last one may be shorter), the next one's loads on their way meanwhile
+    auto chunk = [&](const uint16_t* cur, uint16_t* nxt, uint16_t* cB, uint16_t* cL, int k0, auto full) {
+#pragma unroll
+        for (int g = 0; g < NB; ++g) {
+            uint16_t hi[8], lo[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) split_hi_lo<F16>(b[g][j], hi[j], lo[j]);
+            const int o = (bc + g) * FK + ((bg ^ few_swz(bc + g)) * 8);
+            *(uint4*)&cB[o] = pack8(hi);
+            if constexpr (NT == 3) *(uint4*)&cL[o] = pack8(lo);
+        }
+        __builtin_amdgcn_s_waitcnt(G2_STAGE_WAIT_0);   // this wave's rows of `cur` landed
+        __syncthreads();                               // the other B's readers are past the barrier before
+        if constexpr (full) {                          // past the last chunk: not used
+            load_a(nxt, k0 + FK);
+            load_b(k0 + FK);
+        }
+#pragma unroll
+        for (int s = 0; s < FK / 16; ++s) {
+            if (!full && k0 + s * 16 >= kend) break;
+            const int p = 2 * s + (lane >> 5), ra = wave * 32 + (lane & 31);
+            const int ro = ra * FK + ((p ^ few_swz(ra)) * 8);
+            const uint4 xh = *(const uint4*)&cur[ro], xl = *(const uint4*)&cur[2 * FR * FK + ro];
+            uint4 bh[NB], bl[NB];
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const int c = j * 32 + (lane & 31);
+                const int o = c * FK + ((p ^ few_swz(c)) * 8);
+                bh[j] = *(const uint4*)&cB[o];
+                if constexpr (NT == 3) bl[j] = *(const uint4*)&cL[o];
+            }
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                acc[j] = mfma16<F16>((const uint16_t*)&xh, (const uint16_t*)&bh[j], acc[j]);
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                acc[j] = mfma16<F16>((const uint16_t*)&xl, (const uint16_t*)&bh[j], acc[j]);
+            if constexpr (NT == 3)
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    acc[j] = mfma16<F16>((const uint16_t*)&xh, (const uint16_t*)&bl[j], acc[j]);
+        }
+    };
+    load_a(sA0, 0);
+    load_b(0);
+    constexpr int L1 = NT == 3 ? 1 : 0;
+    int k0 = 0;
+    for (; k0 + 2 * FK <= kend; k0 += 2 * FK) {
+        chunk(sA0, sA1, sB[0], sL[0], k0, std::true_type{});
+        chunk(sA1, sA0, sB[1], sL[L1], k0 + FK, std::true_type{});
+    }
+    if (k0 + FK <= kend) {
+        chunk(sA0, sA1, sB[0], sL[0], k0, std::true_type{});
+        if (k0 + FK < kend) chunk(sA1, sA0, sB[1], sL[L1], k0 + FK, std::false_type{});
+    } else if (k0 < kend) {
+        chunk(sA0, sA1, sB[0], sL[0], k0, std::false_type{});
+    }
+    // lane holds column (lane & 31); values e: row 8 (e / 4) + 4 (lane / 32) + (e % 4)
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+        const int64_t r = (row0 + 8 * (e / 4) + 4 * (lane >> 5) + (e % 4)) >> 1;
+        if (r >= R) continue;
+        const float2 e0 = Eenv[r];
+        const float sr = F16 ? ldexpf(scale, -sexp[r]) : scale;   // exact: a power of two
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int c = col0 + j * 32 + (lane & 31);
+            if (c >= C) continue;
+            const float er = e0.x + sr * acc[j][e];
+            const float ei = e0.y + sr * acc[j][e + 1];
+            if (Eout) Eout[r * C + c] = make_float2(er, ei);
+            if (Pout) Pout[r * C + c] = (er * er + ei * ei) / (2.0f * ETA0_F);
+        }
+    }
+}
+
 // Two-product split (H hi + lo against Gamma hi) on 256 x 256 tiles: 8 waves
 // (4 x 2), each 64 x 128 outputs = 2 x 4 blocks of 32 x 32, so every A
 // fragment (hi and lo) read from LDS feeds four blocks and every B fragment four.
@@ -381,10 +578,7 @@ constexpr int G2M = 256, G2N = 256, G2K = 32;
 constexpr int G2R = 32;                 // LDS row length (elements)
 constexpr int G2OP = G2M * G2R;         // elements of one operand tile in LDS
 constexpr int G2_STAGE_WAIT_1 = 0x0076;   // s_waitcnt vmcnt(6) lgkmcnt(0): one later tile's loads may fly
-constexpr int G2_STAGE_WAIT_0 = 0x0070;   // s_waitcnt vmcnt(0) lgkmcnt(0)
 constexpr int G2_STAGE_WAIT_2 = 0x007C;   // s_waitcnt vmcnt(12) lgkmcnt(0): two later tiles' loads may fly
-typedef __attribute__((address_space(3))) void lds_void;
-
 __device__ __forceinline__ int g2_swz(int r) { return ((r >> 1) ^ (r >> 2)) & 3; }
 
 // a barrier after an explicit wait: the direct loads are counted by vmcnt only,
@@ -588,10 +782,30 @@ static int cu_count()
 // Shapes of the matrix-core product of one sum (the split buffers' sizes).
 struct SumShape {
     bool f16, three;
+    bool few;        // the small tiles (k_sum_few): no split of Gamma
     int layout;      // cached split key: 1 / 2 bf16 real / complex Gamma, 3 / 4 fp16
     int lay;         // 1 real, 2 complex Gamma
     int64_t kp, rows_p, cols_p;
 };
+
+// Small tiles?  A large tile is eight small ones and takes its CU 2.5 times as
+// long as a small one (45 against 18 ns a k), and Gamma's own split costs 8 us
+// more.  Four small tiles a CU for every large one are still the faster way up
+// to 512 k (4096 receivers x 127 complex: 29 against 37 us at 1024
+// configurations, 49 against 41 at 2048; 65536 receivers: 59 against 63 us at
+// 65, 113 against 70 at 256), two above (1024 complex elements, 16384
+// receivers: 75 against 113 us at 100 configurations, 162 against 113 at 256);
+// half of that for three products, whose stages leave room for one workgroup
+// a CU.  Byte offsets into Gamma and into a tile of H's split are 32 bits.
+static bool few_tiles(const SumShape& sh, int64_t R, int64_t M, int64_t C, int64_t kend)
+{
+    if (C > ((int64_t)1 << 24) || M > ((int64_t)1 << 21) || 16 * C * (M + FK) >= ((int64_t)1 << 31)) return false;
+    const int64_t cus = cu_count();
+    const int64_t large = (sh.rows_p / G2M) * (sh.cols_p / G2N);
+    const int64_t small = (R + FR - 1) / FR * ((C + 63) / 64);
+    const int64_t per = (kend <= 512 ? 4 : 2) / (sh.three ? 2 : 1);
+    return small <= per * cus * ((large + cus - 1) / cus) && small < ((int64_t)1 << 31);
+}
 
 static SumShape sum_shape(int64_t R, int64_t M, int64_t C, bool gamma_real, int precision)
 {
@@ -604,6 +818,7 @@ static SumShape sum_shape(int64_t R, int64_t M, int64_t C, bool gamma_real, int 
     sh.kp = round_up(kd > 0 ? kd : 1, GBK);
     sh.rows_p = round_up(2 * R, G2M);   // a multiple of both tile heights
     sh.cols_p = round_up(C, G2N);
+    sh.few = few_tiles(sh, R, M, C, kd);
     return sh;
 }
 
@@ -616,17 +831,47 @@ static void launch_split_a(const Channel& ch, const SumShape& sh, uint16_t* a_hi
         hipLaunchKernelGGL(k_row_scale, dim3(nblk(R, 4)), dim3(256), 0, st, ch.H.as<float2>(), R, M, sexp);
         HIP_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_split_A, dim3(nblk(sh.rows_p * sh.kp, 256)), dim3(256), 0, st, ch.H.as<float2>(), R, M,
-                       sh.lay, sh.rows_p, sh.kp, sh.f16 ? (const int32_t*)sexp : (const int32_t*)nullptr, a_hi, a_lo);
+    const dim3 grid(nblk(sh.rows_p, SA_ROWS));
+    if (sh.f16)
+        hipLaunchKernelGGL(k_split_A<true>, grid, dim3(256), 0, st, ch.H.as<float2>(), R, M, sh.lay, sh.rows_p, sh.kp,
+                           sexp, a_hi, a_lo);
+    else
+        hipLaunchKernelGGL(k_split_A<false>, grid, dim3(256), 0, st, ch.H.as<float2>(), R, M, sh.lay, sh.rows_p, sh.kp,
+                           sexp, a_hi, a_lo);
     HIP_CHECK(hipGetLastError());
 }
 
-// Split of Gamma into b_hi (b_lo for three products) and the product itself, on `st`.
+template <int NT, bool F16>
+static void launch_few(const Channel& ch, const SumShape& sh, const float2* G, int64_t C, float scale,
+                       const uint16_t* a_hi, const uint16_t* a_lo, const int32_t* sexp, float* E_out, float* P_out,
+                       hipStream_t st)
+{
+    const int M = (int)ch.M, kend = sh.lay == 1 ? M : 2 * M;
+    const unsigned n_tm = nblk(ch.R, FR);
+    if (C <= 32)
+        hipLaunchKernelGGL((k_sum_few<1, NT, F16>), dim3(n_tm), dim3(256), 0, st, a_hi, a_lo, sh.kp, G, M, kend,
+                           ch.E_env.as<float2>(), sexp, ch.R, (int)C, scale, (float2*)E_out, P_out, n_tm);
+    else
+        hipLaunchKernelGGL((k_sum_few<2, NT, F16>), dim3(n_tm * nblk(C, 64)), dim3(256), 0, st, a_hi, a_lo, sh.kp, G, M,
+                           kend, ch.E_env.as<float2>(), sexp, ch.R, (int)C, scale, (float2*)E_out, P_out, n_tm);
+    HIP_CHECK(hipGetLastError());
+}
+
+// Split of Gamma into b_hi (b_lo for three products) where the large tiles take it, and the product, on `st`.
 static void launch_product(const Channel& ch, const SumShape& sh, const float2* G, int64_t C, float scale,
                            const uint16_t* a_hi, const uint16_t* a_lo, const int32_t* sexp, uint16_t* b_hi,
                            uint16_t* b_lo, float* E_out, float* P_out, hipStream_t st)
 {
     const int64_t R = ch.R, M = ch.M, kp = sh.kp;
+    if (sh.few) {
+        if (sh.three)
+            launch_few<3, false>(ch, sh, G, C, scale, a_hi, a_lo, sexp, E_out, P_out, st);
+        else if (sh.f16)
+            launch_few<2, true>(ch, sh, G, C, scale, a_hi, a_lo, sexp, E_out, P_out, st);
+        else
+            launch_few<2, false>(ch, sh, G, C, scale, a_hi, a_lo, sexp, E_out, P_out, st);
+        return;
+    }
     hipLaunchKernelGGL(k_split_B, dim3(nblk(sh.cols_p, SBT), nblk(kp, SBT)), dim3(256), 0, st, G, M, C, sh.lay, sh.cols_p, kp,
                        sh.f16, b_hi, sh.three ? b_lo : (uint16_t*)nullptr);
     HIP_CHECK(hipGetLastError());
@@ -699,9 +944,9 @@ void ris_sum(Ctx& c, Channel& ch, const float* gamma, int64_t C, float scale, bo
         if (!ch.split_ev) HIP_CHECK(hipEventCreateWithFlags(&ch.split_ev, hipEventDisableTiming));
         HIP_CHECK(hipEventRecord(ch.split_ev, st));
     }
-    Scratch bhi(c, sizeof(uint16_t) * (size_t)(sh.cols_p * sh.kp), st);
-    Scratch blo;
-    if (sh.three) blo = Scratch(c, sizeof(uint16_t) * (size_t)(sh.cols_p * sh.kp), st);
+    Scratch bhi, blo;
+    if (!sh.few) bhi = Scratch(c, sizeof(uint16_t) * (size_t)(sh.cols_p * sh.kp), st);
+    if (sh.three && !sh.few) blo = Scratch(c, sizeof(uint16_t) * (size_t)(sh.cols_p * sh.kp), st);
     launch_product(ch, sh, G, C, scale, ch.a_hi.as<uint16_t>(), ch.a_lo.as<uint16_t>(), ch.a_sexp.as<int32_t>(),
                    bhi.as<uint16_t>(), blo.as<uint16_t>(), E_out, P_out, st);
     // this stream has read the split up to here

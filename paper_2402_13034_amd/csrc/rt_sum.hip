@@ -400,8 +400,8 @@ __global__ __launch_bounds__(256) void k_sum_mfma(const uint16_t* __restrict__ A
 // The same product on tiles of 64 receivers x 32 NB configurations (4 waves,
 // each 32 rows), for the sums whose large tiles would leave most CUs idle.
 // Gamma is read and split here (no split kernel, no buffer for it): a chunk of
-// 64 k is converted into LDS once per workgroup, 16-byte pieces at piece ^
-// (column & 7) so that neither its writes nor the fragment reads conflict; H's
+// 64 k is converted into LDS once per workgroup, 16-byte pieces swizzled
+// so that neither its writes nor the fragment reads conflict; H's
 // rows come straight into LDS as in the large tiles, a chunk ahead.  The
 // products and their order are those of the large tiles, so the tile chosen
 // does not change a result.  Bound by
@@ -413,7 +413,6 @@ constexpr int G2_STAGE_WAIT_0 = 0x0070;   // s_waitcnt vmcnt(0) lgkmcnt(0)
 constexpr int FK = 64;   // k of a chunk
 constexpr int FR = 64;   // receivers of a tile
 typedef __attribute__((address_space(3))) void lds_void;
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ int few_swz(int r) { return (r ^ (r >> 3)) & 7; }
 
 template <int NB, int NT, bool F16>

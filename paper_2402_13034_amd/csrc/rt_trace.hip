@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <memory>
 #include <utility>
 #include <vector>
@@ -2204,121 +2205,182 @@ void trace(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, bool timing, 
 // receiver's paths summed per bin.
 // --------------------------------------------------------------------------
 constexpr int CIR_B = 256;
-constexpr int CIR_G = 2048;   // bins per pass (two 64-bit LDS counters each)
+constexpr int CIR_G = 3072;   // most bins of a pass (two 64-bit LDS counters each)
 
-// The records of one receiver in order: its environment paths, then its RIS
-// paths slot by slot, element by element.  A thread visits records p, p +
-// CIR_B, ...; the (slot, element) of a RIS record advances by a fixed step.
-struct CirWalk {
-    int64_t n_env, s0, M, dsl, dm, sl = -1, m = 0;
-    __device__ void next(int64_t p)   // p = this thread's current record
-    {
-        if (sl >= 0) {
-            sl += dsl;
-            m += dm;
-            if (m >= M) {
-                m -= M;
-                ++sl;
-            }
-        } else if (p >= n_env && M > 0) {
-            const int64_t q = p - n_env;
-            sl = s0 + q / M;
-            m = q - (q / M) * M;
-        }
-    }
-};
-
-// Contribution of record p for configuration gamma: delay bin (-1: none or
-// outside the window; with BIN false only whether the record is a path) and
-// complex amplitude (FP64 of the FP32 inputs).
-template <bool BIN>
-__device__ __forceinline__ int64_t cir_term(int64_t p, const CirWalk& w, int64_t e0, int64_t n_path,
-                                            const uint8_t* env_valid, const float2* env_amp, const double* env_len,
-                                            const float2* camp, const double* clen, const float2* gamma,
-                                            double l_bin, int64_t n_bins, double& ar, double& ai)
+// Sum over the wave, in lane 63.
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+template <int CTRL, int ROWS>
+__device__ __forceinline__ long long dpp_add_i64(long long v)
 {
-    double bin = -1.0;
-    ar = 0.0;
-    ai = 0.0;
-    if (p < w.n_env) {
-        const int64_t j = e0 + p;
-        if (env_valid[j]) {
-            const float2 a = env_amp[j];
-            bin = BIN ? floor(env_len[j] / l_bin) : 0.0;
-            ar = a.x;
-            ai = a.y;
-        }
-    } else if (p < n_path) {
-        const int64_t cell = w.sl * w.M + w.m;
-        const float2 a = camp[cell];
-        if (a.x != 0.0f || a.y != 0.0f) {
-            const float2 g = gamma[w.m];
-            bin = BIN ? floor(clen[cell] / l_bin) : 0.0;
-            ar = (double)a.x * (double)g.x - (double)a.y * (double)g.y;
-            ai = (double)a.x * (double)g.y + (double)a.y * (double)g.x;
-        }
+    i32x2 x = __builtin_bit_cast(i32x2, v);
+    if constexpr (ROWS == 0xF) {
+        x[0] = __builtin_amdgcn_mov_dpp(x[0], CTRL, 0xF, 0xF, true);
+        x[1] = __builtin_amdgcn_mov_dpp(x[1], CTRL, 0xF, 0xF, true);
+    } else {
+        x[0] = __builtin_amdgcn_update_dpp(0, x[0], CTRL, ROWS, 0xF, false);
+        x[1] = __builtin_amdgcn_update_dpp(0, x[1], CTRL, ROWS, 0xF, false);
     }
-    return bin >= 0.0 && bin < (double)n_bins ? (int64_t)bin : -1;
+    return v + __builtin_bit_cast(long long, x);
+}
+__device__ __forceinline__ long long wave_sum_i64(long long v)
+{
+    v = dpp_add_i64<0xB1, 0xF>(v);    // quads: neighbour, pair
+    v = dpp_add_i64<0x4E, 0xF>(v);
+    v = dpp_add_i64<0x124, 0xF>(v);   // rows of 16: rotate by 4, by 8
+    v = dpp_add_i64<0x128, 0xF>(v);
+    v = dpp_add_i64<0x142, 0xA>(v);   // row 0 to 1, 2 to 3
+    return dpp_add_i64<0x143, 0xC>(v);   // rows 0-1 to 2-3
 }
 
-// One workgroup per receiver.  The bins are summed in fixed point: every
-// term is rounded to a multiple of 2^-S, where 2^S scales the receiver's sum
-// of |re| + |im| below 2^61, and added with 64-bit integer LDS atomics, so the
-// result does not depend on the order of the additions (deterministic) and
-// each term's rounding error is at most 2^-61 of that sum.
+// gamma-weighted amplitude of a RIS record (FP64 of the FP32 inputs)
+__device__ __forceinline__ void cir_weight(float2 a, float2 g, double& ar, double& ai)
+{
+    ar = (double)a.x * (double)g.x - (double)a.y * (double)g.y;
+    ai = (double)a.x * (double)g.y + (double)a.y * (double)g.x;
+}
+
+// an integer of magnitude below 2^62
+__device__ __forceinline__ long long cir_i64(double x)
+{
+    const double h = floor(x * 0x1p-32);
+    const i32x2 v = {(int)(unsigned)__builtin_fma(h, -0x1p32, x), (int)h};
+    return __builtin_bit_cast(long long, v);
+}
+
+// Two records a lane, elements m and m + 64 of a slot (past the last element: no path).
+struct CirPair {
+    float2 a[2], g[2];
+    double len[2];
+};
+template <bool LEN>
+__device__ __forceinline__ void cir_load(CirPair& p, const float2* camp, const double* clen, const float2* gamma,
+                                         int64_t sl, int64_t m0, int64_t M)
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int64_t m = m0 + 64 * i;
+        const int64_t mc = m < M ? m : M - 1;
+        p.a[i] = camp[sl * M + mc];
+        p.g[i] = gamma[mc];
+        if (LEN) p.len[i] = clen[sl * M + mc];
+        if (m >= M) p.a[i] = make_float2(0.0f, 0.0f);
+    }
+}
+
+// One workgroup per receiver, one wave per slot of its RIS records (element by
+// element).  The bins are summed in fixed point: every term is rounded to a
+// multiple of 2^-S, where 2^S scales the receiver's sum of |re| + |im| below
+// 2^61, and added as a 64-bit integer, so the result does not depend on the
+// order of the additions (deterministic) and each term's rounding error is at
+// most 2^-61 of that sum.
+//
+// A slot's elements lie within a few centimetres, so most of a wave's 128
+// records fall into two or three bins: the wave sums them bin by bin and one
+// lane adds to the bin (64 lanes adding to one LDS word take turns).  `inv` is 1 / l_bin where a length over l_bin rounds correctly
+// by it, 0 for the general division.  Bound by the vector instructions and the
+// kept records (16 bytes each, the amplitudes read twice), the next 128 on their
+// way while 128 are summed: 145000 slots of 127 elements in 400 bins 116 us,
+// 215 with a record and two LDS additions a lane and no loads ahead.
 __global__ __launch_bounds__(CIR_B) void k_cir(const int64_t* env_rstart, const uint8_t* env_valid,
                                                const float2* env_amp, const double* env_len, const int64_t* uptr,
                                                const float2* camp, const double* clen, int64_t M, const float2* gamma,
-                                               double l_bin, int64_t n_bins, float2* cir)
+                                               double l_bin, double inv, int64_t n_bins, int gper, float2* cir)
 {
-    __shared__ unsigned long long acc[2 * CIR_G];
-    __shared__ double red[CIR_B];
+    extern __shared__ unsigned long long acc[];   // 2 gper
+    __shared__ double red[CIR_B / 64];
     const int64_t r = blockIdx.x;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t e0 = env_rstart ? env_rstart[r] : 0, e1 = env_rstart ? env_rstart[r + 1] : 0;
     const int64_t s0 = uptr ? uptr[r] + r : 0, s1 = uptr ? uptr[r + 1] + r + 1 : 0;
-    const int64_t n_env = e1 - e0, n_path = n_env + (s1 - s0) * M;
-    const int64_t dsl = M > 0 ? CIR_B / M : 0, dm = M > 0 ? CIR_B - dsl * M : 0;
     // the scale: sum of |re| + |im| over the receiver's paths (inside the window or not), reduced in a
     // fixed order
     double sa = 0.0;
-    {
-        CirWalk w{n_env, s0, M, dsl, dm};
-        for (int64_t p = tid; p < n_path; p += CIR_B) {
-            w.next(p);
-            double ar, ai;
-            if (cir_term<false>(p, w, e0, n_path, env_valid, env_amp, env_len, camp, clen, gamma, l_bin, n_bins, ar,
-                                ai) >= 0)
-                sa += fabs(ar) + fabs(ai);
+    for (int64_t j = e0 + tid; j < e1; j += CIR_B)
+        if (env_valid[j]) sa += fabs((double)env_amp[j].x) + fabs((double)env_amp[j].y);
+    // a wave's records, 128 elements of a slot at a time, the next ones on their way meanwhile
+    auto walk = [&](auto with_len, auto use) {
+        int64_t sl = s0 + wave, m0 = lane;
+        if (sl >= s1 || M <= 0) return;
+        CirPair p, q;
+        cir_load<with_len>(p, camp, clen, gamma, sl, m0, M);
+        for (;;) {
+            const bool last = m0 - lane + 128 >= M;
+            const int64_t nsl = last ? sl + CIR_B / 64 : sl, nm0 = last ? lane : m0 + 128;
+            const bool more = nsl < s1;
+            if (more) cir_load<with_len>(q, camp, clen, gamma, nsl, nm0, M);
+            use(p);
+            if (!more) break;
+            p = q;
+            sl = nsl;
+            m0 = nm0;
         }
-    }
-    red[tid] = sa;
+    };
+    walk(std::false_type{}, [&](const CirPair& p) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (p.a[i].x != 0.0f || p.a[i].y != 0.0f) {
+                double ar, ai;
+                cir_weight(p.a[i], p.g[i], ar, ai);
+                sa += fabs(ar) + fabs(ai);
+            }
+    });
+    for (int o = 32; o > 0; o >>= 1) sa += __shfl_xor(sa, o, 64);
+    if (lane == 0) red[wave] = sa;
     __syncthreads();
-    for (int h = CIR_B / 2; h > 0; h >>= 1) {
-        if (tid < h) red[tid] += red[tid + h];
-        __syncthreads();
-    }
-    const double total = red[0];
+    double total = 0.0;
+    for (int w = 0; w < CIR_B / 64; ++w) total += red[w];
     // total * 2^S < 2^61 (S kept in the range where 2^S is a finite double)
     const int S = total > 0.0 ? min(1000, max(-1000, 60 - ilogb(total))) : 0;
     const double scale = ldexp(1.0, S), unscale = ldexp(1.0, -S);
-    for (int64_t g0 = 0; g0 < n_bins; g0 += CIR_G) {
-        const int64_t gn = n_bins - g0 < CIR_G ? n_bins - g0 : CIR_G;
-        for (int64_t i = tid; i < 2 * gn; i += CIR_B) acc[i] = 0ull;
+    for (int64_t g0 = 0; g0 < n_bins; g0 += gper) {
+        const int gn = (int)(n_bins - g0 < gper ? n_bins - g0 : gper);
+        for (int i = tid; i < 2 * gn; i += CIR_B) acc[i] = 0ull;
         __syncthreads();
-        CirWalk w{n_env, s0, M, dsl, dm};
-        for (int64_t p = tid; p < n_path; p += CIR_B) {
-            w.next(p);
-            double ar, ai;
-            const int64_t bin =
-                cir_term<true>(p, w, e0, n_path, env_valid, env_amp, env_len, camp, clen, gamma, l_bin, n_bins, ar, ai);
-            if (bin >= g0 && bin < g0 + gn) {
-                atomicAdd(&acc[2 * (bin - g0)], (unsigned long long)(long long)rint(ar * scale));
-                atomicAdd(&acc[2 * (bin - g0) + 1], (unsigned long long)(long long)rint(ai * scale));
-            }
+        // delay bin of a path in this pass, -1: outside
+        auto bin_of = [&](double len) {
+            const double bin = floor(inv != 0.0 ? div_by(len, l_bin, inv) : len / l_bin) - (double)g0;
+            return bin >= 0.0 && bin < (double)gn ? (int)bin : -1;
+        };
+        auto add = [&](int bin, long long re, long long im) {
+            atomicAdd(&acc[2 * bin], (unsigned long long)re);
+            atomicAdd(&acc[2 * bin + 1], (unsigned long long)im);
+        };
+        for (int64_t j = e0 + tid; j < e1; j += CIR_B) {
+            if (!env_valid[j]) continue;
+            const int bin = bin_of(env_len[j]);
+            if (bin >= 0)
+                add(bin, (long long)rint((double)env_amp[j].x * scale), (long long)rint((double)env_amp[j].y * scale));
         }
+        walk(std::true_type{}, [&](const CirPair& p) {
+            int bin[2];
+            long long re[2], im[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                bin[i] = p.a[i].x != 0.0f || p.a[i].y != 0.0f ? bin_of(p.len[i]) : -1;
+                double ar, ai;
+                cir_weight(p.a[i], p.g[i], ar, ai);
+                re[i] = cir_i64(rint(ar * scale));
+                im[i] = cir_i64(rint(ai * scale));
+            }
+            // the bins of the wave one by one, then lane by lane if there are many
+            for (int k = 0; k < 4; ++k) {
+                const int any = bin[0] >= 0 ? bin[0] : bin[1];
+                const unsigned long long act = __ballot(any >= 0);
+                if (!act) return;
+                const int b0 = __builtin_amdgcn_readlane(any, __builtin_ctzll(act));
+                const bool m0 = bin[0] == b0, m1 = bin[1] == b0;
+                const long long tr = wave_sum_i64((m0 ? re[0] : 0) + (m1 ? re[1] : 0));
+                const long long ti = wave_sum_i64((m0 ? im[0] : 0) + (m1 ? im[1] : 0));
+                if (lane == 63) add(b0, tr, ti);
+                if (m0) bin[0] = -1;
+                if (m1) bin[1] = -1;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (bin[i] >= 0) add(bin[i], re[i], im[i]);
+        });
         __syncthreads();
-        for (int64_t i = tid; i < gn; i += CIR_B)
+        for (int i = tid; i < gn; i += CIR_B)
             cir[r * n_bins + g0 + i] = make_float2((float)((double)(long long)acc[2 * i] * unscale),
                                                    (float)((double)(long long)acc[2 * i + 1] * unscale));
         __syncthreads();
@@ -2331,10 +2393,19 @@ void cir(Ctx& c, const Channel& ch, const float* gamma, double bin_s, int64_t n_
     if (ch.R == 0 || n_bins == 0) return;
     const double l_bin = 299792458.0 * bin_s;
     const bool ris = ch.M > 0 && ch.cir_uptr.bytes > 0;
-    hipLaunchKernelGGL(k_cir, dim3((unsigned)ch.R), dim3(CIR_B), 0, st, ch.env_cells > 0 ? ch.env_rstart.as<int64_t>() : nullptr,
-                       ch.env_valid.as<uint8_t>(), ch.env_amp.as<float2>(), ch.env_len.as<double>(),
-                       ris ? ch.cir_uptr.as<int64_t>() : nullptr, ch.cir_amp.as<float2>(), ch.cir_len.as<double>(),
-                       ris ? ch.M : 0, (const float2*)gamma, l_bin, n_bins, (float2*)out);
+    // a length times the reciprocal, corrected, is the rounded quotient except for a divisor with all
+    // fraction bits set, and away from the ends of the range
+    uint64_t u;
+    std::memcpy(&u, &l_bin, sizeof u);
+    const bool by_inv = l_bin > 1e-100 && l_bin < 1e100 && (~u & 0xFFFFFFFFFFFFFull) != 0;
+    // the bins in passes of equal size, LDS for one pass
+    const int64_t passes = (n_bins + CIR_G - 1) / CIR_G;
+    const int gper = (int)((n_bins + passes - 1) / passes);
+    hipLaunchKernelGGL(k_cir, dim3((unsigned)ch.R), dim3(CIR_B), sizeof(unsigned long long) * 2 * (size_t)gper, st,
+                       ch.env_cells > 0 ? ch.env_rstart.as<int64_t>() : nullptr, ch.env_valid.as<uint8_t>(),
+                       ch.env_amp.as<float2>(), ch.env_len.as<double>(), ris ? ch.cir_uptr.as<int64_t>() : nullptr,
+                       ch.cir_amp.as<float2>(), ch.cir_len.as<double>(), ris ? ch.M : 0, (const float2*)gamma, l_bin,
+                       by_inv ? 1.0 / l_bin : 0.0, n_bins, gper, (float2*)out);
     HIP_CHECK(hipGetLastError());
 }
 

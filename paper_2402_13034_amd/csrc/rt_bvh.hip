@@ -974,7 +974,8 @@ __global__ void k_surf_csr(const uint64_t* keys, int64_t nt, const int32_t* n_su
 
 // Tables of the surfaces, one wave per surface with the lanes over its
 // triangles (one thread per surface, and per surface and grid cell, took 64 +
-// 119 us for 1566 surfaces of 128 triangles; 13 us so).
+// 119 us for 1566 surfaces of 128 triangles; 27 us so, 14 of them for the lists
+// of a grid finer than 4 x 4).
 //
 // A surface's plane is that of its lowest-numbered triangle; every vertex of
 // the surface must lie within RT_EPS (0.1 mm) of it (bad |= 16), and that
@@ -985,7 +986,15 @@ __global__ void k_surf_csr(const uint64_t* keys, int64_t nt, const int32_t* n_su
 // triangles use the same projection; a triangle is listed in every cell its
 // projected box, grown by a margin that covers the rounding of the FP64 edge
 // tests (relative to the coordinates and inversely to the shortest edge),
-// overlaps.  Lists keep the surface's triangle order.
+// overlaps.  Lists keep the surface's triangle order.  At least as many cells
+// as triangles (4 x 4 to 32 x 32), halved per axis until the lists fit their
+// part of g_tris: with 4 x 4 cells for every surface, a point on an office's
+// floor tile of 800 triangles met some 36 of them one behind the other, 19 of
+// the 46 ms of its per-element kernel (31 ms so; geometry of the two sources
+// 5.6 and 4.6 ms, 2.3 and 1.6 so).
+//
+// The lists of 64 triangles at a time: their bits in the cells' masks in LDS
+// (any order), then every cell's lane appends its bits' triangles in order.
 __device__ __forceinline__ double wave_dmin(double v)
 {
     for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
@@ -1000,10 +1009,15 @@ __device__ __forceinline__ double wave_dmax(double v)
 __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const int32_t* s_tris, const double* v64,
                                                      const double* t_proj, const int32_t* t_axes,
                                                      const int32_t* n_surf_p, double* s_plane, double* s_box,
-                                                     int32_t* g_axes, double* g_frame, int32_t* g_cnt,
+                                                     int32_t* g_axes, double* g_frame, int32_t* g_off,
                                                      int32_t* g_tris, int32_t* bad)
 {
+    constexpr int CELLS = 1 << (2 * RT_SGRID_HI);
+    __shared__ int l_cnt[4][CELLS];                  // per wave and cell: triangles listed so far
+    __shared__ unsigned long long l_mask[4][CELLS];  // and those of the 64 at hand
     const int lane = threadIdx.x & 63;
+    volatile int* cnt = l_cnt[threadIdx.x >> 6];
+    volatile unsigned long long* mask = l_mask[threadIdx.x >> 6];
     const int n_surf = *n_surf_p;
     for (int s = (int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); s < n_surf;
          s += (int)(gridDim.x * (blockDim.x >> 6))) {
@@ -1012,7 +1026,6 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
             if (lane < RT_PLANE) s_plane[RT_PLANE * (int64_t)s + lane] = 0.0;
             if (lane < 6) s_box[6 * (int64_t)s + lane] = lane < 3 ? 1e300 : -1e300;
             if (lane == 0) g_axes[s] = -1;
-            if (lane < RT_SGRID_CELLS) g_cnt[(int64_t)s * RT_SGRID_CELLS + lane] = 0;
             continue;
         }
         const double* v = v64 + 9 * (int64_t)s_tris[b];
@@ -1075,50 +1088,117 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
         const double u0 = i0 == 0 ? lo[0] : i0 == 1 ? lo[1] : lo[2], v0 = i1 == 0 ? lo[0] : i1 == 1 ? lo[1] : lo[2];
         const double eu = (i0 == 0 ? hi[0] : i0 == 1 ? hi[1] : hi[2]) - u0;
         const double ev = (i1 == 0 ? hi[0] : i1 == 1 ? hi[1] : hi[2]) - v0;
-        const double pu = eu > 0.0 ? (double)RT_SGRID / eu : 0.0, pv = ev > 0.0 ? (double)RT_SGRID / ev : 0.0;
+        if (!grid) {
+            if (lane == 0) g_axes[s] = -1;
+            continue;
+        }
+        const int n = e - b;
+        int lg = RT_SGRID_LO;
+        while (lg < RT_SGRID_HI && (1 << (2 * lg)) < n) ++lg;
+        double pu, pv;
+        // cells of triangle j of the surface, first and last along u and v, a byte each; t: the triangle, -1: none
+        auto cells_of = [&](int j, int& t) {
+            t = -1;
+            if (j >= e) return 0u;
+            const int tj = s_tris[j];
+            if (t_axes[tj] & 16) return 0u;   // a degenerate triangle contains nothing
+            t = tj;
+            const double* q = t_proj + 6 * (int64_t)t;
+            const double umin = fmin(q[0], fmin(q[2], q[4])), umax = fmax(q[0], fmax(q[2], q[4]));
+            const double vmin = fmin(q[1], fmin(q[3], q[5])), vmax = fmax(q[1], fmax(q[3], q[5]));
+            const double C = fmax(fmax(fabs(umin), fabs(umax)), fmax(fabs(vmin), fabs(vmax)));
+            auto sq = [](double x, double y) { return x * x + y * y; };
+            const double l2 = fmin(sq(q[2] - q[0], q[3] - q[1]),
+                                   fmin(sq(q[4] - q[2], q[5] - q[3]), sq(q[0] - q[4], q[1] - q[5])));
+            const double lmin = fmax(sqrt(l2), 1e-300);
+            const double m = 1e-13 * (C * C / lmin) + 1e-9 * C + 1e-12;
+            const unsigned c0 = sgrid_index(umin - m, u0, pu, lg), c1 = sgrid_index(umax + m, u0, pu, lg);
+            const unsigned d0 = sgrid_index(vmin - m, v0, pv, lg), d1 = sgrid_index(vmax + m, v0, pv, lg);
+            return c0 | c1 << 8 | d0 << 16 | d1 << 24;
+        };
+        auto each_cell = [&](unsigned r, auto f) {
+            for (unsigned i = r & 255u; i <= (r >> 8 & 255u); ++i)
+                for (unsigned k = r >> 16 & 255u; k <= r >> 24; ++k) f((i << lg) + k);
+        };
+        // between phases that hand LDS words from lane to lane (one wave: its LDS operations keep their order)
+        auto handed = [] {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+        int t, first_t[2] = {-1, -1};             // the first 128 triangles stay in registers
+        unsigned cells, first_cells[2] = {0, 0};
+        for (;; --lg) {
+            pu = eu > 0.0 ? (double)(1 << lg) / eu : 0.0;
+            pv = ev > 0.0 ? (double)(1 << lg) / ev : 0.0;
+            for (int c = lane; c < 1 << (2 * lg); c += 64) {
+                cnt[c] = 0;
+                mask[c] = 0ull;
+            }
+            handed();
+            long long total = 0;
+            for (int j0 = b; j0 < e; j0 += 64) {
+                cells = cells_of(j0 + lane, t);
+                if (j0 == b) first_t[0] = t, first_cells[0] = cells;
+                if (j0 == b + 64) first_t[1] = t, first_cells[1] = cells;
+                if (t < 0) continue;
+                total += (int)(((cells >> 8 & 255u) - (cells & 255u) + 1u) * ((cells >> 24) - (cells >> 16 & 255u) + 1u));
+                each_cell(cells, [&](unsigned c) { atomicAdd((int*)&cnt[c], 1); });
+            }
+            handed();
+            for (int o = 32; o > 0; o >>= 1) total += __shfl_xor(total, o, 64);
+            if (lg == RT_SGRID_LO || total <= (long long)RT_SGRID_CAP * n) break;
+        }
+        const int nc = 1 << (2 * lg);
         if (lane == 0) {
-            g_axes[s] = grid ? amax : -1;
+            g_axes[s] = amax | lg << 4;
             double* f = g_frame + 4 * (int64_t)s;
             f[0] = u0;
             f[1] = v0;
             f[2] = pu;
             f[3] = pv;
         }
-        int cnt[RT_SGRID_CELLS];   // triangles listed so far per cell (the same on every lane)
-#pragma unroll
-        for (int c = 0; c < RT_SGRID_CELLS; ++c) cnt[c] = 0;
-        const int64_t base = (int64_t)b * RT_SGRID_CELLS;
-        for (int j0 = b; grid && j0 < e; j0 += 64) {
-            unsigned cells = 0;   // bit per cell this lane's triangle goes to
-            int t = -1;
-            if (j0 + lane < e) {
-                t = s_tris[j0 + lane];
-                if (!(t_axes[t] & 16)) {   // a degenerate triangle contains nothing
-                    const double* q = t_proj + 6 * (int64_t)t;
-                    const double umin = fmin(q[0], fmin(q[2], q[4])), umax = fmax(q[0], fmax(q[2], q[4]));
-                    const double vmin = fmin(q[1], fmin(q[3], q[5])), vmax = fmax(q[1], fmax(q[3], q[5]));
-                    const double C = fmax(fmax(fabs(umin), fabs(umax)), fmax(fabs(vmin), fabs(vmax)));
-                    const double l0 = hypot(q[2] - q[0], q[3] - q[1]), l1 = hypot(q[4] - q[2], q[5] - q[3]),
-                                 l2 = hypot(q[0] - q[4], q[1] - q[5]);
-                    const double lmin = fmax(fmin(l0, fmin(l1, l2)), 1e-300);
-                    const double m = 1e-13 * (C * C / lmin) + 1e-9 * C + 1e-12;
-                    const int c0 = sgrid_index(umin - m, u0, pu), c1 = sgrid_index(umax + m, u0, pu);
-                    const int d0 = sgrid_index(vmin - m, v0, pv), d1 = sgrid_index(vmax + m, v0, pv);
-                    const unsigned row = ((2u << d1) - 1u) & ~((1u << d0) - 1u);   // cells d0..d1 of one row
-                    for (int i = c0; i <= c1; ++i) cells |= row << (RT_SGRID * i);
-                }
+        // counts to first places
+        int32_t* off = g_off + (int64_t)RT_SGRID_CAP * b + s;
+        int32_t* list = g_tris + (int64_t)RT_SGRID_CAP * b;
+        int run = 0;
+        for (int c = lane; c < ((nc + 63) & ~63); c += 64) {   // every lane the same number of times
+            const int v = c < nc ? cnt[c] : 0;
+            int x = v;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
             }
-#pragma unroll
-            for (int c = 0; c < RT_SGRID_CELLS; ++c) {
-                const bool in = (cells >> c) & 1u;
-                const unsigned long long m = __ballot(in);
-                if (in) g_tris[base + (int64_t)c * (e - b) + cnt[c] + __popcll(m & ((1ull << lane) - 1ull))] = t;
-                cnt[c] += (int)__popcll(m);
+            if (c < nc) {
+                off[c] = run + x - v;
+                cnt[c] = run + x - v;
             }
+            run += __shfl(x, 63, 64);
         }
-#pragma unroll
-        for (int c = 0; c < RT_SGRID_CELLS; ++c)
-            if (lane == c) g_cnt[(int64_t)s * RT_SGRID_CELLS + c] = cnt[c];
+        if (lane == 0) off[nc] = run;
+        for (int j0 = b; j0 < e; j0 += 64) {
+            if (j0 < b + 128) {
+                t = j0 == b ? first_t[0] : first_t[1];
+                cells = j0 == b ? first_cells[0] : first_cells[1];
+            } else {
+                cells = cells_of(j0 + lane, t);
+            }
+            if (t >= 0)
+                each_cell(cells, [&](unsigned c) { atomicOr((unsigned long long*)&mask[c], 1ull << lane); });
+            handed();
+            for (int c = lane; c < ((nc + 63) & ~63); c += 64) {
+                unsigned long long m = c < nc ? mask[c] : 0ull;
+                int at = c < nc ? cnt[c] : 0;
+                if (m) mask[c] = 0ull;
+                while (__ballot(m != 0ull) != 0ull) {
+                    const int from = m ? __builtin_ctzll(m) : 0;
+                    const int tt = __shfl(t, from, 64);
+                    if (m) list[at++] = tt;
+                    m &= m - 1ull;
+                }
+                if (c < nc) cnt[c] = at;
+            }
+            handed();
+        }
     }
 }
 
@@ -1403,12 +1483,12 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
 
     s.g_axes = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
     s.g_frame = Scratch(c, sizeof(double) * 4 * (size_t)nt, st);
-    s.g_cnt = Scratch(c, sizeof(int32_t) * RT_SGRID_CELLS * (size_t)nt, st);
-    s.g_tris = Scratch(c, sizeof(int32_t) * RT_SGRID_CELLS * (size_t)nt, st);
+    s.g_off = Scratch(c, sizeof(int32_t) * (RT_SGRID_CAP + 1) * (size_t)nt, st);   // n_surf <= nt
+    s.g_tris = Scratch(c, sizeof(int32_t) * RT_SGRID_CAP * (size_t)nt, st);
     hipLaunchKernelGGL(k_surf_tables, dim3(std::min<unsigned>(blocks_for(nt, 4), 2048)), dim3(256), 0, st,
                        s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), s.v64.as<double>(), t_proj.as<double>(),
                        t_axes.as<int32_t>(), nsurf, s.s_plane.as<double>(), s.s_box.as<double>(),
-                       s.g_axes.as<int32_t>(), s.g_frame.as<double>(), s.g_cnt.as<int32_t>(),
+                       s.g_axes.as<int32_t>(), s.g_frame.as<double>(), s.g_off.as<int32_t>(),
                        s.g_tris.as<int32_t>(), bad);
     HIP_CHECK(hipGetLastError());
     // one read-back: input checks, tree checks, surface count

@@ -131,7 +131,7 @@ struct Scene {
     Scratch tri4, nodes, node4, v64, refl, surf, s_ptr, s_tris, s_plane, s_box, t_edge;
     Scratch mat;   // float2 per triangle (eps_r, sigma), empty until set
     Scratch nrm;   // 3 doubles per triangle: unit normal, computed with the materials
-    Scratch g_axes, g_frame, g_cnt, g_tris;
+    Scratch g_axes, g_frame, g_off, g_tris;
     Scratch box;   // 6 floats: the vertices' lower and upper corner
     SceneView view() const {
         SceneView v;
@@ -154,7 +154,7 @@ struct Scene {
         v.t_edge = t_edge.as<double>();
         v.g_axes = g_axes.as<int32_t>();
         v.g_frame = g_frame.as<double>();
-        v.g_cnt = g_cnt.as<int32_t>();
+        v.g_off = g_off.as<int32_t>();
         v.g_tris = g_tris.as<int32_t>();
         return v;
     }

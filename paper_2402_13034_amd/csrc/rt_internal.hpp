@@ -57,24 +57,26 @@ struct SceneView {
     const double* s_plane; // RT_PLANE per surface: n (not unit), c = n . v0 of its first triangle, n . n, 1 / (n . n)
     const double* s_box;   // 6 per surface: lo, hi (inflated by 1e-9 m)
     const double* t_edge;  // RT_EDGE per triangle: the edge functions of the containment test, see triangle_edges
-    // containment grid per surface (RT_SGRID x RT_SGRID cells over the surface box in the
-    // projection all its triangles share; g_axes -1: no grid, scan every triangle)
-    const int32_t* g_axes;   // per surface
+    // containment grid per surface: 2^lg x 2^lg cells (lg of RT_SGRID_LO .. RT_SGRID_HI) over the
+    // surface box in the projection all its triangles share
+    const int32_t* g_axes;   // per surface: the projection's axes | lg << 4; -1: no grid, scan every triangle
     const double* g_frame;   // 4 per surface: u0, v0, cells per unit along u and v
-    const int32_t* g_cnt;    // per (surface, cell): triangles listed
-    const int32_t* g_tris;   // cell (c) of surface sf lists from s_ptr[sf] * cells + c * n_tris(sf)
+    const int32_t* g_off;    // cell c of surface sf lists [off[c], off[c + 1]) of the surface's part of g_tris,
+                             // off = g_off + RT_SGRID_CAP * s_ptr[sf] + sf
+    const int32_t* g_tris;   // surface sf's part: from RT_SGRID_CAP * s_ptr[sf] on
 };
 
 #define RT_PLANE 6
 #define RT_EDGE 16
-#define RT_SGRID 4
-#define RT_SGRID_CELLS (RT_SGRID * RT_SGRID)
+#define RT_SGRID_LO 2
+#define RT_SGRID_HI 5
+#define RT_SGRID_CAP 16   // cells and list entries of a surface per triangle, at most
 
-// Grid cell coordinate of x (monotone in x, clamped to the grid)
-__host__ __device__ __forceinline__ int sgrid_index(double x, double origin, double per_unit)
+// Grid cell coordinate of x (monotone in x, clamped to the 2^lg cells)
+__host__ __device__ __forceinline__ int sgrid_index(double x, double origin, double per_unit, int lg)
 {
     double y = (x - origin) * per_unit;
-    y = fmin(fmax(y, 0.0), (double)(RT_SGRID - 1));
+    y = fmin(fmax(y, 0.0), (double)((1 << lg) - 1));
     return (int)y;
 }
 
@@ -1148,14 +1150,15 @@ __device__ inline int surface_contains(const SceneView& s, int sf, const double*
     const int gax = CNT ? -1 : s.g_axes[sf];
     if (gax >= 0) {
         const double* fr = s.g_frame + 4 * sf;
-        const double u = (gax & 3) == 0 ? px : (gax & 3) == 1 ? py : pz;
-        const double v = (gax >> 2) == 0 ? px : (gax >> 2) == 1 ? py : pz;
-        const int cell = sgrid_index(u, fr[0], fr[2]) * RT_SGRID + sgrid_index(v, fr[1], fr[3]);
-        const int b = s.s_ptr[sf];
-        const int64_t beg = (int64_t)b * RT_SGRID_CELLS + (int64_t)cell * (s.s_ptr[sf + 1] - b);
-        const int cnt = s.g_cnt[sf * RT_SGRID_CELLS + cell];
-        for (int j = 0; j < cnt; ++j) {
-            const int t = s.g_tris[beg + j];
+        const int au = gax & 3, av = (gax >> 2) & 3, lg = gax >> 4;
+        const double u = au == 0 ? px : au == 1 ? py : pz;
+        const double v = av == 0 ? px : av == 1 ? py : pz;
+        const int cell = (sgrid_index(u, fr[0], fr[2], lg) << lg) + sgrid_index(v, fr[1], fr[3], lg);
+        const int64_t b = (int64_t)RT_SGRID_CAP * s.s_ptr[sf];
+        const int32_t* off = s.g_off + b + sf + cell;
+        const int end = off[1];
+        for (int j = off[0]; j < end; ++j) {
+            const int t = s.g_tris[b + j];
             if (contains_proj<false>(s, t, p)) return t;
         }
         return -1;

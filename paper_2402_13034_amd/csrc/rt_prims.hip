@@ -152,21 +152,24 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_tiles(const In* in, int64_t n, 
 }
 
 // Up to SCAN_ONE_MAX values in one workgroup that carries its sum from one
-// stretch of 8192 to the next: one launch of 5 us where the three of the tiled
-// scan take 14 (a receiver grid's counts; 4096 values).
-constexpr int SCAN_ONE_T = 1024;
-constexpr int64_t SCAN_ONE_MAX = 32768;
+// stretch of 4096 to the next: one launch of 5 us where the three of the tiled
+// scan take 14 (a receiver grid's counts; 4096 values).  Four waves: sixteen
+// find room on a compute unit only between a busy kernel's workgroups (100 to
+// 400 us beside the geometry kernel of the other branch).
+constexpr int SCAN_ONE_T = 256;
+constexpr int SCAN_ONE_IPT = 16;
+constexpr int64_t SCAN_ONE_MAX = 16384;
 template <class In, class Out>
 __global__ __launch_bounds__(SCAN_ONE_T) void k_scan_one(const In* in, int64_t n, Out* out, Out* total)
 {
     __shared__ Out wsum[SCAN_ONE_T / 64];
     Out carry = 0;
-    for (int64_t b0 = 0; b0 < n; b0 += SCAN_ONE_T * SCAN_IPT) {
-        const int64_t base = b0 + (int64_t)threadIdx.x * SCAN_IPT;
-        Out v[SCAN_IPT];
+    for (int64_t b0 = 0; b0 < n; b0 += SCAN_ONE_T * SCAN_ONE_IPT) {
+        const int64_t base = b0 + (int64_t)threadIdx.x * SCAN_ONE_IPT;
+        Out v[SCAN_ONE_IPT];
         Out s = 0;
 #pragma unroll
-        for (int j = 0; j < SCAN_IPT; ++j) {
+        for (int j = 0; j < SCAN_ONE_IPT; ++j) {
             v[j] = base + j < n ? (Out)in[base + j] : (Out)0;
             s += v[j];
         }
@@ -174,7 +177,7 @@ __global__ __launch_bounds__(SCAN_ONE_T) void k_scan_one(const In* in, int64_t n
         Out run = carry + block_exclusive_add<Out, SCAN_ONE_T>(s, wsum, &tot);
         carry += tot;
 #pragma unroll
-        for (int j = 0; j < SCAN_IPT; ++j) {
+        for (int j = 0; j < SCAN_ONE_IPT; ++j) {
             if (base + j < n) out[base + j] = run;
             run += v[j];
         }

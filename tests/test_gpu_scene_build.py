@@ -117,3 +117,65 @@ def test_counting_walk_is_the_morton_tree(ctx):
         assert np.array_equal(g[0][0], got[0][0][0]) and np.array_equal(g[0][1], got[0][0][1])
         assert g[2] == got[0][2]
     assert got[1][1] == got[2][1] and min(got[1][1]) > 0
+
+
+# triangles per face at which the containment grid gets finer (16, 64, 256 cells; 1024 are the most), and a fan whose
+# long triangles overlap so many cells that the grid is halved until its lists fit
+@pytest.mark.parametrize("mesh,n", [("cells", 2), ("cells", 18), ("cells", 128), ("cells", 242), ("cells", 512),
+                                    ("cells", 1152), ("fan", 15), ("fan", 65), ("fan", 300), ("fan", 1500)])
+def test_containment_grid(ctx, mesh, n):
+    """A box whose faces are single surfaces of n triangles, each with its own
+    coefficient: the triangle of every reflection against the oracle's scan of
+    the whole surface, fields against the build that scans too."""
+    from oracle import oracle as O
+    from paper_2402_13034_amd import risrt
+    rng = np.random.default_rng(n)
+    size = np.array([4.0, 3.0, 2.5])
+    V, T, surf = [], [], []
+    for axis in range(3):
+        for side in (0.0, 1.0):
+            o, eu, ev = np.zeros(3), np.zeros(3), np.zeros(3)
+            o[axis] = side * size[axis]
+            eu[(axis + 1) % 3] = size[(axis + 1) % 3]
+            ev[(axis + 2) % 3] = size[(axis + 2) % 3]
+            base = sum(len(v) for v in V)
+            if mesh == "cells":
+                g = int(np.sqrt(n // 2))
+                a, b = np.meshgrid(np.arange(g + 1) / g, np.arange(g + 1) / g, indexing="ij")
+                i, j = (x.ravel() for x in np.meshgrid(np.arange(g), np.arange(g), indexing="ij"))
+                q = i * (g + 1) + j
+                tri = np.r_[np.c_[q, q + g + 1, q + 1], np.c_[q + 1, q + g + 1, q + g + 2]]
+                pts = np.c_[a.ravel(), b.ravel()]
+            else:   # from one corner over the two far edges
+                h = n // 2
+                e = np.r_[np.c_[np.ones(h), np.arange(h) / h], np.c_[1 - np.arange(n - h) / (n - h), np.ones(n - h)],
+                          [[0.0, 1.0]]]
+                pts = np.r_[[[0.0, 0.0]], e]
+                tri = np.c_[np.zeros(n, int), np.arange(1, n + 1), np.arange(2, n + 2)]
+            V.append(o + pts[:, :1] * eu + pts[:, 1:] * ev)
+            T.append(base + rng.permutation(tri))
+            surf += [2 * axis + int(side)] * len(tri)
+    V, T = np.concatenate(V).astype(np.float32), np.concatenate(T).astype(np.int32)
+    re = rng.uniform(0.2, 0.9, len(T)).astype(np.float32)
+    p = synth.lab_room(nx=3, ny=3, n_rays=4_000, order=2)
+    p.scene = synth.Scene(V, T, re, np.zeros_like(re), np.array(surf, np.int32))
+    p.tx_pos = np.array([0.7, 0.6, 1.9])
+    p.ris.centre = np.array([3.99, 1.5, 1.2])
+    p.ris.elems = p.ris.centre + rng.uniform(-0.3, 0.3, (70, 3)) * [0.0, 1.0, 1.0]
+    p.gamma = np.ones((70, 1), np.complex128)
+    p.rx_pos = rng.uniform(0.1, 0.9, (9, 3)) * size
+    print("case grid", mesh, n, flush=True)
+    out = []
+    for flags in (risrt.FLAG_KEEP_PATHS, risrt.FLAG_COUNT_WORK):
+        scene, ris = risrt.upload_problem(ctx, p)
+        ch, _ = risrt.trace_problem(ctx, p, scene, ris, flags=flags)
+        out.append(ctx.channel_read(ch))
+        if flags == risrt.FLAG_KEEP_PATHS:
+            kept = ctx.paths_read(ch)
+        for h in (ch, scene, ris):
+            ctx.destroy(h)
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    with O.accelerated():
+        ref = O.trace(p)
+    assert np.array_equal(kept["env"]["tri"][:, :2], ref["env_tri"][:, :2])
+    assert np.array_equal(kept["ris_valid"], ref["ris_valid"])

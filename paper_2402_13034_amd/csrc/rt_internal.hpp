@@ -814,10 +814,9 @@ __device__ __forceinline__ float wave_max(float v)
 // All legs of one slot at once: one tube per leg, frontier and candidate
 // entries tagged with their leg (3 bits above a 29-bit node or slot index),
 // so the wave walks the levels of the tree once for up to KM + 1 legs.
-// lb: the wave's leg rays in LDS, [leg][7][64] = ox, oy, oz, dx, dy, dz, tmax;
-// end: the last leg's end point (the receiver, the same for every lane);
-// tube: 3 float4 per leg in LDS; front: 2 x RT_TUBE_FRONT ints, cand:
-// RT_TUBE_CAND ints, wstack: RT_STACK4 ints (fallback), all per wave;
+// legs: the lanes' rays; end: the last leg's end point (the receiver, the same
+// for every lane); tube: 3 float4 per leg in LDS; front: 2 x RT_TUBE_FRONT
+// ints (the fallback's stack as well), cand: RT_TUBE_CAND ints, all per wave;
 // seq: the slot's surfaces (wave-uniform), k its order; ok: the lane's path
 // is still valid.  Returns the lane's bit set of blocked legs, plus
 // RT_TUBE_FELL_BACK if the lists overflowed and the legs were walked one by
@@ -849,12 +848,48 @@ __device__ __forceinline__ int leg_surface_b(const int* seq, int j, int k)
     return v;
 }
 
+// A lane's leg rays, 7 floats each: ox, oy, oz, dx, dy, dz, tmax.  The first
+// REG legs in registers, the others in the wave's part of LDS, [leg][7][64].
+// LDS is given out in 1280 bytes of a CU's 160 KB: with two of six legs in registers
+// four waves fit a SIMD (three without), with one of four five (four without).
+template <int KM>
+struct LegRays {
+    static constexpr int REG = KM > RT_KM_SMALL ? 2 : 1;
+    static constexpr int LDS_FLOATS = (KM + 1 - REG) * 7 * 64;   // per wave
+    float reg[REG > 0 ? REG : 1][7];
+    float* lds;   // this lane's first
+    // j, c: constants
+    __device__ __forceinline__ void set(int j, int c, float v)
+    {
+        if (j < REG)
+            reg[j < REG ? j : 0][c] = v;
+        else
+            lds[((j - REG) * 7 + c) * 64] = v;
+    }
+    __device__ __forceinline__ float at(int j, int c) const
+    {
+        return j < REG ? reg[j < REG ? j : 0][c] : lds[((j - REG) * 7 + c) * 64];
+    }
+    // leg j, the same for every lane of the wave
+    __device__ __forceinline__ void get(int j, float* r) const
+    {
+        if (j < REG) {
+#pragma unroll
+            for (int c = 0; c < 7; ++c) r[c] = j == 0 ? reg[0][c] : reg[REG > 1 ? 1 : 0][c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 7; ++c) r[c] = lds[((j - REG) * 7 + c) * 64];
+        }
+    }
+};
+
 template <int KM>
 __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool ok, int k, const int* seq,
-                                                      const float* lb, const float* end, float4* tube, int* front,
-                                                      int* cand, int* wstack)
+                                                      const LegRays<KM>& legs, const float* end, float4* tube,
+                                                      int* front, int* cand)
 {
     static_assert(KM + 1 <= 8, "three bits of leg index");
+    static_assert(2 * RT_TUBE_FRONT >= RT_STACK4, "the fallback's stack");
     const int lane = threadIdx.x & 63;
     const float tmin = (float)RT_EPS;
     unsigned blocked = 0;
@@ -873,9 +908,9 @@ __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool o
         if (j > k + 1) break;
         float cx, cy, cz, d2 = 0.0f;
         if (j <= k) {
-            const float* r0 = lb + j * 7 * 64 + lane;
-            const float ox = r0[0], oy = r0[64], oz = r0[128];
-            live |= __ballot(ok && r0[384] > tmin) ? 1u << j : 0u;
+            const int jc = j <= KM ? j : KM;
+            const float ox = legs.at(jc, 0), oy = legs.at(jc, 1), oz = legs.at(jc, 2);
+            live |= __ballot(ok && legs.at(jc, 6) > tmin) ? 1u << j : 0u;
             cx = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ox), lead));
             cy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(oy), lead));
             cz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(oz), lead));
@@ -991,13 +1026,12 @@ __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool o
     if (overflow) {   // exact walk of every leg
         blocked = RT_TUBE_FELL_BACK;
         for (int j = 0; j <= k; ++j) {
-            const float* r0 = lb + j * 7 * 64 + lane;
-            const float tmax = r0[384];
-            const bool searching = ok && tmax > tmin;
+            float r[7];
+            legs.get(j, r);
+            const bool searching = ok && r[6] > tmin;
             const int sa = j == 0 ? -1 : seq[j - 1];
             const int sb = j == k ? -1 : seq[j];
-            if (any_hit_wave4(s, searching, r0[0], r0[64], r0[128], r0[192], r0[256], r0[320], tmin, tmax, sa, sb,
-                              wstack))
+            if (any_hit_wave4(s, searching, r[0], r[1], r[2], r[3], r[4], r[5], tmin, r[6], sa, sb, front))
                 blocked |= 1u << j;
         }
         return blocked;
@@ -1007,9 +1041,9 @@ __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool o
         const int slot = (int)(v & RT_TUBE_IDX_MASK), j = (int)(v >> RT_TUBE_TAG_SHIFT);
         const float4* tp = s.tri4 + 3 * (int64_t)slot;
         const float4 a = tp[0], b = tp[1], c = tp[2];
-        const float* r0 = lb + j * 7 * 64 + lane;
-        const float tmax = r0[384];
-        const float ox = r0[0], oy = r0[64], oz = r0[128], dx = r0[192], dy = r0[256], dz = r0[320];
+        float ray[7];
+        legs.get(j, ray);
+        const float ox = ray[0], oy = ray[1], oz = ray[2], dx = ray[3], dy = ray[4], dz = ray[5], tmax = ray[6];
         const bool open = ok && tmax > tmin && !(blocked & (1u << j));
         // most candidates are missed by every lane: decided without the division
         if (__ballot(open && mt_maybe(ox, oy, oz, dx, dy, dz, a, b, c)) == 0ull) continue;

@@ -1179,10 +1179,13 @@ constexpr int RIS_B = 128;
 // Back-trace like image_backtrace, but each reflection first tries the
 // triangle the RIS-centre path used (hint); a point on a surface lies in
 // exactly one of its triangles, so the result is the same as a full search.
+// S: the source; img: this lane's images 1 .. KM - 1 in LDS, [3][64] each;
+// last: image k (used for k = KM).
+typedef double lds_double __attribute__((may_alias));
 template <bool CNT, int KM>
 __device__ inline bool image_backtrace_hint(const SceneView& s, const int* seq, const int* hint, int k,
-                                            const double (*I)[3], const double* X, double (*P)[3], int* tri,
-                                            WorkCount* wc)
+                                            const double* S, const lds_double* img, const double* last,
+                                            const double* X, double (*P)[3], int* tri, WorkCount* wc)
 {
 #pragma clang fp contract(off)
     double Q[3] = {X[0], X[1], X[2]};
@@ -1190,12 +1193,14 @@ __device__ inline bool image_backtrace_hint(const SceneView& s, const int* seq, 
     for (int i = KM; i >= 1; --i) {
         if (i > k) continue;
         const double* pl = s.s_plane + RT_PLANE * seq[i - 1];
-        double w0 = Q[0] - I[i][0], w1 = Q[1] - I[i][1], w2 = Q[2] - I[i][2];
+        double Im[3];
+        for (int q = 0; q < 3; ++q) Im[q] = i == KM ? last[q] : img[(3 * (i - 1) + q) * 64];
+        double w0 = Q[0] - Im[0], w1 = Q[1] - Im[1], w2 = Q[2] - Im[2];
         double den = pl[0] * w0 + pl[1] * w1 + pl[2] * w2;
         if (den == 0.0) return false;
-        double sp = div_fast(pl[3] - (pl[0] * I[i][0] + pl[1] * I[i][1] + pl[2] * I[i][2]), den);
+        double sp = div_fast(pl[3] - (pl[0] * Im[0] + pl[1] * Im[1] + pl[2] * Im[2]), den);
         if (!(sp > 0.0 && sp < 1.0)) return false;
-        double p[3] = {I[i][0] + sp * w0, I[i][1] + sp * w1, I[i][2] + sp * w2};
+        double p[3] = {Im[0] + sp * w0, Im[1] + sp * w1, Im[2] + sp * w2};
         int h = hint[i - 1];
         if (CNT && h >= 0) wc->contain++;
         int t = (h >= 0 && contains_proj<true>(s, h, p)) ? h : surface_contains<CNT>(s, seq[i - 1], p, wc);
@@ -1210,7 +1215,7 @@ __device__ inline bool image_backtrace_hint(const SceneView& s, const int* seq, 
         const double* pl = s.s_plane + RT_PLANE * seq[i];
         double prev[3], next[3];
         for (int q = 0; q < 3; ++q) {
-            prev[q] = i == 0 ? I[0][q] : P[i > 0 ? i - 1 : 0][q];
+            prev[q] = i == 0 ? S[q] : P[i > 0 ? i - 1 : 0][q];
             next[q] = (i == k - 1 || i + 1 >= KM) ? X[q] : P[i + 1 < KM ? i + 1 : 0][q];
         }
         double a = plane_side(pl, prev);
@@ -1222,34 +1227,41 @@ __device__ inline bool image_backtrace_hint(const SceneView& s, const int* seq, 
 
 // CNT: counting build; work[0..4] += node visits, triangle tests,
 // containment tests, (slot, element) pairs, legs.
-#ifndef RT_RIS_WAVES_PER_SIMD
-#define RT_RIS_WAVES_PER_SIMD 4   // register cap that measured fastest on the lab room
-#endif
+//
+// Waves a SIMD: bound by issue and latency together, so every wave more counts
+// (lab room 1110 us with three, 945 with four; office floor 42 ms with two, 31
+// with three).  Registers and LDS are cut to five for up to order 3 (96
+// registers: lab room 880 us, 64 x 64 receivers among 50000 triangles 1030 ->
+// 930) and to four above (28 ms): the images of the elements wait in the legs'
+// LDS until the legs are written there, one or two legs stay in registers.  The
+// instances with more to keep stay at four.
 
 // FRES: Fresnel coefficients of the materials (tc.fresnel) instead of the fixed ones
 template <bool BRUTE, bool KEEP, int STK, bool CNT, bool FRES, int KM>
-__global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView s, TraceConst tc, RisView rv, const TxmRec* txm,
+__global__ __launch_bounds__(RIS_B, KEEP || BRUTE || CNT || KM > RT_KM_SMALL ? 4 : 5) void k_ris(SceneView s, TraceConst tc, RisView rv, const TxmRec* txm,
                                                const double* rx, int64_t R, const int64_t* uptr,
                                                const int32_t* useq, const uint64_t* order, int n_mchunk, float2* H,
                                                uint8_t* rvalid, float2* camp, double* clen, unsigned long long* segs,
                                                unsigned long long* work, unsigned long long* fallbacks)
 {
-    // one traversal stack per wave (the 4-wide walk needs RT_STACK4 >= STK entries)
-    __shared__ int wstack[RT_STACK4 * (RIS_B / 64)];
     // the rays of a slot's legs wait in LDS while earlier legs are walked (fewer live registers)
-    __shared__ float legbuf[RIS_B / 64][KM + 1][7][64];
-    // per-wave frontier and candidate lists of the tube walk
+    static_assert(LegRays<KM>::LDS_FLOATS >= 6 * (KM - 1) * 64, "the images of a lane");
+    __shared__ __attribute__((aligned(16))) float legbuf[RIS_B / 64][LegRays<KM>::LDS_FLOATS];
+    // per-wave frontier and candidate lists of the tube walk; the frontier's room is the stack of the walks
+    // leg by leg
     __shared__ int tfront[RIS_B / 64][2 * RT_TUBE_FRONT];
     __shared__ int tcand[RIS_B / 64][RT_TUBE_CAND];
     __shared__ float4 ttube[RIS_B / 64][3 * (KM + 1)];
     constexpr int US = useq_stride(KM);
-    static_assert(RT_STACK4 >= STK, "wave stack");
+    static_assert(2 * RT_TUBE_FRONT >= STK, "wave stack");
     WorkCount wc;
     unsigned pairs = 0;
     const int wib = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave in block (uniform)
     const int64_t w = (int64_t)blockIdx.x * (RIS_B / 64) + wib;
     const int lane = threadIdx.x & 63;
-    int* my_stack = wstack + wib * RT_STACK4;
+    int* my_stack = tfront[wib];
+    LegRays<KM> legs;
+    legs.lds = &legbuf[wib][lane];
     unsigned nseg = 0;
     unsigned n_fallback = 0;   // slots whose grouped leg walk fell back (wave-uniform)
     if (w < R * n_mchunk) {
@@ -1302,14 +1314,20 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
 #pragma unroll
                 for (int j = 0; j < KM; ++j) tri[j] = -1;
                 {
-                    double I[KM + 1][3];
-                    I[0][0] = E[0];
-                    I[0][1] = E[1];
-                    I[0][2] = E[2];
+                    // the images wait in the room of the legs (KM = 5: 36 registers less)
+                    lds_double* img = (lds_double*)&legbuf[wib][0] + lane;
+                    double cur[3] = {E[0], E[1], E[2]};
 #pragma unroll
                     for (int j = 0; j < KM; ++j)
-                        if (j < k) mirror(s.s_plane + RT_PLANE * seq[j], I[j], I[j + 1]);
-                    if (ok) ok = image_backtrace_hint<CNT, KM>(s, seq, hint, k, I, X, P, tri, &wc);
+                        if (j < k) {
+                            double nx[3];
+                            mirror(s.s_plane + RT_PLANE * seq[j], cur, nx);
+                            for (int q = 0; q < 3; ++q) {
+                                cur[q] = nx[q];
+                                if (j + 1 < KM) img[(3 * j + q) * 64] = nx[q];
+                            }
+                        }
+                    if (ok) ok = image_backtrace_hint<CNT, KM>(s, seq, hint, k, E, img, cur, X, P, tri, &wc);
                 }
                 float Fout = 0.0f, Fr = 0.0f;
                 if (ok) {
@@ -1338,14 +1356,13 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
                         sqrt_inv(w0 * w0 + w1 * w1 + w2 * w2, L, il);
                         if (FRES) Lk[j] = L;
                         Dr += L;
-                        float* lb = &legbuf[wib][j][0][lane];
-                        lb[0 * 64] = (float)A[0];
-                        lb[1 * 64] = (float)A[1];
-                        lb[2 * 64] = (float)A[2];
-                        lb[3 * 64] = (float)(w0 * il);
-                        lb[4 * 64] = (float)(w1 * il);
-                        lb[5 * 64] = (float)(w2 * il);
-                        lb[6 * 64] = (float)(L - RT_EPS);
+                        legs.set(j, 0, (float)A[0]);
+                        legs.set(j, 1, (float)A[1]);
+                        legs.set(j, 2, (float)A[2]);
+                        legs.set(j, 3, (float)(w0 * il));
+                        legs.set(j, 4, (float)(w1 * il));
+                        legs.set(j, 5, (float)(w2 * il));
+                        legs.set(j, 6, (float)(L - RT_EPS));
                     }
                 }
                 if (KEEP) Dr_keep = Dr;
@@ -1383,10 +1400,10 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
                 for (int j = 0; j <= k; ++j) {
                     const int sa = leg_surface_a<KM>(seq, j);
                     const int sb = leg_surface_b<KM>(seq, j, k);
-                    const float* lb = &legbuf[wib][j][0][lane];
-                    const float ox = lb[0 * 64], oy = lb[1 * 64], oz = lb[2 * 64];
-                    const float dx = lb[3 * 64], dy = lb[4 * 64], dz = lb[5 * 64];
-                    const float tmax = lb[6 * 64];
+                    float ray[7];
+                    legs.get(j, ray);
+                    const float ox = ray[0], oy = ray[1], oz = ray[2], dx = ray[3], dy = ray[4], dz = ray[5];
+                    const float tmax = ray[6];
                     if (ok) ++nseg;
                     const bool searching = ok && tmax > tmin;
                     bool blocked;
@@ -1401,8 +1418,8 @@ __global__ __launch_bounds__(RIS_B, RT_RIS_WAVES_PER_SIMD) void k_ris(SceneView 
             } else {
                 // every leg at once; legs are counted as the sequential test would (up to the first blocked one)
                 const float end[3] = {(float)X[0], (float)X[1], (float)X[2]};
-                const unsigned res = legs_blocked_tube<KM>(s, ok, k, seq, &legbuf[wib][0][0][0], end, ttube[wib],
-                                                       tfront[wib], tcand[wib], my_stack);
+                const unsigned res = legs_blocked_tube<KM>(s, ok, k, seq, legs, end, ttube[wib], tfront[wib],
+                                                       tcand[wib]);
                 n_fallback += (res & RT_TUBE_FELL_BACK) ? 1u : 0u;   // same on every lane
                 const unsigned bl = res & ~RT_TUBE_FELL_BACK;
                 if (ok) nseg += bl ? (unsigned)(__ffs((int)bl)) : (unsigned)(k + 1);

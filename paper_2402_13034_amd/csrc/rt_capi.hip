@@ -247,27 +247,38 @@ SideStream::~SideStream()
 }
 
 // ---- small read-backs through a pinned buffer ----
+// A kernel stores the values there: its launch costs the host 3 us where a copy
+// costs 8 (a trace waits for five of them).
+constexpr int PINNED_N = 64;
 static int64_t* pinned_buf()
 {
     static thread_local int64_t* buf = nullptr;
-    if (!buf) HIP_CHECK(hipHostMalloc((void**)&buf, 64 * sizeof(int64_t), hipHostMallocDefault));
+    if (!buf)
+        HIP_CHECK(hipHostMalloc((void**)&buf, PINNED_N * sizeof(int64_t),
+                                hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
     return buf;
+}
+
+__global__ __launch_bounds__(PINNED_N) void k_publish(const int64_t* d, int n, int64_t* host)
+{
+    if ((int)threadIdx.x < n) host[threadIdx.x] = d[threadIdx.x];
 }
 
 int64_t read_i64(const int64_t* d, hipStream_t st)
 {
-    int64_t* h = pinned_buf();
-    HIP_CHECK(hipMemcpyAsync(h, d, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_CHECK(hipStreamSynchronize(st));
-    return h[0];
+    int64_t v;
+    read_i64s(d, &v, 1, st);
+    return v;
 }
 
 void read_i64s(const int64_t* d, int64_t* out, int n, hipStream_t st)
 {
+    if (n > PINNED_N) throw inval_error("too many values for one read-back");
     int64_t* h = pinned_buf();
-    HIP_CHECK(hipMemcpyAsync(h, d, sizeof(int64_t) * (size_t)n, hipMemcpyDeviceToHost, st));
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(PINNED_N), 0, st, d, n, h);
+    HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(st));
-    for (int i = 0; i < n; ++i) out[i] = h[i];
+    for (int i = 0; i < n; ++i) out[i] = ((volatile int64_t*)h)[i];
 }
 
 }  // namespace rt

@@ -27,6 +27,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <type_traits>
 #include <memory>
 #include <utility>
@@ -575,6 +576,7 @@ __global__ __launch_bounds__(TC_B) void k_table_compact2(const unsigned long lon
 // groups the work, so it takes two bits per axis more than a square grid of R
 // receivers has (24 bits for 64 x 64, three sort passes instead of six).
 constexpr int RX_IDX_BITS = 22;
+constexpr int64_t RX_SORT_MIN = 256;   // most receivers that go unsorted
 static int rx_axis_bits(int64_t R)
 {
     int lg = 0;
@@ -601,7 +603,7 @@ __global__ void k_rx_keys(const double* rx, int64_t R, const float* box, int bit
 // surfaces, planes and triangles are wave-uniform (scalar loads, no divergence
 // in the loops over a surface's triangles).  The receivers of a wave are 64
 // consecutive ones of `order` (the receivers sorted by Morton code of their
-// positions): neighbours, so that a candidate tends to fail for all lanes of a
+// positions; null: as they come): neighbours, so that a candidate tends to fail for all lanes of a
 // wave at the same bounce.  A block covers 32 candidates = one 32-bit word of
 // the receiver's row of the validity mask (mask[r * n_words + w], bit b =
 // candidate 32 w + b).
@@ -617,7 +619,7 @@ __global__ __launch_bounds__(GEO_B) void k_geo_mask(SceneView s, CandView cv, do
     const int wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int64_t slot = (int64_t)blockIdx.y * 64 + lane;
-    const int64_t r = slot < R ? (int64_t)(order[slot] & ((1ull << RX_IDX_BITS) - 1ull)) : R;
+    const int64_t r = slot >= R ? R : order ? (int64_t)(order[slot] & ((1ull << RX_IDX_BITS) - 1ull)) : slot;
     uint32_t bits = 0;
     if (r < R) {
         const double S[3] = {sx, sy, sz};
@@ -1856,6 +1858,23 @@ struct Event {
     Event& operator=(const Event&) = delete;
 };
 
+// A buffer that two streams read: an error on the way waits for both before
+// the buffer, declared ahead of this, goes back.
+struct DrainOnError {
+    hipStream_t a, b;
+    int n = std::uncaught_exceptions();
+    DrainOnError(hipStream_t a_, hipStream_t b_) : a(a_), b(b_) {}
+    ~DrainOnError()
+    {
+        if (std::uncaught_exceptions() > n) {
+            (void)hipStreamSynchronize(a);
+            (void)hipStreamSynchronize(b);
+        }
+    }
+    DrainOnError(const DrainOnError&) = delete;
+    DrainOnError& operator=(const DrainOnError&) = delete;
+};
+
 // events that can time the kernels between them
 struct TimedEvent {
     hipEvent_t e = nullptr;
@@ -1950,25 +1969,28 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     }
     clear3(ctr.as<uint64_t>(), 24, bt.table.as<uint64_t>(), (int64_t)(bt.table.bytes / 8), bu.table.as<uint64_t>(),
            (int64_t)(bu.table.bytes / 8), st);
-    SideStream side_in(c);   // the receivers' order, then the field reaching the elements
     HIP_CHECK(hipEventRecord(fork.e, st));
     if (two) HIP_CHECK(hipStreamWaitEvent(bu.st, fork.e, 0));
-    // the receivers in Morton order of their positions, for the geometry kernel: on a stream of
-    // its own ahead of the discoveries (43-57 us of a lone workgroup behind the Tx one)
+    // The receivers in Morton order of their positions, for the geometry kernel: on the centre
+    // branch's stream, ahead of the discoveries (25 us of a lone workgroup for 64 x 64 receivers,
+    // that would wait for a free compute unit behind them; the Tx branch is the one that the
+    // first geometry waits for).  A few receivers go as they come: at most 4 waves of them a
+    // candidate, and two launches and a wait cost 20 us of the 350 of a small trace.
     if (R >= ((int64_t)1 << RX_IDX_BITS)) throw inval_error("too many receivers");
-    HIP_CHECK(hipStreamWaitEvent(side_in.s, fork.e, 0));
-    Scratch rx_order(c, sizeof(uint64_t) * (size_t)(R > 0 ? R : 1), side_in.s);
+    Scratch rx_order;
+    DrainOnError drain(st, two ? bu.st : st);
     Event rx_ready;
-    if (R > 0) {
-        Scratch rx_keys(c, sizeof(uint64_t) * (size_t)R, side_in.s);
+    if (R > RX_SORT_MIN) {
+        hipStream_t sx = two ? bu.st : st;
+        rx_order = Scratch(c, sizeof(uint64_t) * (size_t)R, sx);
+        Scratch rx_keys(c, sizeof(uint64_t) * (size_t)R, sx);
         const int bits = rx_axis_bits(R);
-        hipLaunchKernelGGL(k_rx_keys, dim3(nblk(R, 256)), dim3(256), 0, side_in.s, a.rx_dev, R, a.scene->box.as<float>(),
+        hipLaunchKernelGGL(k_rx_keys, dim3(nblk(R, 256)), dim3(256), 0, sx, a.rx_dev, R, a.scene->box.as<float>(),
                            bits, rx_keys.as<uint64_t>());
         HIP_CHECK(hipGetLastError());
-        sort_keys(c, rx_keys.as<uint64_t>(), rx_order.as<uint64_t>(), R, 1, RX_IDX_BITS, RX_IDX_BITS + 3 * bits,
-                  side_in.s);
+        sort_keys(c, rx_keys.as<uint64_t>(), rx_order.as<uint64_t>(), R, 1, RX_IDX_BITS, RX_IDX_BITS + 3 * bits, sx);
+        if (two) HIP_CHECK(hipEventRecord(rx_ready.e, sx));
     }
-    HIP_CHECK(hipEventRecord(rx_ready.e, side_in.s));
     // 1-3: candidates
     cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, bt, d_disc);
     if (two) cand_phase_a<KM>(c, svc, stk, a, brute, exhaustive, keep_hits, ch, bu, d_disc);
@@ -1990,14 +2012,10 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     const int64_t n_tx = cand_phase_b(c, a, exhaustive, bt, count_of(bt));
     tm.mark();   // 2
     // 4: geometry of every (receiver, candidate)
-    HIP_CHECK(hipStreamWaitEvent(st, rx_ready.e, 0));
-    rx_order.st = st;
+    if (two && R > RX_SORT_MIN) HIP_CHECK(hipStreamWaitEvent(st, rx_ready.e, 0));
     geo_launch<KM>(c, sv, a, bt, n_tx, rx_order.as<uint64_t>());
     const int64_t n_u0 = two ? cand_phase_b(c, a, exhaustive, bu, count_of(bu)) : 0;
-    if (two) {
-        HIP_CHECK(hipStreamWaitEvent(bu.st, rx_ready.e, 0));
-        geo_launch<KM>(c, sv, a, bu, n_u0, rx_order.as<uint64_t>());
-    }
+    if (two) geo_launch<KM>(c, sv, a, bu, n_u0, rx_order.as<uint64_t>());
     out.n_cand_tx = n_tx;
     out.n_cand_u = n_u0;
     // the field reaching every element, on its own stream (forked here, launched
@@ -2005,6 +2023,7 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
     RisView rv{};
     Scratch txm;
     Event in_fork, in_ready;
+    SideStream side_in(c);
     if (a.ris) {
         rv = make_ris_view(a);
         txm = Scratch(c, sizeof(TxmRec) * (size_t)rv.M, st);
@@ -2148,6 +2167,7 @@ static void trace_km(Ctx& c, const TraceArgs& a, Channel& ch, TraceOut& out, boo
             p->st = st;
         if (!keep_paths) useq.st = st;
         order.st = st;
+        rx_order.st = st;
     }
     int64_t h[24];
     read_i64s((const int64_t*)d_ctr, h, 24, st);

@@ -1,6 +1,6 @@
 """Receivers by the thousand: where the counts per receiver go from one
 workgroup's scan to the tiled one and from one stretch of 8192 to the next, the
-order by position takes more bits, and the centre's sequences come out of one
+order by position begins and takes more bits, and the centre's sequences come out of one
 wave per receiver.  Every receiver's result is that of a trace with a few of
 them, whatever the others are."""
 import numpy as np
@@ -9,7 +9,7 @@ import pytest
 from paper_2402_13034_amd import synth
 
 pytestmark = pytest.mark.gpu
-PART = 1500
+PART = 700
 
 
 @pytest.fixture(scope="module")
@@ -30,8 +30,9 @@ def _trace(ctx, prob, flags):
     return E, H, st, p
 
 
-# R + 1 counts: one stretch less one, a full one, one more, then the same around the one-workgroup limit of 32768
-@pytest.mark.parametrize("n_rx", [1, 65, 8190, 8191, 8192, 32766, 32767, 32768])
+# unsorted up to 256; R + 1 counts: a stretch of 4096 less one, a full one, one more, two, then around the limit of
+# one workgroup's scan, 16384, and twice that
+@pytest.mark.parametrize("n_rx", [1, 65, 256, 257, 4094, 4095, 4096, 8191, 8192, 16382, 16383, 16384, 32768])
 def test_receivers_do_not_touch_each_other(ctx, n_rx):
     from paper_2402_13034_amd import risrt
     p = synth.lab_room(nx=4, ny=4, n_rays=20_000, order=2)

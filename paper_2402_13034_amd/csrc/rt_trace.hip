@@ -2284,24 +2284,20 @@ __device__ __forceinline__ long long cir_i64(double x)
     return __builtin_bit_cast(long long, v);
 }
 
-// Two records a lane, elements m and m + 64 of a slot (past the last element: no path).
+// Two records a lane (past the last element or slot: no path).
 struct CirPair {
     float2 a[2], g[2];
     double len[2];
 };
 template <bool LEN>
-__device__ __forceinline__ void cir_load(CirPair& p, const float2* camp, const double* clen, const float2* gamma,
-                                         int64_t sl, int64_t m0, int64_t M)
+__device__ __forceinline__ void cir_load(CirPair& p, int i, const float2* camp, const double* clen, const float2* gamma,
+                                         int64_t sl, int64_t m, int64_t M, bool on)
 {
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int64_t m = m0 + 64 * i;
-        const int64_t mc = m < M ? m : M - 1;
-        p.a[i] = camp[sl * M + mc];
-        p.g[i] = gamma[mc];
-        if (LEN) p.len[i] = clen[sl * M + mc];
-        if (m >= M) p.a[i] = make_float2(0.0f, 0.0f);
-    }
+    const int64_t mc = m < M ? m : M - 1;
+    p.a[i] = camp[sl * M + mc];
+    p.g[i] = gamma[mc];
+    if (LEN) p.len[i] = clen[sl * M + mc];
+    if (!on || m >= M) p.a[i] = make_float2(0.0f, 0.0f);
 }
 
 // One workgroup per receiver, one wave per slot of its RIS records (element by
@@ -2317,7 +2313,8 @@ __device__ __forceinline__ void cir_load(CirPair& p, const float2* camp, const d
 // by it, 0 for the general division.  Bound by the vector instructions and the
 // kept records (16 bytes each, the amplitudes read twice), the next 128 on their
 // way while 128 are summed: 145000 slots of 127 elements in 400 bins 116 us,
-// 215 with a record and two LDS additions a lane and no loads ahead.
+// 215 with a record and two LDS additions a lane and no loads ahead; slots of
+// 61 elements, two to a wave's step, 78 and 123 us a call, of 37: 73 and 83.
 __global__ __launch_bounds__(CIR_B) void k_cir(const int64_t* env_rstart, const uint8_t* env_valid,
                                                const float2* env_amp, const double* env_len, const int64_t* uptr,
                                                const float2* camp, const double* clen, int64_t M, const float2* gamma,
@@ -2334,17 +2331,25 @@ __global__ __launch_bounds__(CIR_B) void k_cir(const int64_t* env_rstart, const 
     double sa = 0.0;
     for (int64_t j = e0 + tid; j < e1; j += CIR_B)
         if (env_valid[j]) sa += fabs((double)env_amp[j].x) + fabs((double)env_amp[j].y);
-    // a wave's records, 128 elements of a slot at a time, the next ones on their way meanwhile
+    // a wave's records, 128 elements of a slot at a time (up to 64 elements: two of its slots), the next ones on
+    // their way meanwhile
+    constexpr int W = CIR_B / 64;
+    const bool two = M <= 64;
     auto walk = [&](auto with_len, auto use) {
         int64_t sl = s0 + wave, m0 = lane;
         if (sl >= s1 || M <= 0) return;
+        auto load = [&](CirPair& p, int64_t sl_, int64_t m_) {
+            const bool b = two && sl_ + W < s1;
+            cir_load<with_len>(p, 0, camp, clen, gamma, sl_, m_, M, true);
+            cir_load<with_len>(p, 1, camp, clen, gamma, b ? sl_ + W : sl_, two ? m_ : m_ + 64, M, b || !two);
+        };
         CirPair p, q;
-        cir_load<with_len>(p, camp, clen, gamma, sl, m0, M);
+        load(p, sl, m0);
         for (;;) {
             const bool last = m0 - lane + 128 >= M;
-            const int64_t nsl = last ? sl + CIR_B / 64 : sl, nm0 = last ? lane : m0 + 128;
+            const int64_t nsl = last ? sl + (two ? 2 * W : W) : sl, nm0 = last ? lane : m0 + 128;
             const bool more = nsl < s1;
-            if (more) cir_load<with_len>(q, camp, clen, gamma, nsl, nm0, M);
+            if (more) load(q, nsl, nm0);
             use(p);
             if (!more) break;
             p = q;

@@ -968,11 +968,25 @@ __device__ __forceinline__ unsigned legs_blocked_tube(const SceneView& s, bool o
                 }
         } else {
             int nf = 0, cur = 0;
-            for (int j = 0; j <= k; ++j)
-                if (live & (1u << j)) {
-                    if (lane == 0) front[nf] = tube_entry(s.root, j);
-                    ++nf;
-                }
+            // The walk begins with the root's children, untested: the first round would test them with four
+            // lanes a leg, the next one has room for 16 entries whether they passed or not (lab room 880 -> 815
+            // us a launch, a room of 50000 triangles 930 -> 885).  A small scene's root, or one with a leaf
+            // below it, goes first itself.
+            static_assert(4 * (KM + 1) <= 64, "one lane per leg and child of the root");
+            int rref = -1;
+            if (s.n_tri >= 64) rref = __float_as_int(((const float*)(s.node4 + 8 * (int64_t)s.root))[24 + (lane & 3)]);
+            if (__ballot(rref < 0) == 0ull) {
+                const bool in = lane <= 4 * k + 3 && (live >> (lane >> 2) & 1u) && rref != RT_NODE4_EMPTY;
+                const unsigned long long m = __ballot(in);
+                if (in) front[__popcll(m & ((1ull << lane) - 1ull))] = tube_entry(rref, lane >> 2);
+                nf = __popcll(m);
+            } else {
+                for (int j = 0; j <= k; ++j)
+                    if (live & (1u << j)) {
+                        if (lane == 0) front[nf] = tube_entry(s.root, j);
+                        ++nf;
+                    }
+            }
             while (nf > 0) {
                 int nn = 0;
                 int* fin = front + cur * RT_TUBE_FRONT;

@@ -2284,40 +2284,52 @@ __device__ __forceinline__ long long cir_i64(double x)
     return __builtin_bit_cast(long long, v);
 }
 
-// Two records a lane (past the last element or slot: no path).
+// Two records a lane (`on` false: no path).
 struct CirPair {
     float2 a[2], g[2];
     double len[2];
 };
 template <bool LEN>
 __device__ __forceinline__ void cir_load(CirPair& p, int i, const float2* camp, const double* clen, const float2* gamma,
-                                         int64_t sl, int64_t m, int64_t M, bool on)
+                                         int64_t cell, int m, bool on)
 {
-    const int64_t mc = m < M ? m : M - 1;
-    p.a[i] = camp[sl * M + mc];
-    p.g[i] = gamma[mc];
-    if (LEN) p.len[i] = clen[sl * M + mc];
-    if (!on || m >= M) p.a[i] = make_float2(0.0f, 0.0f);
+    p.a[i] = camp[cell];
+    p.g[i] = gamma[m];
+    if (LEN) p.len[i] = clen[cell];
+    if (!on) p.a[i] = make_float2(0.0f, 0.0f);
 }
 
-// One workgroup per receiver, one wave per slot of its RIS records (element by
-// element).  The bins are summed in fixed point: every term is rounded to a
-// multiple of 2^-S, where 2^S scales the receiver's sum of |re| + |im| below
-// 2^61, and added as a 64-bit integer, so the result does not depend on the
-// order of the additions (deterministic) and each term's rounding error is at
-// most 2^-61 of that sum.
+// One workgroup per receiver.  The bins are summed in fixed point: every term
+// is rounded to a multiple of 2^-S, where 2^S scales the receiver's sum of
+// |re| + |im| below 2^61, and added as a 64-bit integer, so the result does not
+// depend on the order of the additions (deterministic) and each term's rounding
+// error is at most 2^-61 of that sum.
 //
-// A slot's elements lie within a few centimetres, so most of a wave's 128
-// records fall into two or three bins: the wave sums them bin by bin and one
-// lane adds to the bin (64 lanes adding to one LDS word take turns).  `inv` is 1 / l_bin where a length over l_bin rounds correctly
-// by it, 0 for the general division.  Bound by the vector instructions and the
-// kept records (16 bytes each, the amplitudes read twice), the next 128 on their
-// way while 128 are summed: 145000 slots of 127 elements in 400 bins 116 us,
-// 215 with a record and two LDS additions a lane and no loads ahead; slots of
-// 61 elements, two to a wave's step, 78 and 123 us a call, of 37: 73 and 83.
+// A receiver's RIS records lie one behind the other, slot by slot and element
+// by element, and its four waves take them 128 at a time: in one run (SLOT
+// false), or a slot a step (88 to 128 elements, or two slots of 49 to 64, where
+// that leaves few lanes empty and keeps the bins of a step few).  Elements of a slot lie within a few
+// centimetres, so in wide bins most of the 128 fall into two or three: the wave
+// sums up to ROUNDS bins one by one and one lane adds to each (64 lanes adding
+// to one LDS word take turns); narrow bins and slots of few elements have the
+// lanes add (ROUNDS 0).  `inv` is 1 / l_bin where a length over l_bin rounds
+// correctly by it, 0 for the general division.  Bound by the vector
+// instructions and the kept records (16 bytes each, the amplitudes read
+// twice), the next 128 on their way while 128 are summed.  Measured in turn
+// with a wave a slot throughout, and with a record and two additions a lane in
+// one run without loads ahead, us a call:
+//   35 slots of 127 elements at 4096 receivers, 400 bins of 0.25 ns  113 | 117 | 225
+//   1600 receivers, 400 bins of 0.25 ns: 24 elements                  30 |  39 |  31
+//     61 elements                                                     38 |  43 |  52
+//     271 elements                                                   107 | 137 | 165
+//   1000 bins of 0.1 ns: 24 elements                                  30 |  44 |  34
+//     1027 elements                                                  369 | 520 | 673
+//   one slot a receiver: 64 receivers x 3997 elements, 0.25 ns        32 |  78 |  32
+//     4096 x 1027 elements, 3000 bins of 0.1 ns                       77 | 167 | 100
+template <bool SLOT, int ROUNDS>
 __global__ __launch_bounds__(CIR_B) void k_cir(const int64_t* env_rstart, const uint8_t* env_valid,
                                                const float2* env_amp, const double* env_len, const int64_t* uptr,
-                                               const float2* camp, const double* clen, int64_t M, const float2* gamma,
+                                               const float2* camp, const double* clen, int64_t M_, const float2* gamma,
                                                double l_bin, double inv, int64_t n_bins, int gper, float2* cir)
 {
     extern __shared__ unsigned long long acc[];   // 2 gper
@@ -2331,30 +2343,44 @@ __global__ __launch_bounds__(CIR_B) void k_cir(const int64_t* env_rstart, const 
     double sa = 0.0;
     for (int64_t j = e0 + tid; j < e1; j += CIR_B)
         if (env_valid[j]) sa += fabs((double)env_amp[j].x) + fabs((double)env_amp[j].y);
-    // a wave's records, 128 elements of a slot at a time (up to 64 elements: two of its slots), the next ones on
-    // their way meanwhile
+    // a wave's records, 128 at a time, the next ones on their way meanwhile
     constexpr int W = CIR_B / 64;
-    const bool two = M <= 64;
     auto walk = [&](auto with_len, auto use) {
-        int64_t sl = s0 + wave, m0 = lane;
-        if (sl >= s1 || M <= 0) return;
-        auto load = [&](CirPair& p, int64_t sl_, int64_t m_) {
-            const bool b = two && sl_ + W < s1;
-            cir_load<with_len>(p, 0, camp, clen, gamma, sl_, m_, M, true);
-            cir_load<with_len>(p, 1, camp, clen, gamma, b ? sl_ + W : sl_, two ? m_ : m_ + 64, M, b || !two);
+        const int M = (int)M_;
+        if (M <= 0 || s0 >= s1) return;
+        // the lane's records: c and c + 64 of the receiver's n, m the element of the first (SLOT: elements m and
+        // m + 64 of slot sl, or element m of slots sl and sl + W)
+        const int64_t first = s0 * M, n = (s1 - s0) * M;
+        int64_t c = wave * 128 + lane, sl = s0 + wave;
+        int m = SLOT ? lane : (wave * 128 + lane) % M;
+        const int half = SLOT ? 0 : 64 % M, step = SLOT ? 0 : W * 128 % M;
+        const bool two = M <= 64;
+        auto more = [&]() { return SLOT ? sl < s1 : c - lane < n; };
+        auto load = [&](CirPair& p) {
+            if (SLOT) {
+                const bool in = two ? sl + W < s1 && m < M : m + 64 < M;
+                const int m0 = m < M ? m : M - 1, m1 = two ? m0 : in ? m + 64 : M - 1;
+                cir_load<with_len>(p, 0, camp, clen, gamma, sl * M + m0, m0, m < M);
+                cir_load<with_len>(p, 1, camp, clen, gamma, (two && in ? sl + W : sl) * M + m1, m1, in);
+                sl += two ? 2 * W : W;
+            } else {
+                const int m1 = m + half - (m + half >= M ? M : 0);
+                cir_load<with_len>(p, 0, camp, clen, gamma, first + (c < n ? c : n - 1), m, c < n);
+                cir_load<with_len>(p, 1, camp, clen, gamma, first + (c + 64 < n ? c + 64 : n - 1), m1, c + 64 < n);
+                c += W * 128;
+                m += step;
+                m -= m >= M ? M : 0;
+            }
         };
+        if (!more()) return;
         CirPair p, q;
-        load(p, sl, m0);
+        load(p);
         for (;;) {
-            const bool last = m0 - lane + 128 >= M;
-            const int64_t nsl = last ? sl + (two ? 2 * W : W) : sl, nm0 = last ? lane : m0 + 128;
-            const bool more = nsl < s1;
-            if (more) load(q, nsl, nm0);
+            const bool go = more();
+            if (go) load(q);
             use(p);
-            if (!more) break;
+            if (!go) break;
             p = q;
-            sl = nsl;
-            m0 = nm0;
         }
     };
     walk(std::false_type{}, [&](const CirPair& p) {
@@ -2405,7 +2431,7 @@ __global__ __launch_bounds__(CIR_B) void k_cir(const int64_t* env_rstart, const 
                 im[i] = cir_i64(rint(ai * scale));
             }
             // the bins of the wave one by one, then lane by lane if there are many
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < ROUNDS; ++k) {
                 const int any = bin[0] >= 0 ? bin[0] : bin[1];
                 const unsigned long long act = __ballot(any >= 0);
                 if (!act) return;
@@ -2440,14 +2466,26 @@ void cir(Ctx& c, const Channel& ch, const float* gamma, double bin_s, int64_t n_
     uint64_t u;
     std::memcpy(&u, &l_bin, sizeof u);
     const bool by_inv = l_bin > 1e-100 && l_bin < 1e100 && (~u & 0xFFFFFFFFFFFFFull) != 0;
-    // the bins in passes of equal size, LDS for one pass
-    const int64_t passes = (n_bins + CIR_G - 1) / CIR_G;
+    // The bins in passes of equal size, LDS for one pass: of 3072 where a receiver has many records to walk again or
+    // the receivers are too few to fill the chip, of 2048 (a third more workgroups a compute unit) elsewhere (4096
+    // receivers of one slot, 3000 bins: 50 for 59 us; 1600 of 36 x 512 records: 290 for 233).
+    const int64_t records = ris ? ch.n_slots * ch.M / ch.R : 0;
+    const int64_t most = ch.R >= 1024 && records < 4000 ? 2048 : CIR_G;
+    const int64_t passes = (n_bins + most - 1) / most;
     const int gper = (int)((n_bins + passes - 1) / passes);
-    hipLaunchKernelGGL(k_cir, dim3((unsigned)ch.R), dim3(CIR_B), sizeof(unsigned long long) * 2 * (size_t)gper, st,
-                       ch.env_cells > 0 ? ch.env_rstart.as<int64_t>() : nullptr, ch.env_valid.as<uint8_t>(),
-                       ch.env_amp.as<float2>(), ch.env_len.as<double>(), ris ? ch.cir_uptr.as<int64_t>() : nullptr,
-                       ch.cir_amp.as<float2>(), ch.cir_len.as<double>(), ris ? ch.M : 0, (const float2*)gamma, l_bin,
-                       by_inv ? 1.0 / l_bin : 0.0, n_bins, gper, (float2*)out);
+    auto run = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)ch.R), dim3(CIR_B), sizeof(unsigned long long) * 2 * (size_t)gper, st,
+                           ch.env_cells > 0 ? ch.env_rstart.as<int64_t>() : nullptr, ch.env_valid.as<uint8_t>(),
+                           ch.env_amp.as<float2>(), ch.env_len.as<double>(), ris ? ch.cir_uptr.as<int64_t>() : nullptr,
+                           ch.cir_amp.as<float2>(), ch.cir_len.as<double>(), ris ? ch.M : 0, (const float2*)gamma, l_bin,
+                           by_inv ? 1.0 / l_bin : 0.0, n_bins, gper, (float2*)out);
+    };
+    if (l_bin < 0.05 || ch.M <= 48)
+        run(k_cir<false, 0>);
+    else if (ch.M <= 64 || (ch.M >= 88 && ch.M <= 128))
+        run(k_cir<true, 4>);
+    else
+        run(k_cir<false, 4>);
     HIP_CHECK(hipGetLastError());
 }
 

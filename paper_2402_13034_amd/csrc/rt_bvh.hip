@@ -27,9 +27,9 @@
 // Layouts (leaf slot = rank of the triangle by surface, then Morton code):
 //   tri4  [3 * n]: (v0.xyz, id), (e1.xyz, surface), (e2.xyz, 0)
 //   nodes [4 * ..]: (loL.xyz, childL), (hiL.xyz, childR), (loR.xyz, -), (hiR.xyz, -)
-//   child >= 0: internal node; child < 0: leaf slot ~child.  Nodes 0..n-2 are
-//   Karras nodes over the slots (those that span several surfaces are not
-//   reached), n-1.. the nodes above the surfaces.
+//   child >= 0: internal node; child < 0: leaf slot ~child.  Node indices are
+//   those of the Karras nodes over the slots; the nodes above the surfaces take
+//   the indices of the Karras nodes that span several surfaces.
 // Surfaces: s_tris groups triangle indices by surface (ascending), s_ptr the
 // CSR offsets, s_plane the plane of each surface's lowest-numbered triangle.
 #pragma clang fp contract(off)
@@ -65,7 +65,7 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v)
     return v;
 }
 
-// FP64 vertices and their 2-D projection, reflection coefficients, surface
+// Vertices per triangle, edge functions, reflection coefficients, surface
 // ids and sort keys (surface above triangle), centroids; bounds of the
 // centroids and of the vertices (order-preserving unsigned keys) and the
 // largest surface id.  Every block ends in 13 atomics on the same few words,
@@ -75,9 +75,9 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v)
 constexpr int PREP_B = 256, PREP_BLOCKS = 512;
 __global__ __launch_bounds__(PREP_B) void k_scene_prep(const float* V, const int32_t* T, const int32_t* surf_in,
                                                        const float* rr, const float* ri, int64_t nv, int64_t nt,
-                                                       double* v64, float2* refl, int32_t* surf, float4* cent,
+                                                       float* verts, float2* refl, int32_t* surf, float4* cent,
                                                        uint64_t* skeys, unsigned* bounds, int32_t* bad,
-                                                       int32_t* n_surf, double* proj, int32_t* axes, double* edge)
+                                                       int32_t* n_surf, double* edge)
 {
     __shared__ unsigned red[PREP_B / 64][13];
     unsigned mn[6], mx[6];   // minima and maxima of the centroids (0..2) and the vertices (3..5)
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(PREP_B) void k_scene_prep(const float* V, const int
                 const float x = V[3 * (int64_t)vi + k];
                 if (!(x == x) || fabsf(x) > 1e6f) flags |= 2u;
                 w[3 * j + k] = (double)x;
-                v64[9 * t + 3 * j + k] = (double)x;
+                verts[9 * t + 3 * j + k] = x;
                 c[k] += x;
                 const unsigned u = f2ord(x);
                 mn[3 + k] = min(mn[3 + k], u);
@@ -109,8 +109,6 @@ __global__ __launch_bounds__(PREP_B) void k_scene_prep(const float* V, const int
         double q6[6];
         int32_t ax;
         triangle_projection(w, q6, &ax);
-        for (int k = 0; k < 6; ++k) proj[6 * t + k] = q6[k];
-        axes[t] = ax;
         triangle_edges(q6, ax, edge + RT_EDGE * t);
         refl[t] = make_float2(rr[t], ri[t]);
         const int32_t sf = surf_in[t];
@@ -449,8 +447,12 @@ __global__ __launch_bounds__(256) void k_refit_cross(const int32_t* cross, const
 // workgroup, large ones by all its waves together: up to TOP_LEAF surfaces to
 // the end, beyond until they hold at most TOP_LEAF, and those go one workgroup
 // each over the device: 106 surfaces 67 us, 1566 surfaces 175 + 116 us.
-// A range split before position m makes node base + m - 1 (every position
-// splits once), so the numbering needs no counter.
+// Of the n Karras indices 0..n-1 over the slots (n - 1 is no node), a surface's
+// c triangles hold c, its subtree takes c - 1 of them and leaves one end free:
+// the index of a Karras node over several surfaces (the last surface leaves
+// n - 1).  A range split before position m takes the one that surface m - 1
+// left (every position splits once), so the numbering needs neither a counter
+// nor room of its own.
 // --------------------------------------------------------------------------
 constexpr int TOP_BINS = 11, TOP_LEAF = 256, TOP_T = 1024, TOP_RES = 2048, TOP_FT = 512;
 constexpr int TOP_Q = TOP_LEAF / 2;   // ranges of a level: of two surfaces and more, or of more than TOP_LEAF
@@ -461,7 +463,7 @@ struct TopOut {
     int32_t* child;
     int32_t* parent_int;
     int32_t* root;
-    int64_t base;      // node index of split position 1
+    const int32_t* ids;   // node index of split position 1, 2, ...
 };
 
 // child `ref` of side `side` of node `parent` (-1: the root)
@@ -600,7 +602,7 @@ __device__ __forceinline__ void top_price(const TopBoxes sb, const uint16_t* idx
 __device__ __forceinline__ void top_node(const TopOut& o, int m, int parent, int side, const float* l, const float* r)
 {
     if ((threadIdx.x & 63) != 0) return;
-    const int id = (int)(o.base + m - 1);
+    const int id = o.ids[m - 1];
     float* nd = (float*)(o.nodes + 4 * (int64_t)id);   // the .w words are links
     for (int k = 0; k < 3; ++k) {
         nd[k] = l[k];
@@ -621,7 +623,7 @@ __device__ __forceinline__ void top_pair(const TopBoxes sb, const uint16_t* idx,
     const float l[6] = {l0.x, l0.y, l0.z, h0.x, h0.y, h0.z}, r[6] = {l1.x, l1.y, l1.z, h1.x, h1.y, h1.z};
     top_node(o, a + 1, parent, side, l, r);
     if ((threadIdx.x & 63) == 0) {
-        const int id = (int)(o.base + a);
+        const int id = o.ids[a];
         top_link(o, id, 0, __float_as_int(h0.w));
         top_link(o, id, 1, __float_as_int(h1.w));
     }
@@ -701,6 +703,7 @@ template <int CAP, int RES, int T, int Q>
 struct TopShared {
     static constexpr int NW = T / 64;
     uint16_t idx[CAP], tmp[CAP];
+    int32_t ids[RES];
     float4 box[2 * RES];
     TopAcc part[NW][32];
     float ext[NW][6];
@@ -771,7 +774,7 @@ __device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n,
             if (!together || wave == 0) {
                 const int m = top_split(sb, sh.idx, sh.tmp, it.x, it.y, it.z, it.w, c, acc, o);
                 if (lane == 0) {
-                    const int id = (int)(o.base + m - 1);
+                    const int id = o.ids[m - 1];
                     hand_on(it.x, m, id, 0, cur ^ 1);
                     hand_on(m, it.y, id, 1, cur ^ 1);
                 }
@@ -789,8 +792,8 @@ __device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n,
 // parent, side) and the surfaces' order to order_out.
 __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const int32_t* n_surf_p,
                                                      const int32_t* seen_p, const int2* range, const float* lbox,
-                                                     float4* sb, int32_t* order_out, int4* fin, int32_t* n_fin,
-                                                     TopOut o)
+                                                     float4* sb, int32_t* ids, int32_t* order_out, int4* fin,
+                                                     int32_t* n_fin, TopOut o)
 {
     __shared__ TopShared<RT_TOP_MAX, TOP_RES, TOP_T, TOP_Q> sh;
     const int n = *n_surf_p;
@@ -801,7 +804,7 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
         // the surface's leaves are slots a..b-1; its subtree's node has index a or b - 1
         const int a = s_ptr[s], b = s_ptr[s + 1];
         float4 lo, hi;
-        int ref;
+        int ref, free = a;
         if (b - a == 1) {
             ref = ~a;
             const float* x = lbox + 6 * (int64_t)a;
@@ -810,6 +813,7 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
         } else {
             const int2 ra = range[a];
             ref = ra.x == a && ra.y == b - 1 ? a : b - 1;
+            free = ref == a ? b - 1 : a;
             const float4* nd = o.nodes + 4 * (int64_t)ref;
             const float4 l0 = nd[0], l1 = nd[1], r0 = nd[2], r1 = nd[3];
             lo = make_float4(fminf(l0.x, r0.x), fminf(l0.y, r0.y), fminf(l0.z, r0.z), (float)(b - a));
@@ -819,8 +823,10 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
         if (leaf > 1) {
             sb[2 * s] = lo;
             sb[2 * s + 1] = hi;
+            ids[s] = free;
         }
         if (resident) {
+            sh.ids[s] = free;
             sh.box[2 * s] = lo;
             sh.box[2 * s + 1] = hi;
         }
@@ -833,6 +839,7 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
         sh.queue[0][0] = make_int4(0, n, -1, 0);
     }
     __syncthreads();
+    o.ids = resident ? sh.ids : ids;
     if (resident)
         top_levels(sh, TopBoxes{sh.box}, n, leaf, fin, o);
     else
@@ -844,8 +851,8 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
 
 // Lower levels: one workgroup per range of at most TOP_LEAF surfaces, split to the end.
 __global__ __launch_bounds__(TOP_FT) void k_top_finish(const int32_t* n_surf_p, const int32_t* seen_p,
-                                                       const float4* sb, const int32_t* order, const int4* fin,
-                                                       const int32_t* n_fin, TopOut o)
+                                                       const float4* sb, const int32_t* ids, const int32_t* order,
+                                                       const int4* fin, const int32_t* n_fin, TopOut o)
 {
     __shared__ TopShared<TOP_LEAF, TOP_LEAF, TOP_FT, TOP_Q> sh;
     if (!top_used(*n_surf_p, *seen_p, 0) || (int)blockIdx.x >= *n_fin) return;   // the same for every thread
@@ -854,6 +861,7 @@ __global__ __launch_bounds__(TOP_FT) void k_top_finish(const int32_t* n_surf_p, 
     if ((int)threadIdx.x < cnt) {
         const int s = order[a0 + threadIdx.x];
         sh.idx[threadIdx.x] = (uint16_t)threadIdx.x;
+        sh.ids[threadIdx.x] = ids[a0 + threadIdx.x];   // positions within the range
         sh.box[2 * threadIdx.x] = sb[2 * s];
         sh.box[2 * threadIdx.x + 1] = sb[2 * s + 1];
     }
@@ -863,12 +871,11 @@ __global__ __launch_bounds__(TOP_FT) void k_top_finish(const int32_t* n_surf_p, 
         sh.queue[0][0] = make_int4(0, cnt, root.z, root.w);
     }
     __syncthreads();
-    TopOut here = o;
-    here.base = o.base + a0;   // positions within the range; node indices take the range's start again
-    top_levels(sh, TopBoxes{sh.box}, cnt, 1, nullptr, here);
+    o.ids = sh.ids;
+    top_levels(sh, TopBoxes{sh.box}, cnt, 1, nullptr, o);
 }
 
-// 4-wide nodes: every reached internal node of even depth lists its
+// 4-wide nodes: every internal node of even depth lists its
 // grandchildren (a leaf child stands for itself).  Boxes are copied from the
 // binary nodes.  Also the tree depth: the deepest leaf lies one below the
 // deepest internal node (a broken parent chain gives 2^20).
@@ -881,26 +888,15 @@ struct MortonTree {
     int32_t* maxd;
 };
 __global__ void k_node4(const int32_t* child, const int32_t* parent_int, const float4* nodes, const float4* tri4,
-                        const uint64_t* slot_keys, const int2* range, const int32_t* n_surf_p, const int32_t* seen_p,
-                        int plain, int64_t ni, int64_t ni_all, float4* node4, int32_t* maxd, MortonTree mt)
+                        int64_t ni, float4* node4, int32_t* maxd, MortonTree mt)
 {
     const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool second = blockIdx.y != 0;
     const int32_t* up = second ? mt.parent_int : parent_int;
-    bool live = n < ni;
-    if (!second && top_used(*n_surf_p, *seen_p, plain)) {
-        if (live) {   // a node over several surfaces is replaced by the tree above them
-            const int2 r = range[n];
-            live = slot_keys[2 * (int64_t)r.x + 1] >> RT_KEY_SURF_SHIFT ==
-                   slot_keys[2 * (int64_t)r.y + 1] >> RT_KEY_SURF_SHIFT;
-        } else {
-            live = n < ni + *n_surf_p - 1;
-        }
-    }
-    const int64_t lim = second ? ni : ni_all;
+    const bool live = n < ni;
     int d = 0;
     int32_t p = live ? up[n] : -1;
-    for (; p >= 0 && p < lim && d < 4096; p = up[p]) ++d;
+    for (; p >= 0 && p < ni && d < 4096; p = up[p]) ++d;
     const unsigned dl = !live ? 0u : (p != -1 ? (1u << 20) : (unsigned)d + 1u);
     const unsigned dm = wave_umax(dl);
     if ((threadIdx.x & 63) == 0 && dm > 0) atomicMax(second ? mt.maxd : maxd, (int32_t)dm);
@@ -987,7 +983,7 @@ __global__ void k_surf_csr(const uint64_t* keys, int64_t nt, const int32_t* n_su
 // projected box, grown by a margin that covers the rounding of the FP64 edge
 // tests (relative to the coordinates and inversely to the shortest edge),
 // overlaps.  Lists keep the surface's triangle order.  At least as many cells
-// as triangles (4 x 4 to 32 x 32), halved per axis until the lists fit their
+// as triangles (2 x 2 to 32 x 32), halved per axis until the lists fit their
 // part of g_tris: with 4 x 4 cells for every surface, a point on an office's
 // floor tile of 800 triangles met some 36 of them one behind the other, 19 of
 // the 46 ms of its per-element kernel (31 ms so; geometry of the two sources
@@ -1006,9 +1002,8 @@ __device__ __forceinline__ double wave_dmax(double v)
     return v;
 }
 
-__global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const int32_t* s_tris, const double* v64,
-                                                     const double* t_proj, const int32_t* t_axes,
-                                                     const int32_t* n_surf_p, double* s_plane, double* s_box,
+__global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const int32_t* s_tris, const float* verts,
+                                                     const double* t_edge, const int32_t* n_surf_p, double* s_plane, double* s_box,
                                                      int32_t* g_axes, double* g_frame, int32_t* g_off,
                                                      int32_t* g_tris, int32_t* bad)
 {
@@ -1028,11 +1023,12 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
             if (lane == 0) g_axes[s] = -1;
             continue;
         }
-        const double* v = v64 + 9 * (int64_t)s_tris[b];
-        double e1[3], e2[3];
+        const float* first = verts + 9 * (int64_t)s_tris[b];
+        double v[3], e1[3], e2[3];
         for (int k = 0; k < 3; ++k) {
-            e1[k] = v[3 + k] - v[k];
-            e2[k] = v[6 + k] - v[k];
+            v[k] = first[k];
+            e1[k] = (double)first[3 + k] - v[k];
+            e2[k] = (double)first[6 + k] - v[k];
         }
         const double n0 = e1[1] * e2[2] - e1[2] * e2[1];
         const double n1 = e1[2] * e2[0] - e1[0] * e2[2];
@@ -1045,16 +1041,17 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
         int amin = 16, amax = -1;   // smallest and largest projection of the non-degenerate triangles
         for (int j = b + lane; j < e; j += 64) {
             const int t = s_tris[j];
-            const double* w = v64 + 9 * (int64_t)t;
+            const float* p = verts + 9 * (int64_t)t;
             for (int a = 0; a < 3; ++a) {
+                const double w[3] = {p[3 * a], p[3 * a + 1], p[3 * a + 2]};
                 for (int k = 0; k < 3; ++k) {
-                    lo[k] = fmin(lo[k], w[3 * a + k]);
-                    hi[k] = fmax(hi[k], w[3 * a + k]);
+                    lo[k] = fmin(lo[k], w[k]);
+                    hi[k] = fmax(hi[k], w[k]);
                 }
-                const double dist = n0 * w[3 * a] + n1 * w[3 * a + 1] + n2 * w[3 * a + 2] - dpl;
+                const double dist = n0 * w[0] + n1 * w[1] + n2 * w[2] - dpl;
                 off_plane |= !(fabs(dist) <= tol);
             }
-            const int ax = t_axes[t];
+            const int ax = edge_axes(t_edge, t);
             if (!(ax & 16)) {
                 amin = min(amin, ax);
                 amax = max(amax, ax);
@@ -1101,9 +1098,10 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
             t = -1;
             if (j >= e) return 0u;
             const int tj = s_tris[j];
-            if (t_axes[tj] & 16) return 0u;   // a degenerate triangle contains nothing
+            if (edge_axes(t_edge, tj) & 16) return 0u;   // a degenerate triangle contains nothing
             t = tj;
-            const double* q = t_proj + 6 * (int64_t)t;
+            const float* p = verts + 9 * (int64_t)t;
+            const double q[6] = {p[i0], p[i1], p[3 + i0], p[3 + i1], p[6 + i0], p[6 + i1]};
             const double umin = fmin(q[0], fmin(q[2], q[4])), umax = fmax(q[0], fmax(q[2], q[4]));
             const double vmin = fmin(q[1], fmin(q[3], q[5])), vmax = fmax(q[1], fmax(q[3], q[5]));
             const double C = fmax(fmax(fabs(umin), fabs(umax)), fmax(fabs(vmin), fabs(vmax)));
@@ -1158,7 +1156,7 @@ __global__ __launch_bounds__(256) void k_surf_tables(const int32_t* s_ptr, const
             f[3] = pv;
         }
         // counts to first places
-        int32_t* off = g_off + (int64_t)RT_SGRID_CAP * b + s;
+        int32_t* off = g_off + (int64_t)RT_SGRID_OFF * b + s;
         int32_t* list = g_tris + (int64_t)RT_SGRID_CAP * b;
         int run = 0;
         for (int c = lane; c < ((nc + 63) & ~63); c += 64) {   // every lane the same number of times
@@ -1214,11 +1212,12 @@ __global__ void k_ctl_init(unsigned* ctl)
 }
 
 // unit normal of e1 x e2 per triangle (0 for a degenerate triangle)
-__global__ void k_unit_normals(const double* v64, int64_t nt, double* nrm)
+__global__ void k_unit_normals(const float* verts, int64_t nt, double* nrm)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= nt) return;
-    const double* v = v64 + 9 * t;
+    double v[9];
+    for (int k = 0; k < 9; ++k) v[k] = verts[9 * t + k];
     const double ex = v[3] - v[0], ey = v[4] - v[1], ez = v[5] - v[2];
     const double fx = v[6] - v[0], fy = v[7] - v[1], fz = v[8] - v[2];
     const double nx = ey * fz - ez * fy, ny = ez * fx - ex * fz, nz = ex * fy - ey * fx;
@@ -1233,7 +1232,7 @@ void scene_normals(Ctx& c, Scene& s, hipStream_t st)
 {
     if (s.n_tri == 0 || s.nrm.bytes) return;
     s.nrm = Scratch(c, sizeof(double) * 3 * (size_t)s.n_tri, st);
-    hipLaunchKernelGGL(k_unit_normals, dim3(blocks_for(s.n_tri, 256)), dim3(256), 0, st, s.v64.as<double>(), s.n_tri,
+    hipLaunchKernelGGL(k_unit_normals, dim3(blocks_for(s.n_tri, 256)), dim3(256), 0, st, s.verts.as<float>(), s.n_tri,
                        s.nrm.as<double>());
     HIP_CHECK(hipGetLastError());
 }
@@ -1326,9 +1325,7 @@ void lbvh_nodes(Ctx& c, const Scene& s, Scratch& nodes, hipStream_t st)
         flags(c, sizeof(int32_t) * (size_t)ni, st);
     hipLaunchKernelGGL(k_zero_i32, dim3(blocks_for(ni, B)), dim3(B), 0, st, flags.as<int32_t>(), ni);
     HIP_CHECK(hipGetLastError());
-    // every leaf is an entry of a node below the surfaces' roots, or of one above them
-    const int64_t n_nodes = ni + (s.root >= ni ? s.n_surf - 1 : 0);
-    hipLaunchKernelGGL(k_leaf_boxes, dim3(blocks_for(n_nodes, B)), dim3(B), 0, st, s.nodes.as<float4>(), n_nodes, nt,
+    hipLaunchKernelGGL(k_leaf_boxes, dim3(blocks_for(ni, B)), dim3(B), 0, st, s.nodes.as<float4>(), ni, nt,
                        lbox.as<float>());
     HIP_CHECK(hipGetLastError());
     hipLaunchKernelGGL(k_parents, dim3(blocks_for(ni, B)), dim3(B), 0, st, s.lbvh_child.as<int32_t>(), ni,
@@ -1351,8 +1348,6 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
         return;
     }
     if (nt >= (int64_t)1 << 29) throw inval_error("too many triangles (at most 2^29 - 1)");
-    // node indices stay below 2^29 with the tree above the surfaces too
-    if (nt + RT_TOP_MAX >= (int64_t)1 << 29) plain = true;
     // inputs in device memory are read in place (the build is complete before the call returns);
     // host arrays are staged
     Scratch stage_buf[5];
@@ -1368,9 +1363,8 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     const float* dR = (const float*)input(rr, sizeof(float) * (size_t)nt, 3);
     const float* dI = (const float*)input(ri, sizeof(float) * (size_t)nt, 4);
 
-    s.v64 = Scratch(c, sizeof(double) * 9 * (size_t)nt, st);
+    s.verts = Scratch(c, sizeof(float) * 9 * (size_t)nt, st);
     s.t_edge = Scratch(c, sizeof(double) * RT_EDGE * (size_t)nt, st);
-    Scratch t_proj(c, sizeof(double) * 6 * (size_t)nt, st), t_axes(c, sizeof(int32_t) * (size_t)nt, st);
     s.refl = Scratch(c, sizeof(float2) * (size_t)nt, st);
     s.surf = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
     s.tri4 = Scratch(c, sizeof(float4) * 3 * (size_t)nt, st);
@@ -1392,9 +1386,8 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     const int B = 256;
     Scratch skeys(c, sizeof(uint64_t) * (size_t)nt, st);
     hipLaunchKernelGGL(k_scene_prep, dim3(std::min<unsigned>(blocks_for(nt, PREP_B), PREP_BLOCKS)), dim3(PREP_B), 0, st,
-                       dV, dT, dS, dR, dI, nv, nt, s.v64.as<double>(), s.refl.as<float2>(), s.surf.as<int32_t>(),
-                       cent.as<float4>(), skeys.as<uint64_t>(), bounds, bad, nsurf, t_proj.as<double>(),
-                       t_axes.as<int32_t>(), s.t_edge.as<double>());
+                       dV, dT, dS, dR, dI, nv, nt, s.verts.as<float>(), s.refl.as<float2>(), s.surf.as<int32_t>(),
+                       cent.as<float4>(), skeys.as<uint64_t>(), bounds, bad, nsurf, s.t_edge.as<double>());
     HIP_CHECK(hipGetLastError());
     s.box = Scratch(c, 6 * sizeof(float), st);
     Scratch keys_raw(c, 2 * sizeof(uint64_t) * (size_t)nt, st), keys(c, 2 * sizeof(uint64_t) * (size_t)nt, st);
@@ -1435,11 +1428,10 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
 
     if (nt >= 2) {
         const int64_t ni = nt - 1;
-        const int64_t ni_all = ni + (plain ? 0 : std::min<int64_t>(nt, RT_TOP_MAX) - 1);
-        s.nodes = Scratch(c, sizeof(float4) * 4 * (size_t)ni_all, st);
+        s.nodes = Scratch(c, sizeof(float4) * 4 * (size_t)ni, st);
         s.lbvh_child = Scratch(c, sizeof(int32_t) * 2 * (size_t)ni, st);
         const int64_t n_tiles = (nt + RT_REFIT_TILE - 1) / RT_REFIT_TILE;
-        Scratch child(c, sizeof(int32_t) * 2 * (size_t)ni_all, st), pint(c, sizeof(int32_t) * (size_t)ni_all, st),
+        Scratch child(c, sizeof(int32_t) * 2 * (size_t)ni, st), pint(c, sizeof(int32_t) * (size_t)ni, st),
             pleaf(c, sizeof(int32_t) * (size_t)nt, st), range(c, sizeof(int2) * (size_t)ni, st),
             cross(c, sizeof(int32_t) * (size_t)(n_tiles > 1 ? ni : 1), st),
             tbox(c, sizeof(float) * 6 * (size_t)n_tiles, st), mpint(c, sizeof(int32_t) * (size_t)ni, st);
@@ -1460,34 +1452,35 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
         }
         if (!plain) {
             const int64_t ns = std::min<int64_t>(nt, RT_TOP_MAX);
-            Scratch sb(c, sizeof(float4) * 2 * (size_t)ns, st), order(c, sizeof(int32_t) * (size_t)ns, st),
-                fin(c, sizeof(int4) * (size_t)ns, st);
-            const TopOut to{s.nodes.as<float4>(), child.as<int32_t>(), pint.as<int32_t>(), troot, ni};
+            Scratch sb(c, sizeof(float4) * 2 * (size_t)ns, st), ids(c, sizeof(int32_t) * (size_t)ns, st),
+                order(c, sizeof(int32_t) * (size_t)ns, st), fin(c, sizeof(int4) * (size_t)ns, st);
+            const TopOut to{s.nodes.as<float4>(), child.as<int32_t>(), pint.as<int32_t>(), troot, nullptr};
             hipLaunchKernelGGL(k_top_split, dim3(1), dim3(TOP_T), 0, st, s.s_ptr.as<int32_t>(), nsurf, seen,
-                               range.as<int2>(), lbox.as<float>(), sb.as<float4>(), order.as<int32_t>(),
-                               fin.as<int4>(), nfin, to);
-            HIP_CHECK(hipGetLastError());
-            hipLaunchKernelGGL(k_top_finish, dim3((unsigned)std::max<int64_t>(1, ns / 2)), dim3(TOP_FT), 0, st, nsurf, seen,
-                               sb.as<float4>(),
+                               range.as<int2>(), lbox.as<float>(), sb.as<float4>(), ids.as<int32_t>(),
                                order.as<int32_t>(), fin.as<int4>(), nfin, to);
             HIP_CHECK(hipGetLastError());
+            hipLaunchKernelGGL(k_top_finish, dim3((unsigned)std::max<int64_t>(1, ns / 2)), dim3(TOP_FT), 0, st, nsurf, seen,
+                               sb.as<float4>(), ids.as<int32_t>(), order.as<int32_t>(), fin.as<int4>(), nfin, to);
+            HIP_CHECK(hipGetLastError());
         }
-        s.node4 = Scratch(c, sizeof(float4) * 8 * (size_t)ni_all, st);
+        s.node4 = Scratch(c, sizeof(float4) * 8 * (size_t)ni, st);
         const MortonTree mt{keys.as<uint64_t>(), mpint.as<int32_t>(), tslot.as<int32_t>(), s.lbvh_child.as<int32_t>(),
                             maxd};
-        hipLaunchKernelGGL(k_node4, dim3(blocks_for(ni_all, B), 2), dim3(B), 0, st, child.as<int32_t>(),
-                           pint.as<int32_t>(), s.nodes.as<float4>(), s.tri4.as<float4>(), slots.as<uint64_t>(),
-                           range.as<int2>(), nsurf, seen, plain ? 1 : 0, ni, ni_all, s.node4.as<float4>(), wmaxd, mt);
+        hipLaunchKernelGGL(k_node4, dim3(blocks_for(ni, B), 2), dim3(B), 0, st, child.as<int32_t>(),
+                           pint.as<int32_t>(), s.nodes.as<float4>(), s.tri4.as<float4>(), ni,
+                           s.node4.as<float4>(), wmaxd, mt);
         HIP_CHECK(hipGetLastError());
     }
+    // the tree's scratch goes back before the tables below are allocated
+    for (Scratch* p : {&cent, &keys_raw, &keys, &skeys, &slots, &tslot, &lbox}) p->release();
 
     s.g_axes = Scratch(c, sizeof(int32_t) * (size_t)nt, st);
     s.g_frame = Scratch(c, sizeof(double) * 4 * (size_t)nt, st);
-    s.g_off = Scratch(c, sizeof(int32_t) * (RT_SGRID_CAP + 1) * (size_t)nt, st);   // n_surf <= nt
+    s.g_off = Scratch(c, sizeof(int32_t) * (RT_SGRID_OFF + 1) * (size_t)nt, st);   // n_surf <= nt
     s.g_tris = Scratch(c, sizeof(int32_t) * RT_SGRID_CAP * (size_t)nt, st);
     hipLaunchKernelGGL(k_surf_tables, dim3(std::min<unsigned>(blocks_for(nt, 4), 2048)), dim3(256), 0, st,
-                       s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), s.v64.as<double>(), t_proj.as<double>(),
-                       t_axes.as<int32_t>(), nsurf, s.s_plane.as<double>(), s.s_box.as<double>(),
+                       s.s_ptr.as<int32_t>(), s.s_tris.as<int32_t>(), s.verts.as<float>(), s.t_edge.as<double>(),
+                       nsurf, s.s_plane.as<double>(), s.s_box.as<double>(),
                        s.g_axes.as<int32_t>(), s.g_frame.as<double>(), s.g_off.as<int32_t>(),
                        s.g_tris.as<int32_t>(), bad);
     HIP_CHECK(hipGetLastError());
@@ -1513,7 +1506,7 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     const bool top = !plain && n_surf >= 2 && n_surf <= RT_TOP_MAX;
     s.walk_depth = wdepth;
     s.root = nt < 2 ? ~0 : top ? (int32_t)(hq[3] & 0xffffffff) : 0;
-    if (top && (s.root < nt - 1 || s.root >= nt - 1 + n_surf - 1 || wdepth >= (1 << 20)))
+    if (top && (s.root < 0 || s.root >= nt - 1 || wdepth >= (1 << 20)))
         throw hip_error("BVH build produced an inconsistent tree");
 }
 

@@ -389,7 +389,7 @@ void release_obj(rt_ctx ctx, Obj& o)
     hipStream_t fs = ctx->free_stream;
     if (o.scene) {
         Scene& s = *o.scene;
-        for (Scratch* p : {&s.lbvh_child, &s.tri4, &s.nodes, &s.node4, &s.v64, &s.refl, &s.surf, &s.s_ptr, &s.s_tris, &s.s_plane,
+        for (Scratch* p : {&s.lbvh_child, &s.tri4, &s.nodes, &s.node4, &s.verts, &s.refl, &s.surf, &s.s_ptr, &s.s_tris, &s.s_plane,
                            &s.s_box, &s.t_edge, &s.g_axes, &s.g_frame, &s.g_off, &s.g_tris, &s.mat,
                            &s.nrm, &s.box})
             retarget(*p, fs);
@@ -516,7 +516,7 @@ rt_status rt_scene_info(rt_ctx ctx, uint64_t scene, int64_t* n_tri, int64_t* n_s
         if (bvh_depth) *bvh_depth = sc.max_depth;
         if (bytes) {
             uint64_t b = 0;
-            for (const Scratch* p : {&sc.lbvh_child, &sc.tri4, &sc.nodes, &sc.node4, &sc.v64, &sc.refl, &sc.surf, &sc.s_ptr,
+            for (const Scratch* p : {&sc.lbvh_child, &sc.tri4, &sc.nodes, &sc.node4, &sc.verts, &sc.refl, &sc.surf, &sc.s_ptr,
                                      &sc.s_tris, &sc.s_plane, &sc.s_box, &sc.t_edge, &sc.g_axes,
                                      &sc.g_frame, &sc.g_off, &sc.g_tris, &sc.mat, &sc.nrm})
                 b += p->bytes;

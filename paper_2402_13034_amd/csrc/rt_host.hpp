@@ -128,7 +128,7 @@ struct Scene {
     int32_t max_depth = 0;    // of the scene's Morton tree (the depth a scene reports)
     int32_t walk_depth = 0;   // of the tree in nodes / node4
     Scratch lbvh_child;       // int32 [2 (n_tri - 1)]: the Morton tree, leaves as slots (lbvh_nodes)
-    Scratch tri4, nodes, node4, v64, refl, surf, s_ptr, s_tris, s_plane, s_box, t_edge;
+    Scratch tri4, nodes, node4, verts, refl, surf, s_ptr, s_tris, s_plane, s_box, t_edge;
     Scratch mat;   // float2 per triangle (eps_r, sigma), empty until set
     Scratch nrm;   // 3 doubles per triangle: unit normal, computed with the materials
     Scratch g_axes, g_frame, g_off, g_tris;
@@ -142,7 +142,6 @@ struct Scene {
         v.tri4 = tri4.as<float4>();
         v.nodes = nodes.as<float4>();
         v.node4 = node4.as<float4>();
-        v.v64 = v64.as<double>();
         v.refl = refl.as<float2>();
         v.mat = mat.bytes ? mat.as<float2>() : nullptr;
         v.nrm = nrm.bytes ? nrm.as<double>() : nullptr;

@@ -47,7 +47,6 @@ struct SceneView {
     const float4* tri4;    // 3 per leaf slot: (v0, id), (e1, surf), (e2, 0)
     const float4* nodes;   // 4 per internal node: (loL, cL), (hiL, cR), (loR, -), (hiR, -)
     const float4* node4;   // 8 per internal node of even depth (4-wide collapse), see RT_NODE4
-    const double* v64;     // 9 per triangle (original order)
     const float2* refl;    // per triangle
     const float2* mat;     // per triangle: relative permittivity, conductivity S/m (null: none set)
     const double* nrm;     // per triangle unit normal e1 x e2 / |e1 x e2| (FP64), set with the materials
@@ -62,15 +61,16 @@ struct SceneView {
     const int32_t* g_axes;   // per surface: the projection's axes | lg << 4; -1: no grid, scan every triangle
     const double* g_frame;   // 4 per surface: u0, v0, cells per unit along u and v
     const int32_t* g_off;    // cell c of surface sf lists [off[c], off[c + 1]) of the surface's part of g_tris,
-                             // off = g_off + RT_SGRID_CAP * s_ptr[sf] + sf
+                             // off = g_off + RT_SGRID_OFF * s_ptr[sf] + sf
     const int32_t* g_tris;   // surface sf's part: from RT_SGRID_CAP * s_ptr[sf] on
 };
 
 #define RT_PLANE 6
-#define RT_EDGE 16
-#define RT_SGRID_LO 2
+#define RT_EDGE 13
+#define RT_SGRID_LO 1
 #define RT_SGRID_HI 5
-#define RT_SGRID_CAP 16   // cells and list entries of a surface per triangle, at most
+#define RT_SGRID_OFF 4    // cells of a surface per triangle, at most (the fewest 4^lg that are as many as its triangles)
+#define RT_SGRID_CAP 16   // list entries of a surface per triangle, at most
 
 // Grid cell coordinate of x (monotone in x, clamped to the 2^lg cells)
 __host__ __device__ __forceinline__ int sgrid_index(double x, double origin, double per_unit, int lg)
@@ -1130,29 +1130,35 @@ __device__ inline void triangle_projection(const double* v, double* out, int32_t
 // lexicographically smaller end point and the edge vector from it, negated
 // where the test negates (exact either way), so that one formula
 //   w = dx (py - by) - dy (px - bx)
-// gives the test's value; and per edge the threshold it must exceed: 0, or,
-// for a top-left edge (0 counts as inside), the largest negative number.  The
-// test is then three edge functions of five operations and a compare; derived
-// from the vertices at every test it was some 75 vector instructions.
-// [0] the axis the projection drops (as an integer), then per edge bx, by, dx,
-// dy and the threshold (infinite for a degenerate triangle).
+// gives the test's value.  The test is then three edge functions of five
+// operations and a compare; derived from the vertices at every test it was some
+// 75 vector instructions.
+// [0] two integers, the axis the projection drops with the top-left edges in
+// bits 2..4, and its axes as triangle_projection gives them; then per edge bx,
+// by, dx, dy (dx = dy = 0 for a degenerate triangle: no value above 0).
 __device__ inline void triangle_edges(const double* q6, int32_t axes, double* out)
 {
 #pragma clang fp contract(off)
     const int i0 = axes & 3;   // kept axes are drop + 1, drop + 2
-    const long long drop = (i0 + 2) % 3;
-    __builtin_memcpy(&out[0], &drop, 8);
+    int32_t head[2] = {(i0 + 2) % 3, axes};
+    const bool none = (axes & 16) != 0;
     for (int i = 0; i < 3; ++i) {
         // edges b c, c a, a b
         const int u = (i + 1) % 3, v = (i + 2) % 3;
         const double sx = q6[2 * u], sy = q6[2 * u + 1], ex = q6[2 * v], ey = q6[2 * v + 1];
         const bool s_first = (sx < ex) || (sx == ex && sy < ey);
-        out[5 * i + 1] = s_first ? sx : ex;
-        out[5 * i + 2] = s_first ? sy : ey;
-        out[5 * i + 3] = s_first ? ex - sx : -(sx - ex);
-        out[5 * i + 4] = s_first ? ey - sy : -(sy - ey);
-        out[5 * i + 5] = (axes & 16) ? __builtin_inf() : (top_left(sx, sy, ex, ey) ? -4.9406564584124654e-324 : 0.0);
+        out[4 * i + 1] = s_first ? sx : ex;
+        out[4 * i + 2] = s_first ? sy : ey;
+        out[4 * i + 3] = none ? 0.0 : s_first ? ex - sx : -(sx - ex);
+        out[4 * i + 4] = none ? 0.0 : s_first ? ey - sy : -(sy - ey);
+        if (!none && top_left(sx, sy, ex, ey)) head[0] |= 4 << i;
     }
+    __builtin_memcpy(&out[0], head, 8);
+}
+
+__device__ __forceinline__ int edge_axes(const double* t_edge, int t)
+{
+    return ((const int*)(t_edge + RT_EDGE * (int64_t)t))[1];
 }
 
 // p on the triangle's plane inside triangle t?  Half-open top-left rule in
@@ -1167,15 +1173,20 @@ __device__ __forceinline__ bool contains_proj(const SceneView& s, int t, const d
 {
 #pragma clang fp contract(off)
     const double* e = s.t_edge + RT_EDGE * (int64_t)t;
-    const int drop = ((const int*)e)[0];
+    const int head = ((const int*)e)[0], drop = head & 3;
+    // what an edge's value has to exceed: 0, or the largest negative number (0 counts as inside)
+    auto above = [head](int i) {
+        const int tl = head >> (2 + i) & 1;
+        return __hiloint2double(tl << 31, tl);
+    };
     const double px = p[0], py = p[1], pz = p[2];
     const double q0 = drop == 0 ? py : drop == 1 ? pz : px;
     const double q1 = drop == 0 ? pz : drop == 1 ? px : py;
     const double w0 = e[3] * (q1 - e[2]) - e[4] * (q0 - e[1]);
-    if (!UNIFORM && !(w0 > e[5])) return false;
-    const double w1 = e[8] * (q1 - e[7]) - e[9] * (q0 - e[6]);
-    const double w2 = e[13] * (q1 - e[12]) - e[14] * (q0 - e[11]);
-    return w0 > e[5] && w1 > e[10] && w2 > e[15];
+    if (!UNIFORM && !(w0 > above(0))) return false;
+    const double w1 = e[7] * (q1 - e[6]) - e[8] * (q0 - e[5]);
+    const double w2 = e[11] * (q1 - e[10]) - e[12] * (q0 - e[9]);
+    return w0 > above(0) && w1 > above(1) && w2 > above(2);
 }
 
 __device__ __forceinline__ double plane_side(const double* pl, const double* p)
@@ -1202,8 +1213,8 @@ __device__ inline int surface_contains(const SceneView& s, int sf, const double*
         const double u = au == 0 ? px : au == 1 ? py : pz;
         const double v = av == 0 ? px : av == 1 ? py : pz;
         const int cell = (sgrid_index(u, fr[0], fr[2], lg) << lg) + sgrid_index(v, fr[1], fr[3], lg);
-        const int64_t b = (int64_t)RT_SGRID_CAP * s.s_ptr[sf];
-        const int32_t* off = s.g_off + b + sf + cell;
+        const int64_t first = s.s_ptr[sf], b = RT_SGRID_CAP * first;
+        const int32_t* off = s.g_off + RT_SGRID_OFF * first + sf + cell;
         const int end = off[1];
         for (int j = off[0]; j < end; ++j) {
             const int t = s.g_tris[b + j];

@@ -195,7 +195,6 @@ __global__ void k_morton(const float4* cent, const unsigned* bounds, int64_t nt,
 // (21 bits) above the code's upper 43 bits, word 0 its lower 20 bits above the
 // triangle index (29 bits).  Sorted stably on the surface bits alone.  Without
 // surfaces above the Morton order (plain, or too many of them) they are all 0.
-constexpr int RT_TOP_MAX = 8192;   // surfaces the split above them takes
 constexpr uint64_t RT_KEY_TRI = (1ull << 29) - 1;
 constexpr int RT_KEY_SURF_SHIFT = 43;   // in word 1
 __global__ void k_slot_keys(const uint64_t* keys, const int32_t* surf, int64_t nt, const int32_t* n_surf_p, int plain,
@@ -205,16 +204,16 @@ __global__ void k_slot_keys(const uint64_t* keys, const int32_t* surf, int64_t n
     if (i >= nt) return;
     const uint64_t t = keys[2 * i], code = keys[2 * i + 1];
     const int32_t sf = surf[t];
-    const uint64_t sc = plain || *n_surf_p > RT_TOP_MAX ? 0ull : (uint64_t)(sf < 0 ? 0 : (sf >= nt ? nt - 1 : sf));
+    const uint64_t sc = plain || !top_wanted(*n_surf_p) ? 0ull : (uint64_t)(sf < 0 ? 0 : (sf >= nt ? nt - 1 : sf));
     out[2 * i] = ((code & 0xfffffull) << 29) | t;
     out[2 * i + 1] = (sc << RT_KEY_SURF_SHIFT) | (code >> 20);
 }
 
 // Is there a tree above the surfaces' subtrees?  (Every id used: an unused one
 // is reported after the build.)
-__device__ __forceinline__ bool top_used(int n_surf, int seen, int plain)
+__device__ __forceinline__ bool top_used(int n_surf, int seen)
 {
-    return !plain && n_surf >= 2 && n_surf <= RT_TOP_MAX && seen == n_surf;
+    return top_wanted(n_surf) && seen == n_surf;
 }
 
 __device__ __forceinline__ int64_t clamp_index(int32_t v, int64_t n) { return v < 0 ? 0 : (v >= n ? n - 1 : v); }
@@ -446,7 +445,13 @@ __global__ __launch_bounds__(256) void k_refit_cross(const int32_t* cross, const
 // fit (up to TOP_RES surfaces).  Ranges are split level by level in one
 // workgroup, large ones by all its waves together: up to TOP_LEAF surfaces to
 // the end, beyond until they hold at most TOP_LEAF, and those go one workgroup
-// each over the device: 106 surfaces 67 us, 1566 surfaces 175 + 116 us.
+// each over the device: 106 surfaces 67 us, 1566 surfaces 175 + 116 us.  The
+// boxes of more surfaces than TOP_RES are gathered from memory at every level
+// (8192 surfaces 1074 + 138 us), so where surfaces are many and have few
+// triangles (top_full) the upper levels split groups of them instead: TOP_GROUP
+// consecutive ones along a Morton order, each group by a workgroup of its own
+// (8000 surfaces 220 us in all instead of 990, traces of 10^5 rays 800 instead of 774
+// us; 969 without a split).
 // Of the n Karras indices 0..n-1 over the slots (n - 1 is no node), a surface's
 // c triangles hold c, its subtree takes c - 1 of them and leaves one end free:
 // the index of a Karras node over several surfaces (the last surface leaves
@@ -454,9 +459,9 @@ __global__ __launch_bounds__(256) void k_refit_cross(const int32_t* cross, const
 // left (every position splits once), so the numbering needs neither a counter
 // nor room of its own.
 // --------------------------------------------------------------------------
-constexpr int TOP_BINS = 11, TOP_LEAF = 256, TOP_T = 1024, TOP_RES = 2048, TOP_FT = 512;
-constexpr int TOP_Q = TOP_LEAF / 2;   // ranges of a level: of two surfaces and more, or of more than TOP_LEAF
-static_assert(RT_TOP_MAX / (TOP_LEAF + 1) <= TOP_Q, "a level's ranges fit the queue");
+constexpr int TOP_BINS = 11, TOP_LEAF = 256, TOP_T = 1024, TOP_RES = RT_TOP_RES, TOP_FT = 512, TOP_GROUP = 64;
+constexpr int TOP_Q = TOP_LEAF / 2;   // ranges of a level: of two surfaces (or groups) and more, or of more than TOP_LEAF
+static_assert(RT_TOP_MAX / (TOP_LEAF + 1) <= TOP_Q && RT_TOP_MAX / TOP_GROUP / 2 <= TOP_Q, "a level's ranges fit the queue");
 
 struct TopOut {
     float4* nodes;
@@ -615,8 +620,9 @@ __device__ __forceinline__ void top_node(const TopOut& o, int m, int parent, int
 }
 
 // A range of two surfaces (about a third of all ranges): nothing to choose.
+template <class Single>
 __device__ __forceinline__ void top_pair(const TopBoxes sb, const uint16_t* idx, int a, int parent, int side,
-                                         const TopOut& o)
+                                         const TopOut& o, Single single)
 {
     const int s0 = idx[a], s1 = idx[a + 1];
     const float4 l0 = sb.get(2 * s0), h0 = sb.get(2 * s0 + 1), l1 = sb.get(2 * s1), h1 = sb.get(2 * s1 + 1);
@@ -624,8 +630,8 @@ __device__ __forceinline__ void top_pair(const TopBoxes sb, const uint16_t* idx,
     top_node(o, a + 1, parent, side, l, r);
     if ((threadIdx.x & 63) == 0) {
         const int id = o.ids[a];
-        top_link(o, id, 0, __float_as_int(h0.w));
-        top_link(o, id, 1, __float_as_int(h1.w));
+        single(s0, id, 0);
+        single(s1, id, 1);
     }
 }
 
@@ -701,8 +707,9 @@ __device__ __forceinline__ int top_split(const TopBoxes sb, uint16_t* idx, uint1
 // A workgroup's shared state: up to CAP surfaces, the boxes of RES, T threads.
 template <int CAP, int RES, int T, int Q>
 struct TopShared {
-    static constexpr int NW = T / 64;
-    uint16_t idx[CAP], tmp[CAP];
+    static constexpr int NW = T / 64, MAX = CAP;
+    alignas(16) uint16_t idx[CAP];
+    uint16_t tmp[CAP];
     int32_t ids[RES];
     float4 box[2 * RES];
     TopAcc part[NW][32];
@@ -720,16 +727,28 @@ __device__ __forceinline__ void top_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// The range in queue[0] split level by level until its parts hold at most `leaf` surfaces.
+// Where group g of n_group of n surfaces begins (and the one before it ends).
+__device__ __forceinline__ int top_group(int g, int n_group, int n) { return (int)((int64_t)g * n / n_group); }
+
+// The range in queue[0], of n_item in all, split level by level until its parts hold at most `leaf` surfaces.
+// n_group > 0: what is split are that many groups of n surfaces, and a single one goes to fin.
 template <class Shared>
-__device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n, int leaf, int4* fin, const TopOut& o)
+__device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n_item, int leaf, int n_group, int n,
+                                           int4* fin, const TopOut& o)
 {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     constexpr int NW = Shared::NW, T = NW * 64;
-    // a part of a split range: split again, left to a wave, or one surface (its link)
+    auto single = [&](int item, int parent, int side) {
+        if (n_group > 0)
+            fin[atomicAdd(&sh.nfin, 1)] =
+                make_int4(top_group(item, n_group, n), top_group(item + 1, n_group, n), parent, side);
+        else
+            top_link(o, parent, side, __float_as_int(sb.get(2 * item + 1).w));
+    };
+    // a part of a split range: split again, left to a workgroup, or one surface (its link) or group
     auto hand_on = [&](int a, int b, int parent, int side, int to) {
         if (b - a == 1)
-            top_link(o, parent, side, __float_as_int(sb.get(2 * sh.idx[a] + 1).w));
+            single(sh.idx[a], parent, side);
         else if (b - a > leaf)
             sh.queue[to][atomicAdd(&sh.nq[to], 1)] = make_int4(a, b, parent, side);
         else
@@ -739,11 +758,11 @@ __device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n,
         const int cnt = sh.nq[cur];
         if (cnt == 0) break;
         // few ranges: all waves price each together
-        const bool together = cnt <= 4 && n > 128 * cnt;
+        const bool together = cnt <= 4 && n_item > 128 * cnt;
         for (int e = together ? 0 : wave; e < cnt; e += together ? 1 : NW) {
             const int4 it = sh.queue[cur][e];
             if (it.y - it.x == 2) {
-                if (!together || wave == 0) top_pair(sb, sh.idx, it.x, it.z, it.w, o);
+                if (!together || wave == 0) top_pair(sb, sh.idx, it.x, it.z, it.w, o, single);
                 continue;
             }
             // one copy of the code for both (a cold instruction cache costs more than the arithmetic)
@@ -787,19 +806,105 @@ __device__ __forceinline__ void top_levels(Shared& sh, const TopBoxes sb, int n,
     }
 }
 
+// Surfaces in Morton order of their boxes' centres (a bitonic sort in LDS, in
+// the room of sh.idx and sh.tmp), and the boxes, triangle counts and node
+// indices of the n_group groups of them.  ce: this thread's extent of the
+// doubled centres.
+template <class Shared>
+__device__ __forceinline__ void top_groups(Shared& sh, int n, int n_group, float* ce, const float4* sb,
+                                           const int32_t* ids, int32_t* order_out)
+{
+    const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    constexpr int NW = Shared::NW, T = NW * 64;
+    static_assert(Shared::MAX >= RT_TOP_MAX && RT_TOP_MAX <= 1 << 13, "room for a key a surface, 13 bits for a surface");
+    uint32_t* keys = (uint32_t*)sh.idx;   // Morton code, 6 bits an axis, above the surface
+    for (int k = 0; k < 3; ++k) {
+        ce[k] = -wave_max(-ce[k]);
+        ce[3 + k] = wave_max(ce[3 + k]);
+    }
+    if (lane == 0)
+        for (int k = 0; k < 6; ++k) sh.ext[wave][k] = ce[k];
+    __syncthreads();   // the boxes in sb too
+    for (int w = 0; w < NW; ++w)
+        for (int k = 0; k < 3; ++k) {
+            ce[k] = fminf(ce[k], sh.ext[w][k]);
+            ce[3 + k] = fmaxf(ce[3 + k], sh.ext[w][3 + k]);
+        }
+    int n2 = 2;
+    while (n2 < n) n2 <<= 1;
+    for (int s = tid; s < n2; s += T) {
+        uint32_t key = 0xffffffffu;
+        if (s < n) {
+            const float4 lo = sb[2 * s], hi = sb[2 * s + 1];
+            const float v[3] = {lo.x + hi.x, lo.y + hi.y, lo.z + hi.z};
+            key = 0;
+            for (int k = 0; k < 3; ++k) {
+                const float ext = ce[3 + k] - ce[k];
+                const float u = ext > 0.0f ? (v[k] - ce[k]) / ext * 64.0f : 0.0f;
+                const uint32_t q = (uint32_t)fminf(fmaxf(u, 0.0f), 63.0f);
+                for (int b = 0; b < 6; ++b) key |= (q >> b & 1u) << (3 * b + 2 - k);
+            }
+            key = key << 13 | (uint32_t)s;
+        }
+        keys[s] = key;
+    }
+    for (int size = 2; size <= n2; size <<= 1)
+        for (int st = size >> 1; st > 0; st >>= 1) {
+            top_barrier();
+            for (int i = tid; i < n2 / 2; i += T) {
+                const int a = 2 * i - (i & (st - 1)), b = a + st;
+                const uint32_t x = keys[a], y = keys[b];
+                if ((x > y) == ((a & size) == 0)) {
+                    keys[a] = y;
+                    keys[b] = x;
+                }
+            }
+        }
+    top_barrier();
+    for (int i = tid; i < n; i += T) order_out[i] = (int32_t)(keys[i] & 8191u);
+    for (int g = wave; g < n_group; g += NW) {
+        const int a = top_group(g, n_group, n), b = top_group(g + 1, n_group, n);
+        float m[6] = {3e38f, 3e38f, 3e38f, -3e38f, -3e38f, -3e38f}, w = 0.0f;
+        for (int i = a + lane; i < b; i += 64) {
+            const int s = (int)(keys[i] & 8191u);
+            const float4 lo = sb[2 * s], hi = sb[2 * s + 1];
+            const float v[6] = {lo.x, lo.y, lo.z, hi.x, hi.y, hi.z};
+            for (int k = 0; k < 3; ++k) {
+                m[k] = fminf(m[k], v[k]);
+                m[3 + k] = fmaxf(m[3 + k], v[3 + k]);
+            }
+            w += lo.w;
+        }
+        for (int k = 0; k < 3; ++k) {
+            m[k] = -wave_max(-m[k]);
+            m[3 + k] = wave_max(m[3 + k]);
+        }
+        for (int d = 32; d > 0; d >>= 1) w += __shfl_xor(w, d, 64);
+        if (lane == 0) {
+            sh.box[2 * g] = make_float4(m[0], m[1], m[2], w);
+            sh.box[2 * g + 1] = make_float4(m[3], m[4], m[5], 0.0f);
+            sh.ids[g] = ids[b - 1];   // a group's own nodes take those of a .. b - 2
+        }
+    }
+    top_barrier();
+    for (int g = tid; g < n_group; g += T) sh.idx[g] = (uint16_t)g;
+}
+
 // Upper levels, one workgroup: the surfaces' subtree boxes into sb, ranges
-// split until they hold at most `leaf` surfaces; those go to fin (start, end,
-// parent, side) and the surfaces' order to order_out.
+// split until they hold at most TOP_LEAF surfaces; those go to fin (start, end,
+// parent, side) and the surfaces' order to order_out.  Or, grouped: the groups
+// split to the end, each of them to fin.
 __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const int32_t* n_surf_p,
-                                                     const int32_t* seen_p, const int2* range, const float* lbox,
-                                                     float4* sb, int32_t* ids, int32_t* order_out, int4* fin,
-                                                     int32_t* n_fin, TopOut o)
+                                                     const int32_t* seen_p, int64_t n_tri, const int2* range,
+                                                     const float* lbox, float4* sb, int32_t* ids, int32_t* order_out,
+                                                     int4* fin, int32_t* n_fin, TopOut o)
 {
     __shared__ TopShared<RT_TOP_MAX, TOP_RES, TOP_T, TOP_Q> sh;
     const int n = *n_surf_p;
-    if (!top_used(n, *seen_p, 0)) return;   // the same for every thread
-    const bool resident = n <= TOP_RES;
-    const int leaf = n <= TOP_LEAF ? 1 : TOP_LEAF;
+    if (!top_used(n, *seen_p)) return;   // the same for every thread
+    const bool grouped = !top_full(n, n_tri), resident = !grouped && n <= TOP_RES;
+    const int leaf = grouped || n <= TOP_LEAF ? 1 : TOP_LEAF;
+    float ce[6] = {3e38f, 3e38f, 3e38f, -3e38f, -3e38f, -3e38f};   // extent of the doubled centres
     for (int s = threadIdx.x; s < n; s += TOP_T) {
         // the surface's leaves are slots a..b-1; its subtree's node has index a or b - 1
         const int a = s_ptr[s], b = s_ptr[s + 1];
@@ -820,7 +925,7 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
             hi = make_float4(fmaxf(l1.x, r1.x), fmaxf(l1.y, r1.y), fmaxf(l1.z, r1.z), 0.0f);
         }
         hi.w = __int_as_float(ref);
-        if (leaf > 1) {
+        if (grouped || leaf > 1) {
             sb[2 * s] = lo;
             sb[2 * s + 1] = hi;
             ids[s] = free;
@@ -830,20 +935,31 @@ __global__ __launch_bounds__(TOP_T) void k_top_split(const int32_t* s_ptr, const
             sh.box[2 * s] = lo;
             sh.box[2 * s + 1] = hi;
         }
-        sh.idx[s] = (uint16_t)s;
+        if (grouped) {
+            const float v[3] = {lo.x + hi.x, lo.y + hi.y, lo.z + hi.z};
+            for (int k = 0; k < 3; ++k) {
+                ce[k] = fminf(ce[k], v[k]);
+                ce[3 + k] = fmaxf(ce[3 + k], v[k]);
+            }
+        } else {
+            sh.idx[s] = (uint16_t)s;
+        }
     }
+    const int n_group = grouped ? (n + TOP_GROUP - 1) / TOP_GROUP : 0;
+    if (grouped) top_groups(sh, n, n_group, ce, sb, ids, order_out);
+    const int n_item = grouped ? n_group : n;
     if (threadIdx.x == 0) {
         sh.nq[0] = 1;
         sh.nq[1] = 0;
         sh.nfin = 0;
-        sh.queue[0][0] = make_int4(0, n, -1, 0);
+        sh.queue[0][0] = make_int4(0, n_item, -1, 0);
     }
     __syncthreads();
-    o.ids = resident ? sh.ids : ids;
-    if (resident)
-        top_levels(sh, TopBoxes{sh.box}, n, leaf, fin, o);
+    o.ids = grouped || resident ? sh.ids : ids;
+    if (grouped || resident)
+        top_levels(sh, TopBoxes{sh.box}, n_item, leaf, n_group, n, fin, o);
     else
-        top_levels(sh, TopBoxes{sb}, n, leaf, fin, o);
+        top_levels(sh, TopBoxes{sb}, n_item, leaf, 0, n, fin, o);
     if (leaf > 1)
         for (int i = threadIdx.x; i < n; i += TOP_T) order_out[i] = sh.idx[i];
     if (threadIdx.x == 0) *n_fin = sh.nfin;
@@ -855,7 +971,7 @@ __global__ __launch_bounds__(TOP_FT) void k_top_finish(const int32_t* n_surf_p, 
                                                        const int4* fin, const int32_t* n_fin, TopOut o)
 {
     __shared__ TopShared<TOP_LEAF, TOP_LEAF, TOP_FT, TOP_Q> sh;
-    if (!top_used(*n_surf_p, *seen_p, 0) || (int)blockIdx.x >= *n_fin) return;   // the same for every thread
+    if (!top_used(*n_surf_p, *seen_p) || (int)blockIdx.x >= *n_fin) return;   // the same for every thread
     const int4 root = fin[blockIdx.x];
     const int a0 = root.x, cnt = root.y - a0;
     if ((int)threadIdx.x < cnt) {
@@ -872,7 +988,7 @@ __global__ __launch_bounds__(TOP_FT) void k_top_finish(const int32_t* n_surf_p, 
     }
     __syncthreads();
     o.ids = sh.ids;
-    top_levels(sh, TopBoxes{sh.box}, cnt, 1, nullptr, o);
+    top_levels(sh, TopBoxes{sh.box}, cnt, 1, 0, cnt, nullptr, o);
 }
 
 // 4-wide nodes: every internal node of even depth lists its
@@ -1455,7 +1571,7 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
             Scratch sb(c, sizeof(float4) * 2 * (size_t)ns, st), ids(c, sizeof(int32_t) * (size_t)ns, st),
                 order(c, sizeof(int32_t) * (size_t)ns, st), fin(c, sizeof(int4) * (size_t)ns, st);
             const TopOut to{s.nodes.as<float4>(), child.as<int32_t>(), pint.as<int32_t>(), troot, nullptr};
-            hipLaunchKernelGGL(k_top_split, dim3(1), dim3(TOP_T), 0, st, s.s_ptr.as<int32_t>(), nsurf, seen,
+            hipLaunchKernelGGL(k_top_split, dim3(1), dim3(TOP_T), 0, st, s.s_ptr.as<int32_t>(), nsurf, seen, nt,
                                range.as<int2>(), lbox.as<float>(), sb.as<float4>(), ids.as<int32_t>(),
                                order.as<int32_t>(), fin.as<int4>(), nfin, to);
             HIP_CHECK(hipGetLastError());
@@ -1503,7 +1619,7 @@ static void build_scene_as(Ctx& c, Scene& s, const float* V, int64_t nv, const i
     s.max_depth = depth;
     s.n_surf = n_surf;
     const int32_t wdepth = (int32_t)(hq[2] >> 32);
-    const bool top = !plain && n_surf >= 2 && n_surf <= RT_TOP_MAX;
+    const bool top = !plain && top_wanted(n_surf);
     s.walk_depth = wdepth;
     s.root = nt < 2 ? ~0 : top ? (int32_t)(hq[3] & 0xffffffff) : 0;
     if (top && (s.root < 0 || s.root >= nt - 1 || wdepth >= (1 << 20)))

@@ -16,6 +16,7 @@
 #include <string>
 
 #include "rt_fp64_core.hpp"
+#include "rt_rules.hpp"
 
 #define RT_MAX_K 5            // largest reflection order (keys of two 64-bit words above 3)
 #define RT_KM_SMALL 3        // orders up to this use one-word keys and the smaller kernel instances

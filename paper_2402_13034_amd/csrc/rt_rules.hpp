@@ -2,6 +2,7 @@
 // them, shared by the library and a host-side test that holds them against the
 // measured times of both ways.
 #pragma once
+#include <math.h>
 #include <stdint.h>
 
 #ifndef RT_HD
@@ -33,5 +34,28 @@ RT_HD inline bool top_wanted(int64_t n_surf) { return n_surf >= 2 && n_surf <= R
 // (592 of 1 616 / 631 / 560, 996 of 2 687 / 706 / 599) or thousand (3000 of 2 970 /
 // 1063 / 810, 8000 of 2 1235 / 1646 / 940).
 RT_HD inline bool top_full(int64_t n_surf, int64_t n_tri) { return n_surf <= 256 || n_tri >= 8 * n_surf; }
+
+// Discovery with four lanes per ray (k_discover_quad) instead of a wave walking
+// for 64 rays (k_discover)?  The wave visits the union of its rays' nodes, one
+// after the other: with few rays against the triangles that is many times a
+// ray's own nodes, and the launch has too few waves to hide the chain.  Its time
+// falls with the rays' density and grows with the order, as the first bounce
+// alone is coherent; four lanes a ray take 1.55 us per 1000 rays at any order.
+// The rays from which the wave is faster go with n_tri^0.4, by order (both
+// sources' kernels, us, wave / four lanes):
+//   order 1  1908 triangles 5 10^4 rays 93 / 100, 17 000 14 10^4 226 / 235,
+//            49 000 14 10^4 357 / 238, 2 10^5 258 / 320
+//   order 2  1908 7 10^4 189 / 139, 14 10^4 150 / 245; 17 000 14 10^4 519 / 252, 3 10^5 366 / 490
+//   order 3  1908 10^5 284 / 192, 2 10^5 267 / 339; 17 000 3 10^5 595 / 499, 4 10^5 528 / 645
+//   order 5  1908 2 10^5 1402 / 1090, 4 10^5 1292 / 1378
+// and from 5 10^5 on (10^6 rays and 1.08 million triangles 2614 / 4086).  What one line gives
+// up: an office floor's rays are coherent (103 000 triangles, order 2, 3 10^5
+// rays 364 / 493), clutter's are not (200 000, order 3, 6 10^5 2125 / 1017).
+inline bool sparse_rays(int64_t n_rays, int64_t n_tri, int order)
+{
+    const double by_order[4] = {2100.0, 4000.0, 6500.0, 12000.0};
+    const double most = by_order[order < 1 ? 0 : order > 4 ? 3 : order - 1] * pow((double)n_tri, 0.4);
+    return n_tri >= 64 && n_rays <= 500000 && (double)n_rays <= most;
+}
 
 }  // namespace rt

@@ -1622,21 +1622,6 @@ static void prepare_table(Ctx& c, const TraceArgs& a, Branch& br, hipStream_t st
     br.table = Scratch(c, sizeof(unsigned long long) * (size_t)key_words(a.tc.K) * (size_t)cap, st);
 }
 
-// Four lanes per ray (k_discover_quad) instead of a wave walking for 64 rays?
-// The wave walk visits the union of its rays' nodes, one after the other: with
-// few rays against the triangles that is many times a ray's own nodes, and the
-// launch has too few waves to hide the chain.  Its time falls with the rays'
-// density, that of the quads grows with the rays (1.3 ns a ray and bounce pair).
-// Both sources, us, wave / quad: 10^4 rays and 200 000 triangles 1204 / 76;
-// 10^5 and 49 000 747 / 203, and 1908 283 / 191 (order 3), and 848 115 / 187;
-// 2 10^5 and 17 000 317 / 336, and 49 000 708 / 347; 4 10^5 and 49 000 478 /
-// 642, and 200 000 1629 / 672; 10^6 and 1.08 million 2614 / 4086.  The line
-// between them runs near 4000 n_tri^0.4 rays, and below 5 10^5.
-static bool sparse_rays(int64_t n_rays, int64_t n_tri)
-{
-    return n_tri >= 64 && n_rays <= 500000 && (double)n_rays <= 4000.0 * std::pow((double)n_tri, 0.4);
-}
-
 template <int KM>
 static void cand_phase_a(Ctx& c, const SceneView& sv, int stk, const TraceArgs& a, bool brute, bool exhaustive,
                          bool keep_hits, Channel& ch, Branch& br, unsigned long long* d_segs)
@@ -1688,7 +1673,7 @@ static void cand_phase_a(Ctx& c, const SceneView& sv, int stk, const TraceArgs& 
         const int64_t n_launch = (rows + RT_FIB_CHUNK - 1) / RT_FIB_CHUNK * RT_FIB_CHUNK;
         const bool count = (a.tc.flags & 16) != 0 && !brute;
         if (br.ev_disc[0]) HIP_CHECK(hipEventRecord(br.ev_disc[0], st));
-        if (!brute && !count && sparse_rays(a.n_rays, sv.n_tri)) {
+        if (!brute && !count && sparse_rays(a.n_rays, sv.n_tri, K)) {
             SEL_STK(stk, hipLaunchKernelGGL((k_discover_quad<STK, KM>), dim3(nblk(4 * n_launch, DISC_B)), dim3(DISC_B),
                                             0, st, sv, src[0], src[1], src[2], perm, off, rows, hemi_n ? 1 : 0,
                                             hemi_n ? hemi_n[0] : 0.0, hemi_n ? hemi_n[1] : 0.0,

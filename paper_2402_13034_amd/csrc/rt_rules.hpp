@@ -58,4 +58,28 @@ inline bool sparse_rays(int64_t n_rays, int64_t n_tri, int order)
     return n_tri >= 64 && n_rays <= 500000 && (double)n_rays <= most;
 }
 
+// The matrix-core sum on tiles of 64 receivers x 64 configurations (k_sum_few)
+// instead of 256 rows (128 receivers) x 256?  kend: the contraction, M for real
+// Gamma, 2 M for complex.  A large tile is eight small ones and takes its CU 2.5
+// times as long as a small one (45 against 18 ns a k), and Gamma's own split
+// costs 8 us more.  While the large tiles leave CUs idle, four small tiles a CU
+// for every large one are still the faster way up to 512 k (4096 receivers x 127
+// complex: 29 against 37 us at 1024 configurations, 49 against 41 at 2048), two
+// above (1024 complex elements, 16384 receivers: 75 against 113 us at 100
+// configurations, 162 against 113 at 256).  Where the large ones fill the chip
+// each column of small tiles reads H's split again, so four are only faster up
+// to 256 k and 2^24 receivers x k (100 configurations, small / large: 32768
+// receivers x 127 complex 39 / 46 us, x 200 complex 55 / 51; 65536 x 127 complex 66 / 68,
+// x 331 real 89 / 78, x 256 complex 118 / 96).  Half as many for three products,
+// whose stages leave room for one workgroup a CU.
+inline bool small_tiles(int64_t R, int64_t C, int64_t kend, bool three, int64_t cus)
+{
+    const int64_t large = (2 * R + 255) / 256 * ((C + 255) / 256);
+    const int64_t small = (R + 63) / 64 * ((C + 63) / 64);
+    const bool filled = large >= cus && !three;
+    const bool four = kend <= 512 && (!filled || (kend <= 256 && R * kend < ((int64_t)1 << 24)));
+    const int64_t per = (four ? 4 : 2) / (three ? 2 : 1);
+    return small <= per * cus * ((large + cus - 1) / cus) && small < ((int64_t)1 << 31);
+}
+
 }  // namespace rt

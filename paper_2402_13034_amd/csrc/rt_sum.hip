@@ -787,23 +787,12 @@ struct SumShape {
     int64_t kp, rows_p, cols_p;
 };
 
-// Small tiles?  A large tile is eight small ones and takes its CU 2.5 times as
-// long as a small one (45 against 18 ns a k), and Gamma's own split costs 8 us
-// more.  Four small tiles a CU for every large one are still the faster way up
-// to 512 k (4096 receivers x 127 complex: 29 against 37 us at 1024
-// configurations, 49 against 41 at 2048; 65536 receivers: 59 against 63 us at
-// 65, 113 against 70 at 256), two above (1024 complex elements, 16384
-// receivers: 75 against 113 us at 100 configurations, 162 against 113 at 256);
-// half of that for three products, whose stages leave room for one workgroup
-// a CU.  Byte offsets into Gamma and into a tile of H's split are 32 bits.
-static bool few_tiles(const SumShape& sh, int64_t R, int64_t M, int64_t C, int64_t kend)
+// Byte offsets into Gamma and into a tile of H's split are 32 bits in k_sum_few.
+static bool few_tiles(int64_t R, int64_t M, int64_t C, int64_t kend, bool three)
 {
     if (C > ((int64_t)1 << 24) || M > ((int64_t)1 << 21) || 16 * C * (M + FK) >= ((int64_t)1 << 31)) return false;
-    const int64_t cus = cu_count();
-    const int64_t large = (sh.rows_p / G2M) * (sh.cols_p / G2N);
-    const int64_t small = (R + FR - 1) / FR * ((C + 63) / 64);
-    const int64_t per = (kend <= 512 ? 4 : 2) / (sh.three ? 2 : 1);
-    return small <= per * cus * ((large + cus - 1) / cus) && small < ((int64_t)1 << 31);
+    static_assert(FR == 64 && G2M == 256 && G2N == 256, "the tiles that small_tiles counts");
+    return small_tiles(R, C, kend, three, cu_count());
 }
 
 static SumShape sum_shape(int64_t R, int64_t M, int64_t C, bool gamma_real, int precision)
@@ -817,7 +806,7 @@ static SumShape sum_shape(int64_t R, int64_t M, int64_t C, bool gamma_real, int 
     sh.kp = round_up(kd > 0 ? kd : 1, GBK);
     sh.rows_p = round_up(2 * R, G2M);   // a multiple of both tile heights
     sh.cols_p = round_up(C, G2N);
-    sh.few = few_tiles(sh, R, M, C, kd);
+    sh.few = few_tiles(R, M, C, kd, sh.three);
     return sh;
 }
 

@@ -462,38 +462,56 @@ __global__ __launch_bounds__(RS_T) void k_rs_scatter(const uint64_t* keys, uint6
 // Up to RANK_MAX keys on at most 64 bits: a key's place is the number of keys
 // below it (and equal ones before it), counted.  A workgroup takes 64 keys, a
 // lane each, and its eight waves an eighth of the list, staged in LDS as the
-// bits that decide; n^2 / 64 lane steps in all, but spread over the chip, where
-// the passes of one workgroup follow each other: 2400 candidate keys 13 us where
-// those took 31, 1908 two-word Morton keys 10 for 35, 64 keys 2 for 6.
+// bits that decide (V: 32 or 64 of them), four to a read; n^2 / 64 lane steps in
+// all, but spread over the chip, where the passes of one workgroup follow each
+// other (2400 candidate keys 12 us where those took 41, 1908 two-word Morton
+// keys 11 for 34, 4096 keys of 20 bits 15 for 24, 64 keys 2 for 17).  One pass of that
+// one workgroup is the faster way beyond 1024 keys that differ in 8 bits at most
+// (4096: 15 us here, 11 there; the same for keys of few different digits,
+// which cannot be known ahead: 20 bits, five values 15 and 12).
 constexpr int RANK_T = 512;
 constexpr int64_t RANK_MAX = 4096;
-template <int W>
+template <int W, class V>
 __global__ __launch_bounds__(RANK_T) void k_sort_rank(const uint64_t* __restrict__ in, uint64_t* __restrict__ out, int n,
                                                       int begin, int len)
 {
-    extern __shared__ __attribute__((aligned(16))) uint64_t vals[];   // n
+    typedef V v4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char room[];   // n rounded up to 4
     __shared__ unsigned part[RANK_T / 64][64];
+    V* vals = (V*)room;
     const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int w = begin >> 6, sh = begin & 63;
+    const int w = begin >> 6, sh = begin & 63, n4 = (n + 3) & ~3;
 #pragma unroll 8
-    for (int i = tid; i < n; i += RANK_T) {
-        uint64_t v = in[(int64_t)i * W + w] >> sh;
-        if (sh && w + 1 < W) v |= in[(int64_t)i * W + w + 1] << (64 - sh);
-        vals[i] = len < 64 ? v & ((1ull << len) - 1ull) : v;
+    for (int i = tid; i < n4; i += RANK_T) {
+        uint64_t v = ~0ull;   // past the list: below no key
+        if (i < n) {
+            v = in[(int64_t)i * W + w] >> sh;
+            if (sh && w + 1 < W) v |= in[(int64_t)i * W + w + 1] << (64 - sh);
+            if (len < 64) v &= (1ull << len) - 1ull;
+        }
+        vals[i] = (V)v;
     }
     __syncthreads();
     const int own = (int)blockIdx.x * 64, i = own + lane;
-    const uint64_t mine = i < n ? vals[i] : 0ull;
-    const int per = (n + RANK_T / 64 - 1) / (RANK_T / 64);
-    const int j0 = wave * per, j1 = min(n, j0 + per);
+    const V mine = i < n ? vals[i] : 0;
+    const int per = (n4 / 4 + RANK_T / 64 - 1) / (RANK_T / 64) * 4;
+    const int j0 = wave * per, j1 = min(n4, j0 + per);
     unsigned rank = 0;
     // keys before this workgroup's, its own, those after
-    const int e0 = min(j1, own), e1 = min(j1, own + 64);
-#pragma unroll 8
-    for (int j = j0; j < e0; ++j) rank += vals[j] <= mine ? 1u : 0u;
+    const int e0 = min(j1, own), e1 = min(min(j1, own + 64), n);
+#pragma unroll 2
+    for (int j = j0; j < e0; j += 4) {
+        const v4 x = *(const v4*)&vals[j];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rank += x[k] <= mine ? 1u : 0u;
+    }
     for (int j = max(j0, own); j < e1; ++j) rank += vals[j] < mine || (vals[j] == mine && j < i) ? 1u : 0u;
-#pragma unroll 8
-    for (int j = max(j0, own + 64); j < j1; ++j) rank += vals[j] < mine ? 1u : 0u;
+#pragma unroll 2
+    for (int j = max(j0, own + 64); j < j1; j += 4) {
+        const v4 x = *(const v4*)&vals[j];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rank += x[k] < mine ? 1u : 0u;
+    }
     part[wave][lane] = rank;
     __syncthreads();
     if (wave == 0 && i < n) {
@@ -513,9 +531,15 @@ static void sort_keys_w(Ctx& c, uint64_t* in, uint64_t* out, int64_t n, int begi
         if (in != out) HIP_CHECK(hipMemcpyAsync(out, in, sizeof(uint64_t) * W * (size_t)n, hipMemcpyDeviceToDevice, st));
         return;
     }
-    if (n <= RANK_MAX && end - begin <= 64 && in != out) {
-        hipLaunchKernelGGL((k_sort_rank<W>), dim3(nblocks(n, 64)), dim3(RANK_T), sizeof(uint64_t) * (size_t)n, st, in,
-                           out, (int)n, begin, end - begin);
+    if (n <= RANK_MAX && end - begin <= 64 && (end - begin > 8 || n <= 1024) && in != out) {
+        const int len = end - begin;
+        const size_t room = (size_t)((n + 3) & ~(int64_t)3) * (len <= 32 ? sizeof(uint32_t) : sizeof(uint64_t));
+        if (len <= 32)
+            hipLaunchKernelGGL((k_sort_rank<W, uint32_t>), dim3(nblocks(n, 64)), dim3(RANK_T), room, st, in, out, (int)n,
+                               begin, len);
+        else
+            hipLaunchKernelGGL((k_sort_rank<W, uint64_t>), dim3(nblocks(n, 64)), dim3(RANK_T), room, st, in, out, (int)n,
+                               begin, len);
         HIP_CHECK(hipGetLastError());
         return;
     }

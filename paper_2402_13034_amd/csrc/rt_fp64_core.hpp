@@ -2,12 +2,16 @@
 // general operations: an estimate, refined until the last correction rounds
 // correctly (Markstein, "Computation of elementary functions on the IBM RISC
 // System/6000 processor", IBM J. R&D 34, 1990), so the results are those of
-// a / b, sqrt(x) and 1.0 / sqrt(x) wherever no intermediate leaves the normal
-// range: coordinates are at most 1e6 m and scene vertices are FP32 (products of
-// their differences stay above 1e-91).  A divisor with all 52 fraction bits set
-// is the method's one exception: its reciprocal may come out one unit below.
-// Shared by the kernels (estimates from
-// v_rcp_f64 and v_rsq_f64) and their host-side test.
+// a / b, sqrt(x) and 1.0 / sqrt(x) wherever the numbers and the residuals stay
+// normal.  Scene vertices are FP32 of at most 1e6 m (products of their
+// differences stay above 1e-91); the points a caller gives (antennas, receivers,
+// elements) are not bounded: legs from 1e-144 to 1.3e154 m are exact.  A shorter
+// one comes out shorter than any that is searched, a longer one as NaN where a
+// root would be infinite: blocked by nothing either way, and only the length of
+// such a kept path shows it.  A divisor with all 52 fraction bits set is the
+// method's one exception: its reciprocal may come out one unit below.
+// Shared by the kernels (estimates from v_rcp_f64 and v_rsq_f64) and their
+// host-side tests.
 #pragma once
 
 #ifndef RT_HD

@@ -248,7 +248,8 @@ SideStream::~SideStream()
 
 // ---- small read-backs through a pinned buffer ----
 // A kernel stores the values there: its launch costs the host 3 us where a copy
-// costs 8 (a trace waits for five of them).
+// costs 8 (a trace with a RIS waits for five: two candidate counts, two path
+// counts and the statistics; each two-word key set takes one more).
 constexpr int PINNED_N = 64;
 static int64_t* pinned_buf()
 {

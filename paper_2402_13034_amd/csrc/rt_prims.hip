@@ -223,7 +223,7 @@ void scan_i64(Ctx& c, const int64_t* in, int64_t* out, int64_t n, int64_t* d_tot
     scan_exclusive<int64_t, int64_t>(c, in, out, n, d_total, st);
 }
 
-// ctr, a and b cleared in one launch (a few kilobytes to a few megabytes; three
+// three arrays cleared in one launch (a few kilobytes to a few megabytes; three
 // fills before the first kernel of a trace otherwise)
 __global__ __launch_bounds__(256) void k_clear3(uint64_t* p0, int64_t n0, uint64_t* p1, int64_t n1, uint64_t* p2,
                                                 int64_t n2)

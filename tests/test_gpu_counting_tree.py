@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("sub,order,ris,disc", [
     (3, 2, [2049132, 539, 60969, 32258, 82821], [941116, 107376, 40000, 1277262, 116817, 40000]),
     (6, 1, [448939, 0, 22606, 11430, 20828], [558870, 40903, 20000, 677365, 42456, 20000]),
-    (1, 3, [4630300, 1721, 168930, 71120, 236284], [2967504, 381414, 119998, 3345144, 415278, 120000])])
+    (1, 3, [4630300, 1721, 168930, 71120, 236284], [1483752, 190707, 59999, 1672572, 207639, 60000])])
 def test_recorded_work(sub, order, ris, disc):
     from paper_2402_13034_amd import risrt
     p = synth.lab_room(nx=4, ny=4, sub=sub, n_rays=20_000, order=order)
